@@ -29,14 +29,17 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 PMC_SUMMARY = os.path.join(ROOT, "profiles", "sweep_line_source_P39_1000_{}_pmc.json")
-SWEEP_SRC = os.path.join(ROOT, "paper_1211_2205_amd", "csrc", "sweep.hip")
+SWEEP_SRC = [os.path.join(ROOT, "paper_1211_2205_amd", "csrc", f) for f in ("sweep.hip", "window.hip")]
 SIZE = {"fp64": 8, "fp32": 4, "bf16": 2}
 DTYPE = {"fp64": "f64", "fp32": "f32", "bf16": "bf16"}
 
 
 def _sweep_source_hash():
-    with open(SWEEP_SRC, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for path in SWEEP_SRC:
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
 
 
 def _pmc_record(precision, workload):

@@ -248,11 +248,13 @@ int starmap_diagnostics(const starmap_solver* s, double* mass_r00, double* l2, d
 int starmap_diagnostics_noalloc(const starmap_solver* s, double* mass_r00, double* l2, double* maxabs,
                                 int32_t* nonfinite);
 
-/* Tile variant of the sweep kernel: -1 chooses by the autotuner (default).
-   Variants differ in the spatial tile (tile_x x tile_y points) and in how
-   many planes of one order are held in registers while the next order loads
-   (fewer registers let more workgroups share a compute unit); all give the
-   same bits.  starmap_autotune times every variant that fits, at every
+/* Tile variant of the sweep kernel; by default chosen from the order, grid and
+   storage type at the first device call.
+   Variants differ in the spatial tile (tile_x x tile_y points) and, with FP64
+   storage, in where the window of input orders is kept: in LDS (and then in
+   how many planes of one order are held in registers while the next order
+   loads) or in registers alone, as with FP32 and BF16 storage in every
+   variant; all give the same bits.  starmap_autotune times every variant that fits, at every
    m-range width (4, 6, 8), on a few sweeps of this solver, keeps the fastest
    pair and writes it to the cache file named by the environment variable
    STARMAP_TUNE_CACHE (if set).  Variants are 0 .. starmap_variant_count()-1;
@@ -269,8 +271,9 @@ int starmap_autotune(starmap_solver* s, int32_t sweeps_per_variant);
 
 /* Width of the m ranges the sweep splits the outputs of one order into (an
    output (l, m) couples only to inputs (l -+ 1, m -+ 1), Lemma 2): 4, 6 or 8
-   (another value: STARMAP_EINVAL; the default is 8, or the autotuner's or
-   the tune cache's choice).  All widths give the same bits.  A width at
+   (another value: STARMAP_EINVAL; by default chosen from the order and the
+   tile at the first device call, or the autotuner's or the tune cache's
+   choice).  All widths give the same bits.  A width at
    which the current tile variant no longer fits the LDS fails with
    STARMAP_EINVAL and leaves the width unchanged. */
 int starmap_set_range_width(starmap_solver* s, int32_t width);

@@ -370,6 +370,10 @@ int fused_pass(starmap_solver* s, size_t off_in, size_t off_out, double tau_odd,
   return STARMAP_OK;
 }
 
+// Bytes of the register-window sweep's coefficient table (eight rows of zeros,
+// a row of eight per moment, eight rows of zeros).
+size_t win_coef_bytes(const starmap_solver* s) { return align256(size_t(s->nmom + 16) * 8 * s->csize); }
+
 void layout(starmap_solver* s) {
   // decay planes and source planes
   s->dmap = decay_map(s->N, s->anisotropic);
@@ -387,10 +391,14 @@ void layout(starmap_solver* s) {
   // on the tile.
   if (s->chunk_width <= 0) {
     s->chunk_width = kDefaultChunkWidth;
-    if (const char* w = std::getenv("STARMAP_CHUNK_WIDTH")) s->chunk_width = std::max(2, std::atoi(w));
+    if (const char* w = std::getenv("STARMAP_CHUNK_WIDTH")) {
+      s->chunk_width = std::max(2, std::atoi(w));
+      s->width_given = true;
+    }
   }
   s->nchunks = sweep_chunk_count(s->N, s->chunk_width);
-  for (int p = 0; p < 2; ++p) {
+  // (FP32 and BF16 sweeps read no programs)
+  for (int p = 0; p < 2 && s->storage == STORE_FP64; ++p) {
     s->prog_bytes[p] = 0;
     for (int w : kChunkWidths) {
       const SweepProgram pr =
@@ -413,6 +421,8 @@ void layout(starmap_solver* s) {
     s->off_prog[p] = off;
     off += s->prog_bytes[p];
   }
+  s->off_win = off;
+  off += win_coef_bytes(s) + align256(size_t(2 * (s->N + 1) + s->nmom) * 4);
   s->off_diag = off;
   int max_rows = s->ny + 1;
   s->diag_nblocks = diag_blocks(s->nmom, max_rows, s->diag_rows_per_block);
@@ -486,9 +496,41 @@ int upload_one_program(starmap_solver* s, const SweepProgram& pr, size_t region,
   return STARMAP_OK;
 }
 
+// Tables of the register-window sweep: per row eight coefficients (x couplings
+// to input order l - 1, index m + 1 and m - 1, then to order l + 1; y couplings
+// likewise; 0 where there is none), the decay planes of every order's rows, the
+// source plane of every moment.  The same for every tile and m-range width.
+int upload_window(starmap_solver* s) {
+  std::vector<double> cf(size_t(s->nmom + 16) * 8, 0.0);
+  std::vector<int32_t> tab(size_t(2 * (s->N + 1) + s->nmom), -1);
+  for (int k = 0; k < s->nmom; ++k) {
+    const MomentInfo& mk = s->moms[k];
+    const CouplingRow& r = s->rows[k];
+    auto place = [&](int j) { return (s->moms[j].l < mk.l ? 0 : 2) + (s->moms[j].m > mk.m ? 0 : 1); };
+    double* row = &cf[size_t(k + 8) * 8];
+    for (int t = 0; t < r.nx; ++t) row[place(r.x[t].col)] = -r.x[t].val / s->dx;
+    for (int t = 0; t < r.ny; ++t) row[4 + place(r.y[t].col)] = -r.y[t].val / s->dy;
+    tab[size_t(2 * mk.l + mk.imag)] = s->dmap.dk[k];
+    tab[size_t(2 * (s->N + 1) + k)] = s->qk[k] >= 0 ? s->nmom + s->qk[k] : -1;
+  }
+  const std::vector<float> cff(cf.begin(), cf.end());
+  const void* src = s->csize == 8 ? static_cast<const void*>(cf.data()) : static_cast<const void*>(cff.data());
+  HIP_TRY(hipMemcpyAsync(dptr(s, s->off_win), src, cf.size() * s->csize, hipMemcpyHostToDevice, s->stream));
+  HIP_TRY(hipMemcpyAsync(dptr(s, s->off_win + win_coef_bytes(s)), tab.data(), tab.size() * 4, hipMemcpyHostToDevice,
+                         s->stream));
+  HIP_TRY(hipStreamSynchronize(s->stream));
+  // decay planes that differ between the orders, or sources beyond the zeroth moment's
+  s->win_general = s->anisotropic || s->nsrc > (s->qk[0] >= 0 ? 1 : 0);
+  return STARMAP_OK;
+}
+
 int upload_program(starmap_solver* s) {
   ++s->graph_version;  // tiles, m ranges or LDS size may change: captured launches are stale
-  const TileShape ts = sweep_variant(s->variant);
+  if (sweep_in_registers(s->storage, s->variant)) {
+    s->prog_uploaded = true;
+    return STARMAP_OK;
+  }
+  const TileShape ts = sweep_variant(s->storage, s->variant);
   s->nchunks = sweep_chunk_count(s->N, s->chunk_width);
   for (int p = 0; p < 2; ++p) {
     s->prog[p] = build_sweep_program(s->N, p, ts.tx, ts.ty, s->dx, s->dy, s->rows, s->dmap, s->qk, s->nchunks);
@@ -592,22 +634,39 @@ int load_tune_cache(starmap_solver* s) {
           w >= 2) {
         found = v;
         s->chunk_width = w;
+        s->width_given = true;
       }
   }
   return found;
 }
 
-int default_variant(const starmap_solver* s) {
-  // largest-reuse tile that fits the LDS of one workgroup
-  int dev = 0;
-  int max_lds = 64 * 1024;
-  if (hipGetDevice(&dev) == hipSuccess) {
-    int v = 0;
-    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && v > 0) max_lds = v;
+// LDS planes that an LDS variant's programs of the current width need.
+int program_slots(const starmap_solver* s, int v) {
+  const TileShape ts = sweep_variant(s->storage, v);
+  int slots = 0;
+  for (int p = 0; p < 2; ++p)
+    slots = std::max(slots, build_sweep_program(s->N, p, ts.tx, ts.ty, s->dx, s->dy, s->rows, s->dmap, s->qk,
+                                                sweep_chunk_count(s->N, s->chunk_width)).slots);
+  return slots;
+}
+
+// Tile of a solver that was given none (and, unless it was given one, its
+// m-range width), from the sizes alone.
+int default_variant(starmap_solver* s) {
+  const double state = double(s->nmom) * double(s->plane_bytes_state());
+  int v = sweep_default_variant(s->storage, s->nx + 1 - s->px, s->ny + 1 - s->py, state);
+  if (!s->width_given) {
+    // (register windows of eight-byte values hold no more than four indices)
+    const bool narrow = s->storage == STORE_FP64 && sweep_in_registers(s->storage, v);
+    s->chunk_width = narrow ? 4 : sweep_default_width(s->N);
   }
-  for (int v = 0; v < sweep_variant_count(); ++v)
-    if (sweep_lds_bytes(v, s->slots, s->storage) <= size_t(max_lds)) return v;
-  return -1;
+  if (s->storage != STORE_FP64) return v;
+  // (a given width of eight: the tile of the same shape that holds ten planes)
+  if (!sweep_in_registers(s->storage, v) && s->chunk_width + 2 > sweep_variant(s->storage, v).cap) v = 2;
+  if (!sweep_in_registers(s->storage, v) &&
+      sweep_lds_bytes(v, program_slots(s, v), s->storage) > size_t(max_lds_bytes()))
+    v = sweep_default_variant(s->storage, 1, 1, 0.0);  // a tile without LDS
+  return v;
 }
 
 static_assert(COMBINE_MAX_TERMS >= STARMAP_MAX_FIELD_TERMS, "combine kernel holds every time factor");
@@ -772,6 +831,8 @@ int ensure_device(starmap_solver* s) {
     HIP_TRY(hipMemcpyAsync(dptr(s, off), geo.data(), geo.size() * 4, hipMemcpyHostToDevice, s->stream));
     HIP_TRY(hipStreamSynchronize(s->stream));
   }
+  rc = upload_window(s);
+  if (rc) return rc;
   if (s->variant < 0) {
     int v = load_tune_cache(s);
     if (v < 0) v = default_variant(s);
@@ -784,13 +845,38 @@ int ensure_device(starmap_solver* s) {
   return STARMAP_OK;
 }
 
-template <typename C>
+// One sweep by the kernel of the solver's variant.
 int launch_one(starmap_solver* s, int parity, double tau) {
-  SweepArgs<C> a;
-  const auto& pr = s->prog[parity];
   // a fused closure solver's even sweep reads the order-5 moments where the
   // last odd sweep wrote them
   const bool from_b = parity == 0 && s->closure && s->closure_fused && s->c5_flip;
+  const TileShape ts = sweep_variant(s->storage, s->variant);
+  if (sweep_in_registers(s->storage, s->variant)) {
+    WindowArgs w;
+    w.u = dptr(s, s->off_state);
+    w.decay = dptr(s, s->off_decay);
+    w.coef = dptr(s, s->off_win);
+    w.tab = reinterpret_cast<const int*>(dptr(s, s->off_win + win_coef_bytes(s)));
+    w.plane_stride = s->plane_stride;
+    w.pitch = s->pitch;
+    w.nx = s->nx;
+    w.ny = s->ny;
+    w.px = s->px;
+    w.py = s->py;
+    w.tx = ts.tx;
+    w.ty = ts.ty;
+    w.N = s->N;
+    w.nm = window_nm(s->N, s->chunk_width);
+    w.parity = parity;
+    w.strip = s->tile_strip;
+    w.general = s->win_general;
+    w.top_shift = from_b ? closure_plane_b(s) - closure_plane_a(s) : 0;
+    w.tau = tau;
+    HIP_TRY(launch_window(s->storage, w, s->stream));
+    return STARMAP_OK;
+  }
+  SweepArgs a;
+  const auto& pr = s->prog[parity];
   char* base = dptr(s, from_b ? s->off_prog_b : s->off_prog[parity]);
   size_t o = 0;
   a.chunks = reinterpret_cast<const int4*>(base + o);
@@ -801,24 +887,23 @@ int launch_one(starmap_solver* s, int parity, double tau) {
   o += align256(pr.loads.size() * 16);
   a.rows = reinterpret_cast<const int*>(base + o);
   o += align256(pr.rows.size() * 64);
-  a.rcoef = reinterpret_cast<const C*>(base + o);
-  a.u = dptr(s, s->off_state);
-  a.decay = reinterpret_cast<const C*>(dptr(s, s->off_decay));
+  a.rcoef = reinterpret_cast<const double*>(base + o);
+  a.u = reinterpret_cast<double*>(dptr(s, s->off_state));
+  a.decay = reinterpret_cast<const double*>(dptr(s, s->off_decay));
   a.plane_stride = s->plane_stride;
   a.pitch = s->pitch;
   a.nx = s->nx;
   a.ny = s->ny;
   a.px = s->px;
   a.py = s->py;
-  const TileShape ts = sweep_variant(s->variant);
   a.ntx = (s->nx + 1 + ts.tx - 1) / ts.tx;
   a.nty = (s->ny + 1 + ts.ty - 1) / ts.ty;
   a.nchunks = int(pr.chunks.size());
   a.zero_off = pr.zero_off;
   a.parity = parity;
   a.strip = s->tile_strip;
-  a.tau = C(tau);
-  HIP_TRY(launch_sweep(s->storage, s->variant, &a, s->slots, s->stream));
+  a.tau = tau;
+  HIP_TRY(launch_sweep(s->variant, a, s->slots, s->stream));
   return STARMAP_OK;
 }
 
@@ -840,8 +925,7 @@ int sweep(starmap_solver* s, int parity, double tau, bool with_closure = true) {
     }
     HIP_TRY(hipEventRecord(s->ev[s->ev_used], s->stream));
   }
-  int rc = fused_closure ? closure_odd_sweep(s, tau)
-           : s->storage == STORE_FP64 ? launch_one<double>(s, parity, tau) : launch_one<float>(s, parity, tau);
+  int rc = fused_closure ? closure_odd_sweep(s, tau) : launch_one(s, parity, tau);
   if (rc) return rc;
   if (s->profiling) {
     HIP_TRY(hipEventRecord(s->ev[s->ev_used + 1], s->stream));
@@ -1533,6 +1617,9 @@ int starmap_set_variant(starmap_solver* s, int32_t v) {
       int x = 0;
       if (hipDeviceGetAttribute(&x, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && x > 0) max_lds = x;
     }
+    // (under a register-window variant no program of the current width is built)
+    if (s->device_ready && sweep_in_registers(s->storage, s->variant) && !sweep_in_registers(s->storage, v))
+      s->slots = program_slots(s, v);
     if (sweep_lds_bytes(v, s->slots, s->storage) > size_t(max_lds))
       return fail(STARMAP_EINVAL, "tile variant does not fit the LDS for this moment order");
   }
@@ -1560,6 +1647,7 @@ int starmap_set_range_width(starmap_solver* s, int32_t width) {
     return fail(STARMAP_EINVAL, "unsupported m-range width");
   const int keep = s->chunk_width;
   s->chunk_width = width;
+  s->width_given = true;
   s->nchunks = sweep_chunk_count(s->N, width);
   if (!s->device_ready) return STARMAP_OK;
   int rc = upload_program(s);
@@ -1582,7 +1670,7 @@ int starmap_get_variant(const starmap_solver* s, int32_t* v, int32_t* tx, int32_
   if (!s) return fail(STARMAP_EINVAL, "solver is NULL");
   if (v) *v = s->variant;
   if (s->variant >= 0) {
-    TileShape t = sweep_variant(s->variant);
+    TileShape t = sweep_variant(s->storage, s->variant);
     if (tx) *tx = t.tx;
     if (ty) *ty = t.ty;
   } else {
@@ -1613,14 +1701,19 @@ int starmap_autotune(starmap_solver* s, int32_t sweeps) {
   int best = -1, best_w = s->chunk_width;
   float best_ms = 0.f;
   const int keep = s->variant, keep_w = s->chunk_width;
-  std::vector<int> tried;
+  std::vector<std::pair<bool, int>> tried;
   for (int w : kChunkWidths) {
     if (rc) break;
-    const int nch = sweep_chunk_count(s->N, w);
-    if (std::find(tried.begin(), tried.end(), nch) != tried.end()) continue;  // same split as a narrower width
-    tried.push_back(nch);
+    // a width that splits the orders as a narrower one does is not timed again
+    bool again[2];
+    for (int reg = 0; reg < 2; ++reg) {
+      const std::pair<bool, int> split{reg != 0, reg ? window_nm(s->N, w) : sweep_chunk_count(s->N, w)};
+      again[reg] = std::find(tried.begin(), tried.end(), split) != tried.end();
+      tried.push_back(split);
+    }
     s->chunk_width = w;
     for (int v = 0; v < sweep_variant_count() && !rc; ++v) {
+      if (again[sweep_in_registers(s->storage, v) ? 1 : 0]) continue;
       s->variant = v;
       // slots depend on the width: build first, then check the LDS
       rc = upload_program(s);
@@ -1642,7 +1735,7 @@ int starmap_autotune(starmap_solver* s, int32_t sweeps) {
       float ms = 0.f;
       HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
       if (std::getenv("STARMAP_VERBOSE")) {
-        const TileShape ts = sweep_variant(v);
+        const TileShape ts = sweep_variant(s->storage, v);
         std::fprintf(stderr, "starmap autotune: width %d variant %d (%dx%d) %.3f ms per sweep pair\n", w, v, ts.tx,
                      ts.ty, ms / sweeps);
       }
@@ -1664,6 +1757,7 @@ int starmap_autotune(starmap_solver* s, int32_t sweeps) {
   if (best < 0) return fail(STARMAP_ENOMEM, "no sweep tile fits the LDS for this moment order");
   s->variant = best;
   s->chunk_width = best_w;
+  s->width_given = true;
   rc = upload_program(s);
   if (rc) return rc;
   if (const char* path = std::getenv("STARMAP_TUNE_CACHE")) {
@@ -1779,6 +1873,7 @@ struct BatchPlan {
   std::vector<int> first;    // workgroup prefix (order.size() + 1 values)
   size_t tab0 = 0;           // first table entry of the plan
   size_t first0 = 0;         // first prefix value of the plan in the table's int array
+  bool general = false;      // register-window sweeps: an instance needs the general kernel
 };
 }  // namespace detail
 }  // namespace starmap
@@ -1822,9 +1917,11 @@ struct starmap_batch {
 namespace starmap {
 namespace detail {
 
-size_t batch_table_bytes(int count, int ngroups) {
-  return align256(size_t(count) * sizeof(BatchEntry)) + size_t(count + ngroups) * 4;
-}
+// The batch's device table: BatchEntry[count], WindowEntry[count] (an instance
+// has the one of its group's kernel), the plans' workgroup prefixes.
+size_t batch_window_offset(int count) { return align256(size_t(count) * sizeof(BatchEntry)); }
+size_t batch_first_offset(int count) { return batch_window_offset(count) + align256(size_t(count) * sizeof(WindowEntry)); }
+size_t batch_table_bytes(int count, int ngroups) { return batch_first_offset(count) + size_t(count + ngroups) * 4; }
 size_t closure_table_bytes(int count) {
   return align256(size_t(count) * sizeof(ClosureInst)) + size_t(count + 1) * 4;
 }
@@ -1870,9 +1967,10 @@ int group_prepare(starmap_batch* b, BatchGroup& g, int variant, int width) {
     starmap_solver* s = b->inst[i];
     s->variant = variant;
     s->chunk_width = width;
+    s->width_given = true;
     rc = upload_program(s);
     if (rc) return rc;
-    if (s->prog[0].chunks.size() != s->prog[1].chunks.size())
+    if (!sweep_in_registers(b->storage, variant) && s->prog[0].chunks.size() != s->prog[1].chunks.size())
       return fail(STARMAP_ESTATE, "sweep programs of the two parities differ in m ranges");
     slots = std::max(slots, s->slots);
   }
@@ -1881,9 +1979,10 @@ int group_prepare(starmap_batch* b, BatchGroup& g, int variant, int width) {
   g.width = width;
   g.slots = slots;
   drop_graph(b);
+  if (sweep_in_registers(b->storage, variant)) return STARMAP_OK;
   if (sweep_lds_bytes(variant, slots, b->storage) > size_t(max_lds_bytes()))
     return fail(STARMAP_EINVAL, "tile variant does not fit the LDS for the moment order of a batch group");
-  HIP_TRY(prepare_sweep(b->storage, variant, slots));
+  HIP_TRY(prepare_sweep(variant, slots));
   return STARMAP_OK;
 }
 
@@ -1905,7 +2004,11 @@ int batch_ready(starmap_batch* b) {
 }
 
 int items_of(const starmap_solver* s) {
-  const TileShape ts = sweep_variant(s->variant);
+  const TileShape ts = sweep_variant(s->storage, s->variant);
+  if (sweep_in_registers(s->storage, s->variant)) {
+    const WindowGrid g = window_grid(s->nx, s->ny, s->px, s->py, ts.tx, ts.ty, s->N, window_nm(s->N, s->chunk_width));
+    return g.ntx * g.nty * g.nchunks;
+  }
   const int ntx = (s->nx + 1 + ts.tx - 1) / ts.tx, nty = (s->ny + 1 + ts.ty - 1) / ts.ty;
   return ntx * nty * int(s->prog[0].chunks.size());
 }
@@ -1941,8 +2044,10 @@ int batch_table(starmap_batch* b, const std::vector<int>& sweeps, bool zero_tau)
       b->plans.push_back(pl);
     }
   }
-  if (b->merged && ng > 1) HIP_TRY(prepare_sweep(b->storage, b->plans[0].variant, b->plans[0].slots));
+  if (b->merged && ng > 1 && !sweep_in_registers(b->storage, b->plans[0].variant))
+    HIP_TRY(prepare_sweep(b->plans[0].variant, b->plans[0].slots));
   std::vector<BatchEntry> tab;
+  std::vector<WindowEntry> wtab;
   std::vector<int> firsts;
   for (auto& g : b->plans) {
     std::vector<int> ord;
@@ -1954,14 +2059,43 @@ int batch_table(starmap_batch* b, const std::vector<int>& sweeps, bool zero_tau)
     g.order = ord;
     g.nsweeps.assign(ord.size(), 0);
     g.first.assign(ord.size() + 1, 0);
+    g.general = false;
     int64_t total = 0;
     for (size_t r = 0; r < ord.size(); ++r) {
       starmap_solver* s = b->inst[ord[r]];
       BatchEntry e;
       std::memset(&e, 0, sizeof(e));
+      WindowEntry w;
+      std::memset(&w, 0, sizeof(w));
+      const bool reg = sweep_in_registers(s->storage, s->variant);
+      const TileShape ts = sweep_variant(s->storage, s->variant);
+      if (reg) {
+        w.u = dptr(s, s->off_state);
+        w.decay = dptr(s, s->off_decay);
+        w.coef = dptr(s, s->off_win);
+        w.tab = reinterpret_cast<const int*>(dptr(s, s->off_win + win_coef_bytes(s)));
+        w.plane_stride = s->plane_stride;
+        w.tau_full = zero_tau ? 0.0 : s->dt;
+        w.tau_half = zero_tau ? 0.0 : 0.5 * s->dt;
+        w.pitch = s->pitch;
+        w.nx = s->nx;
+        w.ny = s->ny;
+        w.px = s->px;
+        w.py = s->py;
+        w.N = s->N;
+        w.nm = window_nm(s->N, s->chunk_width);
+        const WindowGrid wg = window_grid(s->nx, s->ny, s->px, s->py, ts.tx, ts.ty, s->N, w.nm);
+        w.nchunks = wg.nchunks;
+        w.ntx = wg.ntx;
+        w.nty = wg.nty;
+        w.strip = s->tile_strip;
+        w.nsweeps = sweeps[ord[r]];
+        w.top_shift = (s->closure && b->closure_fused) ? closure_plane_b(s) - closure_plane_a(s) : 0;
+        g.general = g.general || s->win_general;
+      }
       e.u = dptr(s, s->off_state);
       e.decay = dptr(s, s->off_decay);
-      for (int p = 0; p < 2; ++p) {
+      for (int p = 0; p < 2 && !reg; ++p) {
         const auto& pr = s->prog[p];
         char* base = dptr(s, s->off_prog[p]);
         size_t o = 0;
@@ -1984,7 +2118,6 @@ int batch_table(starmap_batch* b, const std::vector<int>& sweeps, bool zero_tau)
       e.ny = s->ny;
       e.px = s->px;
       e.py = s->py;
-      const TileShape ts = sweep_variant(s->variant);
       e.ntx = (s->nx + 1 + ts.tx - 1) / ts.tx;
       e.nty = (s->ny + 1 + ts.ty - 1) / ts.ty;
       e.nchunks = int(s->prog[0].chunks.size());
@@ -1992,6 +2125,7 @@ int batch_table(starmap_batch* b, const std::vector<int>& sweeps, bool zero_tau)
       e.strip = s->tile_strip;
       e.even_b_delta = (s->closure && b->closure_fused) ? int64_t(s->off_prog_b) - int64_t(s->off_prog[0]) : 0;
       tab.push_back(e);
+      wtab.push_back(w);
       g.nsweeps[r] = sweeps[ord[r]];
       g.first[r] = int(total);
       total += items_of(s);
@@ -2002,7 +2136,8 @@ int batch_table(starmap_batch* b, const std::vector<int>& sweeps, bool zero_tau)
   }
   std::vector<char> buf(batch_table_bytes(count, ng), 0);
   std::memcpy(buf.data(), tab.data(), tab.size() * sizeof(BatchEntry));
-  std::memcpy(buf.data() + align256(size_t(count) * sizeof(BatchEntry)), firsts.data(), firsts.size() * 4);
+  std::memcpy(buf.data() + batch_window_offset(count), wtab.data(), wtab.size() * sizeof(WindowEntry));
+  std::memcpy(buf.data() + batch_first_offset(count), firsts.data(), firsts.size() * 4);
   HIP_TRY(hipMemcpyAsync(b->dtab, buf.data(), buf.size(), hipMemcpyHostToDevice, b->stream));
   if (b->closure) {
     // the closure sweep's instances in the (single) group's order, with their block prefix
@@ -2039,12 +2174,25 @@ int batch_table(starmap_batch* b, const std::vector<int>& sweeps, bool zero_tau)
   return STARMAP_OK;
 }
 
+// Sweep j of plan g's first na instances on a stream.
+int launch_plan(starmap_batch* b, const BatchPlan& g, int na, int j, hipStream_t stream) {
+  const int count = int(b->inst.size());
+  char* base = static_cast<char*>(b->dtab);
+  const int* first = reinterpret_cast<const int*>(base + batch_first_offset(count)) + g.first0;
+  if (sweep_in_registers(b->storage, g.variant)) {
+    const TileShape ts = sweep_variant(b->storage, g.variant);
+    const WindowEntry* tab = reinterpret_cast<const WindowEntry*>(base + batch_window_offset(count)) + g.tab0;
+    HIP_TRY(launch_window_batch(b->storage, tab, first, na, g.first[na], j, ts.tx, ts.ty, g.general, stream));
+  } else {
+    const BatchEntry* tab = reinterpret_cast<const BatchEntry*>(base) + g.tab0;
+    HIP_TRY(launch_sweep_batch(g.variant, tab, first, na, g.first[na], j, g.slots, stream));
+  }
+  return STARMAP_OK;
+}
+
 // Queue sweeps j0 .. j1-1 of the current table on the batch stream: one
 // launch per plan with instances still running (only plan `only` if >= 0).
 int batch_launch(starmap_batch* b, int j0, int j1, int only = -1) {
-  const BatchEntry* tab = reinterpret_cast<const BatchEntry*>(b->dtab);
-  const int* firsts =
-      reinterpret_cast<const int*>(static_cast<char*>(b->dtab) + align256(b->inst.size() * sizeof(BatchEntry)));
   for (int j = j0; j < j1; ++j) {
     if (b->closure && (j & 1) == 0) {
       // odd sweep of closure solvers: the network and the odd update in one
@@ -2070,8 +2218,8 @@ int batch_launch(starmap_batch* b, int j0, int j1, int only = -1) {
       int na = int(g.nsweeps.size());
       while (na > 0 && g.nsweeps[na - 1] <= j) --na;
       if (na == 0) continue;
-      HIP_TRY(launch_sweep_batch(b->storage, g.variant, tab + g.tab0, firsts + g.first0, na, g.first[na], j,
-                                 g.slots, b->stream));
+      int rc = launch_plan(b, g, na, j, b->stream);
+      if (rc) return rc;
     }
   }
   return STARMAP_OK;
@@ -2104,9 +2252,6 @@ double plan_work(const starmap_batch* b, const BatchPlan& g) {
 // fill the machine while another's drain.
 int batch_launch_all(starmap_batch* b, int j0, int j1) {
   if (b->closure || b->plans.size() == 1) return batch_launch(b, j0, j1);
-  const BatchEntry* tab = reinterpret_cast<const BatchEntry*>(b->dtab);
-  const int* firsts =
-      reinterpret_cast<const int*>(static_cast<char*>(b->dtab) + align256(b->inst.size() * sizeof(BatchEntry)));
   // the plans with the most work first: the chains start one after another
   // as the machine frees up, and the longest one bounds the run
   std::vector<int> ord(b->plans.size());
@@ -2123,8 +2268,8 @@ int batch_launch_all(starmap_batch* b, int j0, int j1) {
       int na = int(g.nsweeps.size());
       while (na > 0 && g.nsweeps[na - 1] <= j) --na;
       if (na == 0) continue;
-      HIP_TRY(launch_sweep_batch(b->storage, g.variant, tab + g.tab0, firsts + g.first0, na, g.first[na], j,
-                                 g.slots, b->gstream[gi]));
+      int rc = launch_plan(b, g, na, j, b->gstream[gi]);
+      if (rc) return rc;
     }
   for (size_t gi = 0; gi < b->plans.size(); ++gi) {
     HIP_TRY(hipEventRecord(b->gdone[gi], b->gstream[gi]));
@@ -2310,6 +2455,7 @@ int starmap_batch_run(starmap_batch* b, int32_t use_graph) {
       // the graph depends on every group's tile (kernel, LDS, programs) and
       // on the launch plans
       std::vector<int> key{b->merged ? 1 : 0, b->closure_fused ? 1 : 0};
+      for (const auto& g : b->plans) key.push_back(g.general ? 1 : 0);
       for (const auto& g : b->groups) key.insert(key.end(), {g.variant, g.width, g.slots});
       for (const auto& g : b->plans) {
         key.insert(key.end(), {g.variant, g.slots, int(g.nsweeps.size())});
@@ -2394,12 +2540,16 @@ int starmap_batch_autotune(starmap_batch* b, int32_t sweeps) {
     BatchGroup& g = b->groups[gi];
     int best_v = -1, best_w = 0;
     float best_ms = 0.f;
-    std::vector<int> tried;
+    std::vector<std::pair<bool, int>> tried;
     for (int w : kChunkWidths) {
-      const int split = sweep_chunk_count(g.N, w);
-      if (std::find(tried.begin(), tried.end(), split) != tried.end()) continue;  // same m ranges as a narrower width
-      tried.push_back(split);
+      bool again[2];  // same m ranges as a narrower width, by kernel
+      for (int reg = 0; reg < 2; ++reg) {
+        const std::pair<bool, int> split{reg != 0, reg ? window_nm(g.N, w) : sweep_chunk_count(g.N, w)};
+        again[reg] = std::find(tried.begin(), tried.end(), split) != tried.end();
+        tried.push_back(split);
+      }
       for (int v = 0; v < sweep_variant_count(); ++v) {
+        if (again[sweep_in_registers(b->storage, v) ? 1 : 0]) continue;
         // LDS check before the kernels are opted in
         int slots = 0;
         for (int i : g.members) {
@@ -2431,7 +2581,7 @@ int starmap_batch_autotune(starmap_batch* b, int32_t sweeps) {
         ms /= float(sweeps);
         times[gi][{v, w}] = ms;
         if (verbose) {
-          const TileShape ts = sweep_variant(v);
+          const TileShape ts = sweep_variant(b->storage, v);
           std::fprintf(stderr, "starmap batch autotune: N %d width %d variant %d (%dx%d) %.3f ms per sweep pair\n",
                        g.N, w, v, ts.tx, ts.ty, ms);
         }

@@ -9,16 +9,30 @@ namespace starmap {
 
 enum StorageType : int { STORE_FP64 = 0, STORE_FP32 = 1, STORE_BF16 = 2 };
 
-// Kernel arguments of one parity sweep (passed by value).
-template <typename C>
+// Tile variants.  FP32 and BF16 solvers run every variant with the window of
+// input orders in registers (window.hip); FP64 solvers run some so and the
+// others with the window staged in LDS (sweep.hip).
+struct TileShape {
+  int tx, ty;
+  int cap;  // LDS window: planes of one staged order and output rows per order held in registers; 0: register window
+};
+int sweep_variant_count();
+TileShape sweep_variant(int storage, int v);
+inline bool sweep_in_registers(int storage, int v) { return sweep_variant(storage, v).cap == 0; }
+// Variant of a solver that was given none, by its points per axis and the bytes
+// of its state, and its m-range width.
+int sweep_default_variant(int storage, int cols, int rows, double state_bytes);
+int sweep_default_width(int N);
+
+// Kernel arguments of one FP64 parity sweep with the window in LDS.
 struct SweepArgs {
-  void* u;                 // state planes, then source planes, storage type
-  const C* decay;          // decay planes c(x, y), compute type
+  double* u;               // state planes, then source planes
+  const double* decay;     // decay planes c(x, y)
   const int4* chunks;      // (order0, order1, -, -) per m range
   const int4* orders;      // (load0, load1, row0, row1) per output order
   const int4* loads;       // (k, lds offset, ox, oy)
   const int* rows;         // 16 ints per row: k, gslot, dk, source LDS offset, xo[4], yo[4], unused[4]
-  const C* rcoef;          // 8 coefficients per row (x couplings, then y couplings)
+  const double* rcoef;     // 8 coefficients per row (x couplings, then y couplings)
   int64_t plane_stride;    // elements between consecutive planes
   int pitch;               // elements between rows
   int nx, ny, px, py;      // cells per axis, periodicity flags
@@ -27,34 +41,25 @@ struct SweepArgs {
   int zero_off;            // LDS element offset of the zero plane
   int parity;              // 0: outputs on G11/G22, 1: outputs on G21/G12
   int strip;               // tile rows per strip of the tile order (<= 1: row by row)
-  C tau;                   // sub-step length
+  double tau;              // sub-step length
 };
 
-struct TileShape {
-  int tx, ty;
-  int cap;  // planes of one staged order and output rows per order held in registers
-};
-
-// Tile shapes compiled into the library (index = variant id).
-int sweep_variant_count();
-TileShape sweep_variant(int v);
-
-// LDS bytes a variant needs for slots planes of the given storage type.
+// LDS bytes a variant needs for slots planes (0: register window).
 size_t sweep_lds_bytes(int v, int slots, int storage);
 
-// Launch one sweep; args.u etc. must be device pointers.  Returns a HIP error.
-hipError_t launch_sweep(int storage, int variant, const void* args, int slots, hipStream_t stream);
+// Launch one sweep; pointers must be device pointers.  Returns a HIP error.
+hipError_t launch_sweep(int variant, const SweepArgs& a, int slots, hipStream_t stream);
 
-// One instance of a batched run: device pointers of its state, decay planes
+// One instance of a batched run of LDS sweeps: device pointers of its state, decay planes
 // and the sweep programs of both parities, and its scalars.
 struct BatchEntry {
   void* u;
-  const void* decay;  // compute type
+  const void* decay;
   const int4* chunks[2];
   const int4* orders[2];
   const int4* loads[2];
   const int* rows[2];
-  const void* rcoef[2];  // compute type
+  const void* rcoef[2];
   int64_t plane_stride;
   double tau_full, tau_half;  // dt and dt / 2
   int pitch, nx, ny, px, py, ntx, nty, nchunks;
@@ -66,14 +71,51 @@ struct BatchEntry {
   int64_t even_b_delta;
 };
 
-// Opts the kernels of a variant in to the LDS it needs (outside any stream
+// One parity sweep with the window of input orders in registers (window.hip).
+struct WindowArgs {
+  void* u;            // state planes, then source planes, storage type
+  const void* decay;  // decay planes, compute type
+  const void* coef;   // (8 + moments + 8) x 8 coefficients by row, compute type
+  const int* tab;     // 2 (N + 1) decay planes of the orders' R and I rows, then per moment its source plane or -1
+  int64_t plane_stride;
+  int pitch, nx, ny, px, py;
+  int tx, ty;         // tile, points
+  int N, nm;          // order; m ranges of 2 nm indices (nm = 2, 3 or 4)
+  int parity, strip;
+  int general;        // decay planes that differ between orders >= 1, or sources beyond the zeroth moment's
+  int top_shift;      // planes from an order-N input to where it is read
+  double tau;
+};
+// nm for m ranges of about the given width, and the tiles and ranges of a sweep.
+int window_nm(int N, int width);
+struct WindowGrid {
+  int ntx, nty, nchunks;
+};
+WindowGrid window_grid(int nx, int ny, int px, int py, int tx, int ty, int N, int nm);
+hipError_t launch_window(int storage, const WindowArgs& w, hipStream_t stream);
+// One instance of a batched run of register-window sweeps.
+struct WindowEntry {
+  void* u;
+  const void* decay;
+  const void* coef;
+  const int* tab;
+  int64_t plane_stride;
+  double tau_full, tau_half;
+  int pitch, nx, ny, px, py, N, nm, nchunks, ntx, nty, strip, nsweeps, top_shift, pad;
+};
+// Sweep number j over the first n_active instances (arguments as
+// launch_sweep_batch); general: one of them needs it.
+hipError_t launch_window_batch(int storage, const WindowEntry* table, const int* first, int n_active, int items, int j,
+                               int tx, int ty, bool general, hipStream_t stream);
+
+// Opts the kernels of an LDS variant in to the LDS it needs (outside any stream
 // capture).  Returns a HIP error.
-hipError_t prepare_sweep(int storage, int variant, int slots);
+hipError_t prepare_sweep(int variant, int slots);
 
 // Launch sweep number j of a batched run over the first n_active instances of
 // table, whose workgroups are numbered from first[i]; items = first[n_active].
-hipError_t launch_sweep_batch(int storage, int variant, const BatchEntry* table, const int* first, int n_active,
-                              int items, int j, int slots, hipStream_t stream);
+hipError_t launch_sweep_batch(int variant, const BatchEntry* table, const int* first, int n_active, int items, int j,
+                              int slots, hipStream_t stream);
 
 // Linear combination of basis planes (compute type) into decay planes
 // (compute type) or source planes (storage type).  For each pair (o, d) of

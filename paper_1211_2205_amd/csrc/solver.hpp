@@ -102,7 +102,7 @@ struct starmap_solver {
   bool owns_stream = false;
   hipStream_t stream = nullptr;
   bool bound = false;
-  size_t off_state = 0, off_decay = 0, off_src = 0, off_prog[2] = {0, 0}, off_diag = 0;
+  size_t off_state = 0, off_decay = 0, off_src = 0, off_prog[2] = {0, 0}, off_win = 0, off_diag = 0;
   size_t prog_bytes[2] = {0, 0};
   int diag_rows_per_block = 64, diag_nblocks = 0;
 
@@ -112,6 +112,8 @@ struct starmap_solver {
   int slots = 0;
   int nchunks = 1;               // m ranges per tile (workgroups per tile and sweep)
   int chunk_width = 0;           // m indices per range (0: default)
+  bool width_given = false;      // chosen by the user, the environment, the cache or the autotuner
+  bool win_general = false;      // register-window sweep: per-order decay planes or sources beyond the zeroth moment's
   int tile_strip = 8;            // tile order of the sweep: strips of k tile rows (k >= 2) or -k columns (k <= -2)
   starmap::SweepProgram prog[2];
   bool prog_uploaded = false;

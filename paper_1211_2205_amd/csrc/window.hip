@@ -1,0 +1,631 @@
+// Parity sweep of the staggered-grid P_N scheme on gfx950 with the window of
+// input orders in registers: the sweep of FP32 and BF16 storage, and of FP64
+// states that stay in the last-level cache (sweep.hip holds the FP64 kernel
+// for larger ones, and says what a sweep computes).
+//
+// Work decomposition: the outputs of a sweep are split into ranges of 2 NM
+// azimuthal indices m (an output (l, m) couples only to inputs
+// (l -+ 1, m -+ 1), Lemma 2).  One workgroup takes a spatial tile, one m range
+// and a run of output orders; every thread owns V x-adjacent points of the
+// tile and walks the output orders from the top down.  An order's rows need
+// the x and y differences of the NM + 1 R and I planes of the input orders
+// l + 1 and l - 1 in the range.  The differences of order l + 1 are in
+// registers from the rows before; of each plane of order l - 1 the thread has
+// loaded its own points, the x neighbour and the y neighbour: it forms the
+// plane's two differences, at once reloads the plane's registers with the
+// order two below, and updates the row whose last input that plane was.
+// Nothing is shared between threads: no LDS, no barrier, and every wave has a
+// whole order's planes and rows in flight while it computes the order before.
+//
+// Why registers: staged through LDS, the same sweep spent two barriers and a
+// load, an LDS store and eight LDS reads per plane and row on values that the
+// L1 cache serves as well (the neighbour loads hit lines that the wave or its
+// neighbours in the workgroup have just loaded).  Per sweep, LDS kernel with
+// its best tile -> this kernel with its default one: P_39 1000^2 BF16 838 ->
+// 529 us, FP32 1107 -> 1021 us; P_31 256^2 FP32 76 -> 48 us, BF16 71 -> 33 us;
+// P_9 317 x 203 FP32 15.5 -> 8.1 us; P_7 280^2 FP64 16.2 -> 14.3 us; P_3 100^2
+// FP64 7.4 -> 4.2 us.  P_39 1000^2 FP32 moves 4.9 GB per sweep at 4.8 TB/s; with
+// every neighbour load left out it takes 1020 us, so the memory's rate for this
+// mix of reads and writes bounds it.  FP64 states beyond the cache are slower
+// here (P_39 1000^2 2285 against 2035 us): eight-byte loads of three points per
+// plane need twice the L1 lines in flight, so the y neighbours' lines are gone
+// before they are asked for.
+//
+// Boundary conditions enter through the offsets of the neighbour loads (wrap
+// for periodic axes, clamp for extrapolation).  A plane that does not exist
+// (m < 0, m > l, order above N) is loaded through a buffer descriptor of no
+// records, which gives zeros without touching memory, so the loads of an order
+// are the same instructions everywhere and none sits under a branch (a load
+// under a branch makes the compiler wait for all earlier ones).
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+#include <type_traits>
+
+#include "device.hpp"
+#include "kernels.hpp"
+
+namespace starmap {
+
+namespace {
+
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+// Output rows are read once and written once per sweep: non-temporal (without
+// it P_39 1000^2 takes 5% longer).
+constexpr int kStream = 2;
+// a byte offset past every plane (planes stay below 2^31 bytes)
+constexpr uint32_t kOutside = 0x80000000u;
+
+// x-adjacent points per thread: two BF16 values make one 32-bit access (one
+// value per thread: half the bytes per instruction, four: 2% slower on P_39
+// 1000^2, more on small grids); FP32 pairs were slower than single points
+// (P_31 256^2: 83 against 53 us, fewer waves of eight-byte loads).
+template <typename T>
+constexpr int kPoints = sizeof(T) == 2 ? 2 : 1;
+
+// A thread's V stored values of a row segment as one memory access.
+template <typename T, int V>
+using Word = std::conditional_t<sizeof(T) * V == 8, u32x2, std::conditional_t<sizeof(T) * V == 4, uint32_t, uint16_t>>;
+
+template <typename W, int AUX = 0>
+__device__ __forceinline__ W buf_load(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+  if constexpr (sizeof(W) == 8)
+    return __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, AUX);
+  else if constexpr (sizeof(W) == 4)
+    return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, AUX);
+  else
+    return __builtin_amdgcn_raw_buffer_load_b16(r, off, 0, AUX);
+}
+template <typename W>
+__device__ __forceinline__ void buf_store(W v, __amdgpu_buffer_rsrc_t r, uint32_t off) {
+  if constexpr (sizeof(W) == 8)
+    __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, kStream);
+  else if constexpr (sizeof(W) == 4)
+    __builtin_amdgcn_raw_buffer_store_b32(v, r, off, 0, kStream);
+  else
+    __builtin_amdgcn_raw_buffer_store_b16(v, r, off, 0, kStream);
+}
+
+// Value e of a thread's word.
+template <typename T, int V>
+__device__ __forceinline__ typename ComputeOf<T>::type value(Word<T, V> w, int e) {
+  if constexpr (sizeof(T) == 8)
+    return __builtin_bit_cast(double, w);
+  else if constexpr (sizeof(T) == 4)
+    return __uint_as_float(w);
+  else if constexpr (V == 1)
+    return __uint_as_float(uint32_t(w) << 16);
+  else
+    return __uint_as_float(e ? (w & 0xFFFF0000u) : (w << 16));
+}
+template <typename T, int V>
+__device__ __forceinline__ Word<T, V> word(const typename ComputeOf<T>::type (&v)[V]) {
+  if constexpr (sizeof(T) == 2)
+    return uint32_t(from_c<bf16>(v[0]).bits) | (uint32_t(from_c<bf16>(v[V - 1]).bits) << 16);
+  else
+    return __builtin_bit_cast(Word<T, V>, v[0]);
+}
+
+// The value of the lane before (BEFORE) or after this one; every lane of the
+// wave must take part.
+template <bool BEFORE>
+__device__ __forceinline__ float lane_near(float v) {
+  return __uint_as_float(
+      uint32_t(__builtin_amdgcn_update_dpp(0, int(__float_as_uint(v)), BEFORE ? 0x138 : 0x130, 0xF, 0xF, true)));
+}
+
+// Scalars of one sweep.
+template <typename C>
+struct WindowScalars {
+  uint32_t ps;  // plane stride in elements
+  int pitch, nx, ny, px, py;
+  int bw, threads, ntx, nty, strip;  // lanes per tile row, threads per tile, tiles, tile order
+  int nchunks, nseg;                 // m ranges, runs of output orders
+  int N, top_shift;                  // order; planes from an order-N input to where it is read
+  C tau;
+};
+
+// Tiles of one group: the work items of a group are numbered range by range,
+// and the ranges of low m, which have the most orders, come first.  Ranges as
+// the inner index, as the LDS kernel takes them (its ranges share staged
+// lines), leave the long ranges to the end of a launch: P_39 1000^2 FP32 1100
+// against 1026 us, P_31 256^2 53 against 48 us.  One group over the whole of a
+// large grid loses the overlap of the ranges' shared planes: 1040 us.
+constexpr int kGroup = 512;
+
+template <typename T, int NM, int P, bool G>
+__device__ __forceinline__ void window_tile(T* __restrict__ U, const typename ComputeOf<T>::type* __restrict__ decay,
+                                            cptr<typename ComputeOf<T>::type> coef, cptr<int> tab,
+                                            const WindowScalars<typename ComputeOf<T>::type>& a, int item) {
+  using C = typename ComputeOf<T>::type;
+  constexpr int V = kPoints<T>;
+  static_assert(V <= 2, "a pair at most");
+  using W = Word<T, V>;
+  using W1 = Word<T, 1>;
+  typedef C C8 __attribute__((ext_vector_type(8)));
+  constexpr uint32_t TS = sizeof(T);
+  constexpr int NB = NM + 1;  // input planes of one order that the range needs, R and I each
+
+  // work item -> run of orders, m range, tile
+  const int seg = item % a.nseg;
+  item /= a.nseg;
+  const int per = kGroup * a.nchunks;
+  const int grp = item / per, within = item - grp * per;
+  const int gtiles = min(kGroup, a.ntx * a.nty - grp * kGroup);
+  const int chunk = within / gtiles;
+  const int tile = grp * kGroup + within - chunk * gtiles;
+  int m0 = chunk * 2 * NM;
+  const int ltop = a.N - ((a.N - P) & 1), lbot = m0 + P;
+  if (lbot > ltop) return;  // no output rows in this m range
+  const int nord = (ltop - lbot) / 2 + 1;
+  const int o0 = nord * seg / a.nseg, o1 = nord * (seg + 1) / a.nseg;
+  if (o0 >= o1) return;
+  const int lfirst = ltop - 2 * o0, llast = ltop - 2 * (o1 - 1);
+
+  // this thread's points (X .. X + V - 1, Y); lanes past the tile or the grid
+  // stand at the origin and store nothing
+  const int2 txy = tile_xy(tile, a.ntx, a.nty, a.strip);
+  const int f = txy.y * a.threads + int(threadIdx.x);
+  int Y = f / a.bw;
+  const int col = f - Y * a.bw;
+  int X = (txy.x * a.bw + col) * V;
+  const int rows = a.ny + 1 - a.py, cols = a.nx + 1 - a.px;
+  const bool in = Y < rows && X < cols;
+  if (!in) X = Y = 0;
+  // points of the lane on the two output grids: R rows are cell-centred along
+  // y (and along x in even sweeps), I rows nodal along y (and along x in even
+  // sweeps); R inputs are cell-centred along y (and along x in odd sweeps),
+  // I inputs nodal along y (and cell-centred along x in even sweeps)
+  const int vxR = P ? cols : a.nx, vxI = P ? a.nx : cols;
+  const bool okR = in && X < vxR && Y < a.ny, okI = in && X < vxI && Y < rows;
+  // y: centre row of R inputs (the last cell again past the last one), and the
+  // other end of the difference: the row below for cells, above for nodes
+  const int ycR = min(Y, a.ny - 1);
+  const int ynR = Y > 0 ? Y - 1 : (a.py ? a.ny - 1 : 0);
+  const int ynI = a.py ? (Y + 1 == a.ny ? 0 : Y + 1) : min(Y + 1, a.ny);
+  // x: for cells the point before the lane's first, for nodes the one after
+  // its last one that a cell needs
+  const int xlo = X > 0 ? X - 1 : (a.px ? a.nx - 1 : 0);
+  const int nv = min(V, a.nx - X);
+  const int xq = X + max(nv, 1);
+  const int xhi = a.px ? (xq >= a.nx ? xq - a.nx : xq) : min(xq, a.nx);
+  const int xcc = V == 1 ? min(X, a.nx - 1) : X;
+  const int xcR = P ? xcc : X, xcI = P ? X : xcc;
+  // With two points per thread the x neighbour is a value of the next lane
+  // (no load: P_39 1000^2 BF16 587 -> 532 us, the address unit had been the limit),
+  // except in the lanes at the ends of a wave, a tile row or the grid, which
+  // load it; single points are faster with the load (P_31 256^2 FP32 53
+  // against 56 us).
+  const int lane = int(threadIdx.x) & 63;
+  const bool endL = V == 1 || lane == 0 || col == 0 || !in || X == 0;
+  const bool endH = V == 1 || lane == 63 || col == a.bw - 1 || !in || X + V >= cols;
+  const uint32_t rowR = uint32_t(ycR * a.pitch), rowI = uint32_t(Y * a.pitch);
+  const uint32_t cR = (rowR + xcR) * TS, bR = uint32_t(ynR * a.pitch + xcR) * TS;
+  const uint32_t cI = (rowI + xcI) * TS, bI = uint32_t(ynI * a.pitch + xcI) * TS;
+  const uint32_t nR = (P ? endL : endH) ? (rowR + (P ? xlo : xhi)) * TS : kOutside;
+  const uint32_t nI = (P ? endH : endL) ? (rowI + (P ? xhi : xlo)) * TS : kOutside;
+  const uint32_t go = uint32_t(Y * a.pitch + X);
+  const uint32_t sR = okR ? go * TS : kOutside, sI = okI ? go * TS : kOutside;
+
+  // address of plane k, and the descriptor of a plane at an address
+  const int pbytes = int(a.ps * TS);
+  auto plane_addr = [&](int k) { return uint64_t(U) + uint64_t(int64_t(k) * int64_t(pbytes)); };
+  auto plane = [&](uint64_t p, int records) {
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(p), 0, records, 0x00020000);
+  };
+  // records of a plane of index m in an order of highest index lm: none past
+  // it (as bit operations: a comparison would travel as a 64-lane mask)
+  auto recs = [&](int m, int lm) { return pbytes & ~((lm - m) >> 31); };
+  const int first = m0 > 0 ? -1 : 0;  // the range of m = 0 has no planes of m < 0 and no I_0
+
+  // raw words of the input planes: centre, x neighbour, y neighbour
+  struct In {
+    W c, b;
+    W1 n;
+  };
+  struct Diff {
+    C x[V], y[V];
+  };
+  In rR[NB], rI[NB];
+  // planes number b (m = m0 + P - 1 + 2 b) of an order, R at address p and I
+  // after it, existing for m <= lm
+  auto load_planes = [&](int b, uint64_t p, int lm) {
+    const int n = recs(m0 + P - 1 + 2 * b, lm);
+    const auto r = plane(p, P == 0 && b == 0 ? n & first : n);
+    rR[b].c = buf_load<W>(r, cR);
+    rR[b].n = buf_load<W1>(r, nR);
+    rR[b].b = buf_load<W>(r, bR);
+    const auto i = plane(p + uint32_t(pbytes), b == 0 ? n & first : n);
+    rI[b].c = buf_load<W>(i, cI);
+    rI[b].n = buf_load<W1>(i, nI);
+    rI[b].b = buf_load<W>(i, bI);
+  };
+  // differences of a plane: along x centre - lower (cells) or upper - centre
+  // (nodes), along y likewise (R planes are cells, I planes nodes)
+  auto diff = [&](const In& w, Diff& d, bool cell, bool isR) {
+    C v[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) v[e] = value<T, V>(w.c, e);
+    C nb = value<T, 1>(w.n, 0);
+    if constexpr (V > 1) {
+      const C near = cell ? lane_near<true>(v[V - 1]) : lane_near<false>(v[0]);
+      nb = (cell ? endL : endH) ? nb : near;
+    }
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      const C q = value<T, V>(w.b, e);
+      d.y[e] = isR ? v[e] - q : q - v[e];
+    }
+    if (cell) {
+      if constexpr (V > 1) {  // the point past the last cell repeats it
+        v[V - 1] = !a.px && X + 1 == a.nx ? v[0] : v[V - 1];
+        v[0] = !a.px && X == a.nx ? nb : v[0];
+      }
+#pragma unroll
+      for (int e = 0; e < V; ++e) d.x[e] = v[e] - (e ? v[e ? e - 1 : 0] : nb);
+    } else {
+#pragma unroll
+      for (int e = 0; e < V; ++e) d.x[e] = (e + 1 == V || e + 1 == nv ? nb : v[e + 1 < V ? e + 1 : e]) - v[e];
+    }
+  };
+
+  // output rows: current values and, with G, source values (planes
+  // tab[2 (N + 1) + k]; none: zeros)
+  W uR[NM], uI[NM], qR[G ? NM : 1], qI[G ? NM : 1];
+  auto load_row = [&](int q, uint64_t p, int lm, int k) {
+    const int m = m0 + P + 2 * q;
+    const int n = recs(m, lm);
+    const int ni = P == 0 && q == 0 ? n & first : n;
+    uR[q] = buf_load<W, kStream>(plane(p, n), sR);
+    uI[q] = buf_load<W, kStream>(plane(p + uint32_t(pbytes), ni), sI);
+    if constexpr (G) {
+      const int r = n ? tab[2 * (a.N + 1) + k] : -1, i = ni ? tab[2 * (a.N + 1) + k + 1] : -1;
+      qR[q] = buf_load<W>(plane(plane_addr(r), r >= 0 ? pbytes : 0), sR);
+      qI[q] = buf_load<W>(plane(plane_addr(i), i >= 0 ? pbytes : 0), sI);
+    }
+  };
+
+  // decay coefficients c and E(-c tau) of the two output grids.  Without G one
+  // plane per grid serves every order but the zeroth (tab[2 l], tab[2 l + 1]:
+  // planes of the order's R and I rows), so E is formed once, before the loop.
+  C cR_[V], eR_[V], cI_[V], eI_[V], ldR[V], ldI[V];
+  auto load_decay = [&](int l) {
+    const C* d0 = plane_at(decay, max(tab[2 * l], 0), a.ps);
+    const C* d1 = plane_at(decay, max(tab[2 * l + 1], 0), a.ps);
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      ldR[e] = d0[go + e];
+      ldI[e] = d1[go + e];
+    }
+  };
+  auto apply_decay = [&]() {
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      cR_[e] = ldR[e];
+      eR_[e] = expm1div(-ldR[e] * a.tau);
+      cI_[e] = ldI[e];
+      eI_[e] = expm1div(-ldI[e] * a.tau);
+    }
+  };
+
+  // prologue: the input planes of both neighbouring orders and the first rows,
+  // all in flight together
+  int l = lfirst;
+  Diff hR[NB], hI[NB];  // differences of input order l + 1
+  {
+    const int r0 = l * (l + 1) / 2 + l - (m0 + P);
+    const int kh = r0 + l + 3, kl = r0 - l;  // planes b = 0 of orders l + 1 and l - 1
+    const int shift = l + 1 == a.N ? a.top_shift : 0;
+#pragma unroll
+    for (int b = NM; b >= 0; --b) load_planes(b, plane_addr(kh + shift - 2 * b), l < a.N ? l + 1 : -1);
+    In pR[NB], pI[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      pR[b] = rR[b];
+      pI[b] = rI[b];
+    }
+#pragma unroll
+    for (int b = NM; b >= 0; --b) load_planes(b, plane_addr(kl - 2 * b), l - 1);
+#pragma unroll
+    for (int q = NM - 1; q >= 0; --q) load_row(q, plane_addr(r0 - 2 * q), l, r0 - 2 * q);
+    load_decay(G || l > 0 ? l : min(1, a.N));
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      diff(pR[b], hR[b], P == 1, true);
+      diff(pI[b], hI[b], P == 0, false);
+    }
+  }
+  // the zeroth moment, the last row of the even sweep's first range, has a
+  // decay plane of its own (and, without G, the only source): updated last
+  const bool zeroth = !G && P == 0 && m0 == 0 && llast == 0;
+  C c0[V] = {};
+  W q0{};
+  if (zeroth) {
+    const C* d = plane_at(decay, tab[0], a.ps);
+#pragma unroll
+    for (int e = 0; e < V; ++e) c0[e] = d[go + e];
+    const int src = tab[2 * (a.N + 1)];
+    q0 = buf_load<W>(plane(plane_addr(src), src >= 0 ? pbytes : 0), sR);
+  }
+  apply_decay();
+
+  const int lend = zeroth ? 2 : llast;
+  for (; l >= lend; l -= 2) {
+    // (keeps what derives from m0 out of the scalar registers between orders)
+    asm volatile("" : "+s"(m0));
+    const bool more = l - 2 >= llast;
+    const int lm = more ? l - 3 : -1, ln = more ? l - 2 : -1;  // highest m of the planes and rows loaded next
+    // with G: the next rows' decay planes, if they are other ones
+    const bool redo = G && more && (tab[2 * l] != tab[2 * l - 4] || tab[2 * l + 1] != tab[2 * l - 3]);
+    if (redo) load_decay(l - 2);
+    // planes and rows in memory order, from the highest m of the range down:
+    // the first row of this order, the first row of the next, the first plane
+    // loaded next
+    const int k0 = l * (l + 1) / 2 + l - (m0 + P) - 2 * (NM - 1);
+    const int kn = k0 - (2 * l + 1), kp = kn - l;
+    uint64_t ps = plane_addr(k0), pn = plane_addr(kn), pl = plane_addr(kp);
+    // their coefficients (the table has eight rows of padding on both sides)
+    const cptr<C8> cf = reinterpret_cast<cptr<C8>>(cat(coef, uint32_t(k0 + 8) * uint32_t(8 * sizeof(C))));
+    C8 cr = cf[0], ci = cf[1];
+    Diff lR, lI;  // differences of the plane before (index m + 1 of the next row)
+#pragma unroll
+    for (int b = NM; b >= 0; --b) {
+      Diff dR, dI;
+      diff(rR[b], dR, P == 1, true);
+      diff(rI[b], dI, P == 0, false);
+      // (the differences before the loads that overwrite their sources)
+#pragma unroll
+      for (int e = 0; e < V; ++e) asm volatile("" : "+v"(dR.x[e]), "+v"(dR.y[e]), "+v"(dI.x[e]), "+v"(dI.y[e]));
+      load_planes(b, pl, lm);
+      pl += 2 * uint64_t(uint32_t(pbytes));
+      if (b < NM) {  // the rows of index m0 + P + 2 b
+        const int j = 2 * (NM - 1 - b);
+        C8 crn{}, cin{};
+        if (b > 0) {  // the next rows' coefficients, read ahead
+          crn = cf[j + 2];
+          cin = cf[j + 3];
+        }
+        const int n = recs(m0 + P + 2 * b, l);
+#pragma unroll
+        for (int z = 0; z < 2; ++z) {
+          // an R row takes the x differences of R planes and the y differences
+          // of I planes, an I row the others
+          const Diff &xl1 = z ? lI : lR, &xl0 = z ? dI : dR, &xh1 = z ? hI[b + 1] : hR[b + 1], &xh0 = z ? hI[b] : hR[b];
+          const Diff &yl1 = z ? lR : lI, &yl0 = z ? dR : dI, &yh1 = z ? hR[b + 1] : hI[b + 1], &yh0 = z ? hR[b] : hI[b];
+          const C8& c8 = z ? ci : cr;
+          C nv_[V];
+#pragma unroll
+          for (int e = 0; e < V; ++e) {
+            C w = fma(c8[0], xl1.x[e], C(0));
+            w = fma(c8[1], xl0.x[e], w);
+            w = fma(c8[2], xh1.x[e], w);
+            w = fma(c8[3], xh0.x[e], w);
+            w = fma(c8[4], yl1.y[e], w);
+            w = fma(c8[5], yl0.y[e], w);
+            w = fma(c8[6], yh1.y[e], w);
+            w = fma(c8[7], yh0.y[e], w);
+            if constexpr (G) w += value<T, V>(z ? qI[b] : qR[b], e);
+            const C u = value<T, V>(z ? uI[b] : uR[b], e);
+            const C r = sub_step(u, w, z ? cI_[e] : cR_[e], z ? eI_[e] : eR_[e], a.tau);
+            // (a lane's second point past the grid keeps the padding's value)
+            nv_[e] = e == 0 || X + e < (z ? vxI : vxR) ? r : u;
+          }
+          buf_store<W>(word<T, V>(nv_), plane(ps, P == 0 && z && b == 0 ? n & first : n), z ? sI : sR);
+          ps += uint32_t(pbytes);
+        }
+        load_row(b, pn, ln, kn + j);
+        pn += 2 * uint64_t(uint32_t(pbytes));
+        hR[b + 1] = lR;
+        hI[b + 1] = lI;
+        cr = crn;
+        ci = cin;
+      }
+      lR = dR;
+      lI = dI;
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    hR[0] = lR;
+    hI[0] = lI;
+    if (redo) apply_decay();
+  }
+  if (zeroth) {  // R_0^0 couples to R_1^1 and I_1^1 alone
+    const cptr<C> cf = cat(coef, uint32_t(8) * uint32_t(8 * sizeof(C)));
+    C nv_[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      C w = fma(cf[2], hR[1].x[e], C(0));
+      w = fma(cf[6], hI[1].y[e], w) + value<T, V>(q0, e);
+      const C u = value<T, V>(uR[0], e);
+      const C r = sub_step(u, w, c0[e], expm1div(-c0[e] * a.tau), a.tau);
+      nv_[e] = e == 0 || X + e < vxR ? r : u;
+    }
+    buf_store<W>(word<T, V>(nv_), plane(plane_addr(0), pbytes), sR);
+  }
+}
+
+// Threads per workgroup at most (a tile of 512 points of FP32).
+template <typename T>
+constexpr int kMaxThreads = sizeof(T) == 8 ? 256 : 512;
+
+template <typename T, int NM, int P, bool G>
+__global__ void __launch_bounds__(kMaxThreads<T>)
+window_kernel(T* __restrict__ U, const typename ComputeOf<T>::type* __restrict__ decay,
+              const typename ComputeOf<T>::type* __restrict__ coef, const int* __restrict__ tab,
+              const WindowScalars<typename ComputeOf<T>::type> a) {
+  using C = typename ComputeOf<T>::type;
+  window_tile<T, NM, P, G>(U, decay, (cptr<C>)coef, (cptr<int>)tab, a, int(blockIdx.x));
+}
+
+// WindowEntry as the device reads it (pointers with their address space, as
+// for the LDS kernel's table).
+template <typename Q>
+using gptr = __attribute__((address_space(1))) Q*;
+struct WindowEntryG {
+  gptr<void> u;
+  gptr<const void> decay;
+  gptr<const void> coef;
+  gptr<const int> tab;
+  int64_t plane_stride;
+  double tau_full, tau_half;
+  int pitch, nx, ny, px, py, N, nm, nchunks, ntx, nty, strip, nsweeps, top_shift, pad;
+};
+static_assert(sizeof(WindowEntryG) == sizeof(WindowEntry), "device view of WindowEntry");
+
+// Sweep number j of a batched run (instances and workgroup prefix as for the
+// LDS kernel); each instance brings its own width of m ranges.
+template <typename T, int P, bool G>
+__global__ void __launch_bounds__(kMaxThreads<T>)
+window_batch_kernel(const WindowEntry* __restrict__ table, const int* __restrict__ first, const int n_active,
+                    const int j, const int bw) {
+  using C = typename ComputeOf<T>::type;
+  const int item = int(blockIdx.x);
+  int lo = 0, hi = n_active - 1;  // last instance with first[i] <= item
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (first[mid] <= item) lo = mid; else hi = mid - 1;
+  }
+  lo = __builtin_amdgcn_readfirstlane(lo);
+  const WindowEntryG& e = reinterpret_cast<const WindowEntryG*>(table)[lo];
+  WindowScalars<C> a;
+  a.ps = uint32_t(e.plane_stride);
+  a.pitch = e.pitch;
+  a.nx = e.nx;
+  a.ny = e.ny;
+  a.px = e.px;
+  a.py = e.py;
+  a.bw = bw;
+  a.threads = int(blockDim.x);
+  a.ntx = e.ntx;
+  a.nty = e.nty;
+  a.strip = e.strip;
+  a.nchunks = e.nchunks;
+  a.nseg = 1;
+  a.N = e.N;
+  // closure solvers: before even sweep j, (j + 1) / 2 odd sweeps have moved
+  // the order-5 moments; an odd count leaves them in the closure planes
+  a.top_shift = (P == 0 && (((j + 1) >> 1) & 1)) ? e.top_shift : 0;
+  a.tau = C((j == 0 || j == e.nsweeps - 1) ? e.tau_half : e.tau_full);
+  T* const u = (T*)(gptr<T>)e.u;
+  const C* const dec = (const C*)(gptr<const C>)e.decay;
+  const cptr<C> cf = (cptr<C>)(gptr<const C>)e.coef;
+  const cptr<int> tab = (cptr<int>)e.tab;
+  const int nm = e.nm, it = item - first[lo];
+  if (nm == 2)
+    window_tile<T, 2, P, G>(u, dec, cf, tab, a, it);
+  else if (nm == 3)
+    window_tile<T, 3, P, G>(u, dec, cf, tab, a, it);
+  else
+    window_tile<T, 4, P, G>(u, dec, cf, tab, a, it);
+}
+
+template <typename T, int NM>
+hipError_t launch_t(const WindowArgs& w, hipStream_t stream) {
+  using C = typename ComputeOf<T>::type;
+  WindowScalars<C> a;
+  a.ps = uint32_t(w.plane_stride);
+  a.pitch = w.pitch;
+  a.nx = w.nx;
+  a.ny = w.ny;
+  a.px = w.px;
+  a.py = w.py;
+  a.bw = w.tx / kPoints<T>;
+  a.threads = a.bw * w.ty;
+  const WindowGrid g = window_grid(w.nx, w.ny, w.px, w.py, w.tx, w.ty, w.N, w.nm);
+  a.ntx = g.ntx;
+  a.nty = g.nty;
+  a.strip = w.strip;
+  a.nchunks = g.nchunks;
+  // A launch of fewer workgroups than compute units is a chain of memory
+  // round trips, one per order: its orders are split into runs that start
+  // their own chains (one more window to load each).  P_3 100^2 FP64 5.7 ->
+  // 5.2 us per sweep when it was put in; with more workgroups it costs (P_7
+  // 280^2 15.0 -> 16.8).
+  const int blocks1 = g.ntx * g.nty * g.nchunks, orders = w.N / 2 + 1;
+  a.nseg = blocks1 > 0 ? 256 / blocks1 : 1;
+  a.nseg = a.nseg < 1 ? 1 : a.nseg > orders ? orders : a.nseg;
+  a.N = w.N;
+  a.top_shift = w.top_shift;
+  a.tau = C(w.tau);
+  if (a.bw < 1 || a.threads < 64 || a.threads > kMaxThreads<T>) return hipErrorInvalidValue;
+  const int64_t blocks = int64_t(blocks1) * a.nseg;
+  if (blocks < 1 || blocks >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+  T* u = static_cast<T*>(w.u);
+  const C *d = static_cast<const C*>(w.decay), *cf = static_cast<const C*>(w.coef);
+#define STARMAP_WINDOW(P, G) \
+  hipLaunchKernelGGL((window_kernel<T, NM, P, G>), dim3(unsigned(blocks)), dim3(a.threads), 0, stream, u, d, cf, w.tab, a)
+  if (w.parity) {
+    if (w.general) STARMAP_WINDOW(1, true); else STARMAP_WINDOW(1, false);
+  } else {
+    if (w.general) STARMAP_WINDOW(0, true); else STARMAP_WINDOW(0, false);
+  }
+#undef STARMAP_WINDOW
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_nm(const WindowArgs& w, hipStream_t stream) {
+  switch (w.nm) {
+    case 2: return launch_t<T, 2>(w, stream);
+    case 3: return launch_t<T, 3>(w, stream);
+    case 4: return launch_t<T, 4>(w, stream);
+  }
+  return hipErrorInvalidValue;
+}
+
+template <typename T>
+hipError_t launch_batch_t(const WindowEntry* table, const int* first, int n_active, int items, int j, int tx, int ty,
+                          bool general, hipStream_t stream) {
+  const int bw = tx / kPoints<T>, threads = bw * ty;
+  if (bw < 1 || threads < 64 || threads > kMaxThreads<T>) return hipErrorInvalidValue;
+#define STARMAP_WINDOW(P, G) \
+  hipLaunchKernelGGL((window_batch_kernel<T, P, G>), dim3(items), dim3(threads), 0, stream, table, first, n_active, j, bw)
+  if (j & 1) {
+    if (general) STARMAP_WINDOW(0, true); else STARMAP_WINDOW(0, false);
+  } else {
+    if (general) STARMAP_WINDOW(1, true); else STARMAP_WINDOW(1, false);
+  }
+#undef STARMAP_WINDOW
+  return hipGetLastError();
+}
+
+}  // namespace
+
+int window_nm(int N, int width) {
+  // as many ranges as the width asks for, of equal (even) widths
+  const int w = width < 4 ? 4 : width > 8 ? 8 : width;
+  const int chunks = (N + 1 + w - 1) / w;
+  const int nm = (N + 1 + 2 * chunks - 1) / (2 * chunks);
+  return nm < 2 ? 2 : nm > 4 ? 4 : nm;
+}
+
+WindowGrid window_grid(int nx, int ny, int px, int py, int tx, int ty, int N, int nm) {
+  // tiles of tx x ty points over every point that lies on one of the grids
+  WindowGrid g;
+  g.ntx = (nx + 1 - px + tx - 1) / tx;
+  g.nty = (ny + 1 - py + ty - 1) / ty;
+  g.nchunks = (N + 1 + 2 * nm - 1) / (2 * nm);
+  return g;
+}
+
+hipError_t launch_window(int storage, const WindowArgs& w, hipStream_t stream) {
+  switch (storage) {
+    case STORE_FP64: return launch_nm<double>(w, stream);
+    case STORE_FP32: return launch_nm<float>(w, stream);
+    case STORE_BF16: return launch_nm<bf16>(w, stream);
+  }
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_window_batch(int storage, const WindowEntry* table, const int* first, int n_active, int items, int j,
+                               int tx, int ty, bool general, hipStream_t stream) {
+  if (n_active < 1 || items < 1) return hipErrorInvalidValue;
+  switch (storage) {
+    case STORE_FP64: return launch_batch_t<double>(table, first, n_active, items, j, tx, ty, general, stream);
+    case STORE_FP32: return launch_batch_t<float>(table, first, n_active, items, j, tx, ty, general, stream);
+    case STORE_BF16: return launch_batch_t<bf16>(table, first, n_active, items, j, tx, ty, general, stream);
+  }
+  return hipErrorInvalidValue;
+}
+
+}  // namespace starmap

@@ -1,0 +1,149 @@
+"""The register-window sweep (window.hip) at the sizes where it can go wrong:
+tiles with one point of remainder, grids smaller than a tile, every remainder
+of the m ranges, sources and decay planes of every order, launches of fewer
+workgroups than compute units (orders split into runs) and more, a value that
+is not finite.  FP64 variants run the same operations in the same order with
+the window in registers or in LDS, so they must agree bit for bit."""
+import numpy as np
+import pytest
+
+import paper_1211_2205_amd as pa
+import workloads as wl
+from gpu_helpers import assert_parity, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+P, X = wl.BC_PERIODIC, wl.BC_EXTRAPOLATION
+LDS, WINDOW = 0, (4, 9, 12)  # FP64 variants
+STEPS = 5
+
+CASES = [
+    # N, (nx, ny), bc, every order with its own decay and source
+    (1, (2, 2), (X, X), False),
+    (1, (63, 3), (P, P), True),
+    (2, (64, 2), (X, P), False),
+    (3, (65, 5), (P, X), True),
+    (4, (127, 4), (X, X), False),
+    (5, (128, 7), (X, P), True),
+    (6, (129, 8), (P, P), False),
+    (7, (33, 65), (X, X), True),
+    (8, (257, 9), (P, X), False),
+    (11, (66, 31), (X, P), False),
+    (13, (191, 130), (X, X), False),
+    (16, (62, 17), (P, P), True),
+    (21, (31, 64), (X, X), True),
+]
+
+
+def _problem(N, n, bc, general, precision="fp64"):
+    rng = np.random.default_rng(17 * N + n[0])
+    sa = rng.uniform(0.1, 2, size=3)
+    src = {0: lambda t, x, y: np.exp(-x * x - y * y)}
+    if general:
+        src.update({k: (lambda k: lambda t, x, y: np.sin(k + x) * y)(k) for k in (1, 2) if N >= 1})
+    return wl.Problem(
+        name="window", N=N, n=n, ax=(-0.3, 0.9, 0.1, 1.3), bc=bc, cfl=0.5, t_final=0.4, precision=precision,
+        sigma_a=lambda t, x, y: sa[0] + sa[1] * np.cos(2 * x) ** 2, sigma_s0=lambda t, x, y: sa[2] + 0 * x * y,
+        sigma_sl=(lambda l, t, x, y: 0.8 ** l * (1 + 0 * x * y)) if general else None, source=src)
+
+
+def _run(prob, init, variant, width):
+    s = pa.Solver.from_problem(prob)
+    for k, a in enumerate(init):
+        s.set_field_array(3, k, a)
+    s.bind_torch()
+    s.set_variant(variant)
+    s.set_chunk_width(width)
+    s.advance(STEPS)
+    out = s.moments()
+    s.close()
+    return out
+
+
+def _init(prob):
+    s = pa.Solver.from_problem(prob)
+    s.bind_torch()
+    shapes = [m.shape for m in s.moments()]
+    s.close()
+    return wl.random_state(5, shapes)
+
+
+@pytest.mark.parametrize("N,n,bc,general", CASES)
+def test_fp64_register_and_lds_windows_agree(N, n, bc, general):
+    prob = _problem(N, n, bc, general)
+    init = _init(prob)
+    init[0][n[1] // 2, n[0] // 2] = np.inf  # spreads as inf and NaN
+    for width in (4, 6, 8):
+        ref = _run(prob, init, LDS, width)
+        for v in WINDOW:
+            got = _run(prob, init, v, width)
+            for k, (a, b) in enumerate(zip(got, ref)):
+                assert np.array_equal(a, b, equal_nan=True), (v, width, k)
+
+
+@pytest.mark.parametrize("N,n,bc,general", CASES)
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
+def test_narrow_storage_against_fp64(precision, N, n, bc, general):
+    """One tile and width against FP64, the others bit for bit against it.
+    FP32: the parity bound of the suite.  BF16: every stored value is rounded
+    by at most 2^-9 of itself in each of the 2 x 5 + 1 sweeps (and once at the
+    start), and a sweep amplifies no error norm: 12 x 2^-9 = 0.024 of the
+    norm."""
+    prob = _problem(N, n, bc, general)
+    init = _init(prob)
+    ref = _run(prob, init, LDS, 8)
+    narrow = _problem(N, n, bc, general, precision)
+    one = _run(narrow, init, 0, 8)
+    if precision == "fp32":
+        assert_parity(one, ref, 1e-5, f"{precision} P_{N} {n}")
+    else:
+        assert rel_l2(one, ref) <= 0.024
+    for width, variants in ((4, (1, 3, 6, 7)), (6, (2, 4, 10, 11)), (8, (5, 8, 9, 12, 13))):
+        for v in variants:
+            for k, (a, b) in enumerate(zip(_run(narrow, init, v, width), one)):
+                assert np.array_equal(a, b), (v, width, k)
+
+
+@pytest.mark.parametrize("precision,variant,width", [("fp64", 4, 4), ("fp64", 9, 6), ("fp64", 12, 8), ("fp32", 0, 8),
+                                                     ("fp32", 7, 4), ("bf16", 4, 6), ("bf16", 12, 8)])
+def test_batched_register_windows_equal_single_runs(precision, variant, width):
+    """Instances of every m-range width and both kernels (with and without
+    per-order decay planes) in one batch, as a graph replayed."""
+    probs = [_problem(*c, precision) for c in CASES[:10]]
+    solvers = [pa.Solver.from_problem(p) for p in probs]
+    b = pa.Batch(solvers)
+    b.set_variant(variant, width)
+    for merged in (False, True):
+        b.set_merged(merged)
+        for _ in range(2):
+            b.reset()
+            b.run(use_graph=True)
+            for p, s in zip(probs, solvers):
+                t = pa.Solver.from_problem(p)
+                t.bind_torch()
+                t.set_variant(variant)
+                t.set_chunk_width(width)
+                t.run()
+                for k, (x, y) in enumerate(zip(s.moments(), t.moments())):
+                    assert np.array_equal(x, y), (p.N, p.n, merged, k)
+                t.close()
+    b.close()
+
+
+def test_refused_tiles_stay_refused_after_a_register_window(monkeypatch):
+    """64 x 8 FP64 tiles of P_39 do not fit the LDS at m ranges of 24: set_variant
+    says so whether the variant before it was a register window or not."""
+    monkeypatch.setenv("STARMAP_CHUNK_WIDTH", "24")
+    prob = _problem(39, (20, 12), (X, X), False)
+    for before in (LDS, 12):
+        s = pa.Solver.from_problem(prob)
+        s.bind_torch()
+        s.set_variant(before)
+        s.advance(1)
+        with pytest.raises(pa.StarmapError):
+            s.set_variant(5)
+        s.set_chunk_width(4)
+        s.set_variant(5)
+        s.advance(1)
+        s.synchronize()
+        s.close()
