@@ -42,15 +42,6 @@ uint16_t bf16_rne(float f) {
   return uint16_t(u >> 16);
 }
 
-// offsets of the parameter blob
-constexpr int OFF_W1 = 0;
-constexpr int OFF_B1 = OFF_W1 + CLOSURE_HIDDEN * CLOSURE_IN;
-constexpr int OFF_W2 = OFF_B1 + CLOSURE_HIDDEN;
-constexpr int OFF_B2 = OFF_W2 + CLOSURE_HIDDEN * CLOSURE_HIDDEN;
-constexpr int OFF_W3 = OFF_B2 + CLOSURE_HIDDEN;
-constexpr int OFF_B3 = OFF_W3 + CLOSURE_OUT * CLOSURE_HIDDEN;
-static_assert(OFF_B3 + CLOSURE_OUT == CLOSURE_PARAMS, "parameter blob layout");
-
 }  // namespace
 
 namespace starmap {
@@ -154,71 +145,40 @@ struct starmap_mlp {
   int max_batch = 0;
   void* mem = nullptr;
   float *params = nullptr, *grads = nullptr, *m = nullptr, *v = nullptr;
-  float *Z1 = nullptr, *A1 = nullptr, *Z2 = nullptr, *A2 = nullptr, *Y = nullptr, *dY = nullptr;
-  float *dZ1 = nullptr, *dZ2 = nullptr, *gpart = nullptr, *cpart = nullptr;
+  float *Y = nullptr, *dY = nullptr, *dZ1 = nullptr, *dZ2 = nullptr, *gpart = nullptr, *cpart = nullptr;
+  uint16_t *xt = nullptr, *h1t = nullptr, *h2t = nullptr, *dz1t = nullptr, *dz2t = nullptr, *dyt = nullptr;
   double *lpart = nullptr, *loss = nullptr;
-  int splits = 1;
   int64_t t = 0;  // Adam steps taken
 };
 
 namespace {
 
 constexpr int kMaxSplits = 64;
-constexpr int kLossBlocks = 256;
 
-int mlp_forward(starmap_mlp* n, const float* X, int B) {
-  const float* P = n->params;
-  auto layer = [&](const float* A, const float* W, int N, const float* bias, int mode, float* out, float* out2,
-                   int ldo) -> int {
-    GemmArgs g{A, CLOSURE_IN, 1, W, 1, CLOSURE_IN, n->gpart, B, N, CLOSURE_IN, 1 << 30};
-    EpiArgs e{n->gpart, 1, B, N, bias, mode, nullptr, 0, out, ldo, out2};
-    HIP_TRY(launch_gemm(g, 1, e, n->stream));
-    return STARMAP_OK;
-  };
-  int rc = layer(X, P + OFF_W1, CLOSURE_HIDDEN, P + OFF_B1, EPI_GELU, n->Z1, n->A1, CLOSURE_HIDDEN);
-  if (!rc) rc = layer(n->A1, P + OFF_W2, CLOSURE_HIDDEN, P + OFF_B2, EPI_GELU, n->Z2, n->A2, CLOSURE_HIDDEN);
-  if (!rc) rc = layer(n->A2, P + OFF_W3, CLOSURE_OUT, P + OFF_B3, EPI_STORE, n->Y, nullptr, CLOSURE_OUT);
-  return rc;
+int mlp_rows(starmap_mlp* n, const float* X, const float* T, int B) {
+  MlpRows g{X, T, n->params, B, n->Y, n->dY, n->dZ1, n->dZ2, n->xt, n->h1t, n->h2t, n->dz1t, n->dz2t, n->dyt, n->lpart};
+  HIP_TRY(launch_mlp_rows(g, T != nullptr, n->stream));
+  return STARMAP_OK;
 }
 
-// weight gradient G (M x 128) = D^T A over the batch: D (B x M), A (B x 128)
-int mlp_weight_grad(starmap_mlp* n, const float* D, int M, const float* A, int B, float* G) {
+// The gradient of a batch and, with a.p, the Adam step.
+int mlp_step(starmap_mlp* n, const float* X, const float* T, int B, const MlpAdam& a) {
+  int rc = mlp_rows(n, X, T, B);
+  if (rc) return rc;
   int splits = std::min(kMaxSplits, std::max(1, B / 256));
-  int kchunk = ((B + splits - 1) / splits + 31) / 32 * 32;
+  const int kchunk = ((B + splits - 1) / splits + 31) / 32 * 32;
   splits = (B + kchunk - 1) / kchunk;
-  GemmArgs g{D, 1, M, A, CLOSURE_HIDDEN, 1, n->gpart, M, CLOSURE_HIDDEN, B, kchunk};
-  EpiArgs e{n->gpart, splits, M, CLOSURE_HIDDEN, nullptr, EPI_STORE, nullptr, 0, G, CLOSURE_HIDDEN, nullptr};
-  HIP_TRY(launch_gemm(g, splits, e, n->stream));
+  const MlpGrad g{n->dY,   n->dZ1,  n->dZ2, n->xt,    n->h1t,   n->h2t, n->dz1t,
+                  n->dz2t, n->dyt, n->gpart, n->cpart, B,       splits, kchunk};
+  HIP_TRY(launch_mlp_grad(g, n->stream));
+  HIP_TRY(launch_mlp_update(g, n->grads, a, n->lpart, n->loss, n->stream));
   return STARMAP_OK;
 }
 
-int mlp_backward(starmap_mlp* n, const float* X, const float* T, int B) {
-  const float* P = n->params;
-  float* G = n->grads;
-  HIP_TRY(launch_mse(n->Y, T, int64_t(B) * CLOSURE_OUT, n->dY, n->lpart, kLossBlocks, n->loss, n->stream));
-  int rc = mlp_weight_grad(n, n->dY, CLOSURE_OUT, n->A2, B, G + OFF_W3);
-  if (rc) return rc;
-  HIP_TRY(launch_colsum(n->dY, B, CLOSURE_OUT, CLOSURE_OUT, n->cpart, G + OFF_B3, n->stream));
-  {  // dZ2 = (dY W3) * gelu'(Z2)
-    GemmArgs g{n->dY, CLOSURE_OUT, 1, P + OFF_W3, CLOSURE_HIDDEN, 1, n->gpart, B, CLOSURE_HIDDEN, CLOSURE_OUT, 1 << 30};
-    EpiArgs e{n->gpart, 1, B, CLOSURE_HIDDEN, nullptr, EPI_GELU_GRAD, n->Z2, CLOSURE_HIDDEN, n->dZ2, CLOSURE_HIDDEN,
-              nullptr};
-    HIP_TRY(launch_gemm(g, 1, e, n->stream));
-  }
-  rc = mlp_weight_grad(n, n->dZ2, CLOSURE_HIDDEN, n->A1, B, G + OFF_W2);
-  if (rc) return rc;
-  HIP_TRY(launch_colsum(n->dZ2, B, CLOSURE_HIDDEN, CLOSURE_HIDDEN, n->cpart, G + OFF_B2, n->stream));
-  {  // dZ1 = (dZ2 W2) * gelu'(Z1)
-    GemmArgs g{n->dZ2, CLOSURE_HIDDEN, 1, P + OFF_W2, CLOSURE_HIDDEN, 1, n->gpart, B, CLOSURE_HIDDEN,
-               CLOSURE_HIDDEN, 1 << 30};
-    EpiArgs e{n->gpart, 1, B, CLOSURE_HIDDEN, nullptr, EPI_GELU_GRAD, n->Z1, CLOSURE_HIDDEN, n->dZ1, CLOSURE_HIDDEN,
-              nullptr};
-    HIP_TRY(launch_gemm(g, 1, e, n->stream));
-  }
-  rc = mlp_weight_grad(n, n->dZ1, CLOSURE_HIDDEN, X, B, G + OFF_W1);
-  if (rc) return rc;
-  HIP_TRY(launch_colsum(n->dZ1, B, CLOSURE_HIDDEN, CLOSURE_HIDDEN, n->cpart, G + OFF_B1, n->stream));
-  return STARMAP_OK;
+MlpAdam adam_args(starmap_mlp* n, double lr) {
+  const double b1 = 0.9, b2 = 0.999;
+  const double c1 = 1.0 - std::pow(b1, double(n->t)), c2 = 1.0 - std::pow(b2, double(n->t));
+  return {n->params, n->m, n->v, float(lr), float(b1), float(b2), 1e-8f, float(c1), float(c2)};
 }
 
 int check_batch(const starmap_mlp* n, int B) {
@@ -359,11 +319,13 @@ int starmap_mlp_create(int32_t max_batch, void* hip_stream, starmap_mlp** out) {
   const size_t P = align256(size_t(CLOSURE_PARAMS) * 4);
   const size_t act = align256(size_t(max_batch) * CLOSURE_HIDDEN * 4);
   const size_t out6 = align256(size_t(max_batch) * CLOSURE_OUT * 4);
-  const size_t gp = align256(std::max(size_t(kMaxSplits) * CLOSURE_HIDDEN * CLOSURE_HIDDEN,
-                                      size_t(max_batch) * CLOSURE_HIDDEN) * 4);
-  const size_t cp = align256(size_t(colsum_part_floats(max_batch, CLOSURE_HIDDEN)) * 4);
-  const size_t lp = align256(size_t(kLossBlocks + 1) * 8);
-  const size_t total = 4 * P + 6 * act + 2 * out6 + gp + cp + lp;
+  // transposed operands: whole blocks of 32 rows
+  const size_t rows = (size_t(max_batch) + 31) / 32 * 32;
+  const size_t tr = align256(rows * CLOSURE_HIDDEN * 2), tr8 = align256(rows * 8 * 2);
+  const size_t gp = align256(size_t(kMaxSplits) * CLOSURE_PARAMS * 4);
+  const size_t cp = align256(size_t(mlp_sum_chunks(max_batch)) * SUM_COLS * 4);
+  const size_t lp = align256(size_t(mlp_row_blocks(max_batch) + 1) * 8);
+  const size_t total = 4 * P + 2 * act + 2 * out6 + 5 * tr + tr8 + gp + cp + lp;
   HIP_TRY(hipMalloc(&n->mem, total));
   HIP_TRY(hipMemsetAsync(n->mem, 0, total, n->stream));
   HIP_TRY(hipStreamSynchronize(n->stream));
@@ -373,18 +335,16 @@ int starmap_mlp_create(int32_t max_batch, void* hip_stream, starmap_mlp** out) {
   n->grads = reinterpret_cast<float*>(take(P));
   n->m = reinterpret_cast<float*>(take(P));
   n->v = reinterpret_cast<float*>(take(P));
-  n->Z1 = reinterpret_cast<float*>(take(act));
-  n->A1 = reinterpret_cast<float*>(take(act));
-  n->Z2 = reinterpret_cast<float*>(take(act));
-  n->A2 = reinterpret_cast<float*>(take(act));
   n->dZ1 = reinterpret_cast<float*>(take(act));
   n->dZ2 = reinterpret_cast<float*>(take(act));
   n->Y = reinterpret_cast<float*>(take(out6));
   n->dY = reinterpret_cast<float*>(take(out6));
+  for (uint16_t** q : {&n->xt, &n->h1t, &n->h2t, &n->dz1t, &n->dz2t}) *q = reinterpret_cast<uint16_t*>(take(tr));
+  n->dyt = reinterpret_cast<uint16_t*>(take(tr8));
   n->gpart = reinterpret_cast<float*>(take(gp));
   n->cpart = reinterpret_cast<float*>(take(cp));
   n->lpart = reinterpret_cast<double*>(take(lp));
-  n->loss = n->lpart + kLossBlocks;
+  n->loss = n->lpart + mlp_row_blocks(max_batch);
   *out = n.release();
   return STARMAP_OK;
 }
@@ -421,7 +381,7 @@ int starmap_mlp_forward(starmap_mlp* n, const float* x, int32_t batch, float* y)
   int rc = check_batch(n, batch);
   if (rc) return rc;
   if (!x || !y) return fail(STARMAP_EINVAL, "bad arguments");
-  rc = mlp_forward(n, x, batch);
+  rc = mlp_rows(n, x, nullptr, batch);
   if (rc) return rc;
   HIP_TRY(hipMemcpyAsync(y, n->Y, size_t(batch) * CLOSURE_OUT * 4, hipMemcpyDeviceToDevice, n->stream));
   return STARMAP_OK;
@@ -432,8 +392,7 @@ int starmap_mlp_gradients(starmap_mlp* n, const float* x, const float* t, int32_
   int rc = check_batch(n, batch);
   if (rc) return rc;
   if (!x || !t) return fail(STARMAP_EINVAL, "bad arguments");
-  rc = mlp_forward(n, x, batch);
-  if (!rc) rc = mlp_backward(n, x, t, batch);
+  rc = mlp_step(n, x, t, batch, MlpAdam{});
   if (rc) return rc;
   if (grad_host)
     HIP_TRY(hipMemcpyAsync(grad_host, n->grads, size_t(CLOSURE_PARAMS) * 4, hipMemcpyDeviceToHost, n->stream));
@@ -446,14 +405,9 @@ int starmap_mlp_train_step(starmap_mlp* n, const float* x, const float* t, int32
   int rc = check_batch(n, batch);
   if (rc) return rc;
   if (!x || !t || !(lr > 0.0)) return fail(STARMAP_EINVAL, "bad arguments");
-  rc = mlp_forward(n, x, batch);
-  if (!rc) rc = mlp_backward(n, x, t, batch);
-  if (rc) return rc;
   n->t += 1;
-  const double b1 = 0.9, b2 = 0.999;
-  const double c1 = 1.0 - std::pow(b1, double(n->t)), c2 = 1.0 - std::pow(b2, double(n->t));
-  HIP_TRY(launch_adam(n->params, n->grads, n->m, n->v, CLOSURE_PARAMS, float(lr), float(b1), float(b2), 1e-8f,
-                      float(c1), float(c2), n->stream));
+  rc = mlp_step(n, x, t, batch, adam_args(n, lr));
+  if (rc) return rc;
   if (loss) {
     HIP_TRY(hipMemcpyAsync(loss, n->loss, 8, hipMemcpyDeviceToHost, n->stream));
     HIP_TRY(hipStreamSynchronize(n->stream));
@@ -465,10 +419,7 @@ int starmap_mlp_adam_step(starmap_mlp* n, const float* grad_host, double lr) {
   if (!n || !grad_host || !(lr > 0.0)) return fail(STARMAP_EINVAL, "bad arguments");
   HIP_TRY(hipMemcpyAsync(n->grads, grad_host, size_t(CLOSURE_PARAMS) * 4, hipMemcpyHostToDevice, n->stream));
   n->t += 1;
-  const double b1 = 0.9, b2 = 0.999;
-  const double c1 = 1.0 - std::pow(b1, double(n->t)), c2 = 1.0 - std::pow(b2, double(n->t));
-  HIP_TRY(launch_adam(n->params, n->grads, n->m, n->v, CLOSURE_PARAMS, float(lr), float(b1), float(b2), 1e-8f,
-                      float(c1), float(c2), n->stream));
+  HIP_TRY(launch_adam(adam_args(n, lr), n->grads, n->stream));
   HIP_TRY(hipStreamSynchronize(n->stream));
   return STARMAP_OK;
 }

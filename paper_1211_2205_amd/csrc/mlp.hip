@@ -76,154 +76,380 @@ __device__ __forceinline__ uint4 pack8(const uint32_t (&h)[8]) {
   return make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
 }
 
-// ------------------------------------------------------------ training GEMM
-// P[z][m][n] = sum over k in split z of bf16(A(m, k)) * bf16(B(k, n)), with
-// A(m, k) = A[m sam + k sak] and B(k, n) = B[k sbk + n sbn].  64 x 64 outputs
-// per workgroup; four waves of 32 x 32; K in steps of 32 through LDS.
-constexpr int GT = 64;        // output tile edge
-constexpr int GK = 32;        // K step
-constexpr int GLD = GK + 8;   // LDS row of one tile row / column (bf16), padded
+// ------------------------------------------------------------ training
+// A training step is three launches: the rows of the batch through the network
+// and back (mlp_rows_kernel), the weight gradients' split partials and the
+// column sums (mlp_grad_kernel), and their sums with the Adam update
+// (mlp_update_kernel).  The arrays a step moves are a few MB, so launches and
+// chains of memory round trips bound it: one product, epilogue or column sum
+// per launch (25 of them), with products whose loads waited for one another,
+// took 293 us per step at 4096 rows; these three take 40 us.
+constexpr int TR = 16;                   // rows of the batch per block
+constexpr int LDT = CLOSURE_HIDDEN + 8;  // LDS row of one row's activations (bf16), padded
+constexpr int KT = 32;                   // rows per k step of the weight gradients
 
-__global__ void __launch_bounds__(256) gemm_bf16_kernel(const GemmArgs g) {
-  __shared__ __align__(16) uint16_t As[GT * GLD];
-  __shared__ __align__(16) uint16_t Bs[GT * GLD];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int m0 = blockIdx.y * GT, n0 = blockIdx.x * GT;
-  const int kb = blockIdx.z * g.kchunk;
-  const int ke = min(g.K, kb + g.kchunk);
-  const int wm = (w >> 1) * 32, wn = (w & 1) * 32;
-  f32x4 acc[2][2];
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // callers' arrays: float alignment
+
+// eight consecutive values as bfloat16
+__device__ __forceinline__ uint4 bf16_row8(const float* p) {
+  const f32x4u v0 = *reinterpret_cast<const f32x4u*>(p), v1 = *reinterpret_cast<const f32x4u*>(p + 4);
+  const uint32_t h[8] = {bf16_bits(v0[0]), bf16_bits(v0[1]), bf16_bits(v0[2]), bf16_bits(v0[3]),
+                         bf16_bits(v1[0]), bf16_bits(v1[1]), bf16_bits(v1[2]), bf16_bits(v1[3])};
+  return pack8(h);
+}
+
+// Transposed activations as the weight gradients read them: per k step of 32
+// rows of the batch [unit][row], so that a lane's eight rows of one unit are one
+// 16-byte load and a wave's loads are 1 KiB together.
+__device__ __forceinline__ int64_t t_index(int b, int units, int unit) {
+  return int64_t(b / KT) * (units * KT) + unit * KT + (b % KT);
+}
+__device__ __forceinline__ void store_transposed(const uint16_t* S, uint16_t* T, int b0) {
+  const int unit = int(threadIdx.x) >> 1, half = 8 * (int(threadIdx.x) & 1);
+  uint32_t h[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) h[e] = S[(half + e) * LDT + unit];
+  *reinterpret_cast<uint4*>(&T[t_index(b0 + half, CLOSURE_HIDDEN, unit)]) = pack8(h);
+}
+
+// Rows of the batch through the network (TRAIN: and the loss's gradient back to
+// the pre-activations).  A workgroup keeps all weights in registers and loops
+// over blocks of 16 rows; wave w owns hidden units [32 w, 32 w + 32).  Products
+// are computed transposed as in the closure kernel, H^T = W X^T; the
+// pre-activations stay in registers until the backward products need them.
+// Only what the weight gradients and the biases' sums read goes to memory.
+template <bool TRAIN>
+__global__ void __launch_bounds__(256, 2) mlp_rows_kernel(const MlpRows g) {
+  __shared__ __align__(16) uint16_t Xs[TR * LDT], H1[TR * LDT], H2[TR * LDT], D2[TR * LDT], D1[TR * LDT];
+  __shared__ __align__(16) uint16_t Ys[TR * 8];
+  const int tid = int(threadIdx.x), lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int pt = lane & 15, grp = lane >> 4, fk = 8 * grp, u0 = 32 * w;
+  const float* P = g.params;
+
+  // weight fragments (A operands): rows are the outputs of each product
+  uint4 w1[2][4], w2[2][4], w2t[2][4], w3[4], w3t[2];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // staging: thread t fills row (or column) t / 4, k offsets 8 (t % 4) .. + 7
-  const int sr = tid >> 2, sk = (tid & 3) * 8;
-  for (int k0 = kb; k0 < ke; k0 += GK) {
-    uint32_t ha[8], hb[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int k = k0 + sk + e;
-      const int m = m0 + sr, n = n0 + sr;
-      const float av = (m < g.M && k < ke) ? g.A[int64_t(m) * g.sam + int64_t(k) * g.sak] : 0.f;
-      const float bv = (n < g.N && k < ke) ? g.B[int64_t(k) * g.sbk + int64_t(n) * g.sbn] : 0.f;
-      ha[e] = bf16_bits(av);
-      hb[e] = bf16_bits(bv);
+    for (int ks = 0; ks < 4; ++ks) {
+      const int row = u0 + 16 * i + pt;
+      w1[i][ks] = bf16_row8(P + OFF_W1 + row * CLOSURE_IN + 32 * ks + fk);
+      w2[i][ks] = bf16_row8(P + OFF_W2 + row * CLOSURE_HIDDEN + 32 * ks + fk);
     }
-    __syncthreads();  // the previous step's fragments are read
-    *reinterpret_cast<uint4*>(&As[sr * GLD + sk]) = pack8(ha);
-    *reinterpret_cast<uint4*>(&Bs[sr * GLD + sk]) = pack8(hb);
-    __syncthreads();
-    const int fk = 8 * (lane >> 4);
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) {
+    const uint4 v = bf16_row8(P + OFF_W3 + min(pt, CLOSURE_OUT - 1) * CLOSURE_HIDDEN + 32 * ks + fk);
+    w3[ks] = pt < CLOSURE_OUT ? v : make_uint4(0, 0, 0, 0);
+  }
+  if constexpr (TRAIN) {
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      const uint4 a = *reinterpret_cast<const uint4*>(&As[(wm + 16 * i + (lane & 15)) * GLD + fk]);
+      const int unit = u0 + 16 * i + pt;
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const uint4 b = *reinterpret_cast<const uint4*>(&Bs[(wn + 16 * j + (lane & 15)) * GLD + fk]);
-        acc[i][j] = mfma16(a, b, acc[i][j]);
+      for (int ks = 0; ks < 4; ++ks) {
+        uint32_t h[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) h[e] = bf16_bits(P[OFF_W2 + (32 * ks + fk + e) * CLOSURE_HIDDEN + unit]);
+        w2t[i][ks] = pack8(h);
       }
+      uint32_t h[8] = {};
+#pragma unroll
+      for (int e = 0; e < CLOSURE_OUT; ++e) h[e] = bf16_bits(P[OFF_W3 + e * CLOSURE_HIDDEN + unit]);
+      const uint4 v = pack8(h);
+      w3t[i] = grp == 0 ? v : make_uint4(0, 0, 0, 0);
     }
   }
-  float* P = g.P + int64_t(blockIdx.z) * g.M * g.N;
+  // biases of the lane's outputs: units u0 + 16 i + 4 grp + r, outputs 4 grp + r
+  f32x4 b1[2], b2[2], b3;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int r = 0; r < 4; ++r) {
+      b1[i][r] = P[OFF_B1 + u0 + 16 * i + 4 * grp + r];
+      b2[i][r] = P[OFF_B2 + u0 + 16 * i + 4 * grp + r];
+    }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) b3[r] = P[OFF_B3 + min(4 * grp + r, CLOSURE_OUT - 1)];
+
+  // a layer: the lane's four units x two tiles of point pt
+  auto product = [&](const uint4 (&wf)[2][4], const uint16_t* S, f32x4 (&acc)[2]) {
+    acc[0] = acc[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const uint4 x = *reinterpret_cast<const uint4*>(&S[pt * LDT + 32 * ks + fk]);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) acc[i] = mfma16(wf[i][ks], x, acc[i]);
+    }
+  };
+  auto put = [&](uint16_t* S, int i, const float (&v)[4]) {
+    *reinterpret_cast<uint2*>(&S[pt * LDT + u0 + 16 * i + 4 * grp]) =
+        make_uint2(bf16_bits(v[0]) | (bf16_bits(v[1]) << 16), bf16_bits(v[2]) | (bf16_bits(v[3]) << 16));
+  };
+
+  double loss = 0.0;
+  const float scale = 2.0f / float(int64_t(g.B) * CLOSURE_OUT);
+  const int nblk = (g.B + TR - 1) / TR;
+  for (int blk = int(blockIdx.x); blk < nblk; blk += int(gridDim.x)) {
+    const int b0 = blk * TR, b = b0 + pt;
+    const bool live = b < g.B;
+    float tv[4] = {};
+    if (TRAIN && w == 0 && live) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (4 * grp + r < CLOSURE_OUT) tv[r] = g.t[int64_t(b) * CLOSURE_OUT + 4 * grp + r];
+    }
+    {  // rows past the batch are zeros (and so are their activations below)
+      const int row = tid >> 4, col = 8 * (tid & 15);
+      uint4 v = make_uint4(0, 0, 0, 0);
+      if (b0 + row < g.B) v = bf16_row8(g.x + int64_t(b0 + row) * CLOSURE_IN + col);
+      *reinterpret_cast<uint4*>(&Xs[row * LDT + col]) = v;
+    }
+    __syncthreads();
+    f32x4 z1[2], z2[2];
+    product(w1, Xs, z1);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      float v[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int m = m0 + wm + 16 * i + 4 * (lane >> 4) + r;
-        const int n = n0 + wn + 16 * j + (lane & 15);
-        if (m < g.M && n < g.N) P[int64_t(m) * g.N + n] = acc[i][j][r];
+        z1[i][r] += b1[i][r];
+        v[r] = live ? gelu(z1[i][r]) : 0.f;
       }
-}
-
-// Sum of the split partials in split order, then the epilogue.
-__global__ void __launch_bounds__(256) gemm_epilogue_kernel(const EpiArgs e) {
-  const int64_t total = int64_t(e.M) * e.N;
-  for (int64_t t = blockIdx.x * int64_t(256) + threadIdx.x; t < total; t += int64_t(gridDim.x) * 256) {
-    const int m = int(t / e.N), n = int(t % e.N);
-    float acc = 0.f;
-    for (int z = 0; z < e.splits; ++z) acc += e.P[z * total + t];
-    if (e.bias) acc += e.bias[n];
-    if (e.mode == EPI_STORE) {
-      e.out[int64_t(m) * e.ldo + n] = acc;
-    } else if (e.mode == EPI_GELU) {
-      e.out[int64_t(m) * e.ldo + n] = acc;
-      e.out2[int64_t(m) * e.ldo + n] = gelu(acc);
-    } else {  // EPI_GELU_GRAD
-      e.out[int64_t(m) * e.ldo + n] = acc * gelu_grad(e.aux[int64_t(m) * e.ldaux + n]);
+      put(H1, i, v);
+    }
+    if constexpr (TRAIN) store_transposed(Xs, g.xt, b0);
+    __syncthreads();
+    product(w2, H1, z2);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      float v[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        z2[i][r] += b2[i][r];
+        v[r] = live ? gelu(z2[i][r]) : 0.f;
+      }
+      put(H2, i, v);
+    }
+    if constexpr (TRAIN) store_transposed(H1, g.h1t, b0);
+    __syncthreads();
+    if (w == 0) {
+      f32x4 y = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+        y = mfma16(w3[ks], *reinterpret_cast<const uint4*>(&H2[pt * LDT + 32 * ks + fk]), y);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int o = 4 * grp + r;
+        const float yv = y[r] + b3[r];
+        if constexpr (TRAIN) {
+          const float d = yv - tv[r];
+          const float dy = live && o < CLOSURE_OUT ? scale * d : 0.f;
+          if (o < 8) {
+            Ys[pt * 8 + o] = uint16_t(bf16_bits(dy));
+            g.dyt[t_index(b, 8, o)] = uint16_t(bf16_bits(dy));
+          }
+          if (live && o < CLOSURE_OUT) {
+            g.dy[int64_t(b) * CLOSURE_OUT + o] = dy;
+            loss += double(d) * double(d);
+          }
+        } else if (live && o < CLOSURE_OUT) {
+          g.y[int64_t(b) * CLOSURE_OUT + o] = yv;
+        }
+      }
+    }
+    if constexpr (TRAIN) {
+      store_transposed(H2, g.h2t, b0);
+      __syncthreads();
+      // dZ2 = (dY W3) * gelu'(Z2), dZ1 = (dZ2 W2) * gelu'(Z1)
+      uint4 yf = *reinterpret_cast<const uint4*>(&Ys[pt * 8]);
+      if (grp) yf = make_uint4(0, 0, 0, 0);
+      auto back = [&](const f32x4 (&acc)[2], const f32x4 (&z)[2], uint16_t* S, float* out) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          float v[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) v[r] = live ? acc[i][r] * gelu_grad(z[i][r]) : 0.f;
+          put(S, i, v);
+          if (live)
+            *reinterpret_cast<float4*>(&out[int64_t(b) * CLOSURE_HIDDEN + u0 + 16 * i + 4 * grp]) =
+                make_float4(v[0], v[1], v[2], v[3]);
+        }
+      };
+      f32x4 acc[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) acc[i] = mfma16(w3t[i], yf, f32x4{0.f, 0.f, 0.f, 0.f});
+      back(acc, z2, D2, g.dz2);
+      __syncthreads();
+      product(w2t, D2, acc);
+      back(acc, z1, D1, g.dz1);
+      store_transposed(D2, g.dz2t, b0);
+      __syncthreads();
+      store_transposed(D1, g.dz1t, b0);
+    }
+    // (the next block writes Xs, H1, H2 and Ys behind barriers that follow every
+    // read of them here; H2, read by wave 0 above, waits for the next block's
+    // two barriers, and D1 for more)
+  }
+  if constexpr (TRAIN) {
+    if (w == 0) {
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) loss += __shfl_xor(loss, d);
+      if (lane == 0) g.lpart[blockIdx.x] = loss;
     }
   }
 }
 
-// Column sums of X (M x N, row stride ld) in a fixed order: partial sums of
-// row chunks, then the chunks in order.
+// Sum of n values in order, the loads of 16 in flight together.
+__device__ __forceinline__ float sum_strided(const float* q, int n, int step) {
+  float a = 0.f;
+  int z = 0;
+  for (; z + 16 <= n; z += 16) {
+    float v[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) v[e] = q[int64_t(z + e) * step];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) a += v[e];
+  }
+  for (; z < n; ++z) a += q[int64_t(z) * step];
+  return a;
+}
+
+// Weight gradients, G (M x 128) = D^T A over the batch, as partials per split of
+// kchunk rows, and partial column sums of the unrounded dZ1, dZ2 and dY (the
+// biases' gradients) per chunk of 256 rows.  A workgroup is one 64 x 64 tile of
+// W1 or W2 (or all of W3) of one split, fragments straight from memory (the
+// operands are laid out for it: no LDS, every load of eight k steps in flight
+// together), or 64 columns of a chunk's sums.
 constexpr int CS_ROWS = 256;
-__global__ void __launch_bounds__(256) colsum_partial_kernel(const float* X, int M, int N, int64_t ld, float* part) {
+constexpr int GRAD_TILES = 9;  // four of W1, four of W2, W3
+constexpr int SUM_TILES = 5;   // dZ1 and dZ2 64 columns each, dY
+__global__ void __launch_bounds__(256) mlp_grad_kernel(const MlpGrad g) {
   __shared__ float s[4][64];
-  const int c = blockIdx.x * 64 + (threadIdx.x & 63), ph = threadIdx.x >> 6;
-  const int r0 = blockIdx.y * CS_ROWS, r1 = min(M, r0 + CS_ROWS);
+  const int tid = int(threadIdx.x), lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int id = int(blockIdx.x);
+  if (id < g.splits * GRAD_TILES) {
+    const int z = id / GRAD_TILES, tile = id - z * GRAD_TILES;
+    const int layer = tile >> 2;  // 0: W1, 1: W2, 2: W3
+    const uint16_t* D = layer == 0 ? g.dz1t : layer == 1 ? g.dz2t : g.dyt;
+    const uint16_t* A = layer == 0 ? g.xt : layer == 1 ? g.h1t : g.h2t;
+    const int units = layer == 2 ? 8 : CLOSURE_HIDDEN;
+    const int m0 = layer == 2 ? 0 : (tile >> 1 & 1) * 64 + (w >> 1) * 32;
+    const int n0 = layer == 2 ? 32 * w : (tile & 1) * 64 + (w & 1) * 32;
+    const int pt = lane & 15, fk = 8 * (lane >> 4);
+    const int kb = z * g.kchunk, ke = min(g.B, kb + g.kchunk);
+    f32x4 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // (rows of W3 past its eight repeat the last one and are not stored)
+    auto frag = [&](const uint16_t* T, int n, int unit, int k) {
+      return *reinterpret_cast<const uint4*>(&T[t_index(k + fk, n, min(unit, n - 1))]);
+    };
+    auto step = [&](const uint4 (&a)[2], const uint4 (&b)[2]) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = mfma16(a[i], b[j], acc[i][j]);
+    };
+    constexpr int DEEP = 8;  // k steps whose loads are in flight together
+    int k = kb;
+    for (; k + DEEP * KT <= ke; k += DEEP * KT) {
+      uint4 a[DEEP][2], b[DEEP][2];
+#pragma unroll
+      for (int d = 0; d < DEEP; ++d)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          a[d][i] = frag(D, units, m0 + 16 * i + pt, k + d * KT);
+          b[d][i] = frag(A, CLOSURE_HIDDEN, n0 + 16 * i + pt, k + d * KT);
+        }
+#pragma unroll
+      for (int d = 0; d < DEEP; ++d) step(a[d], b[d]);
+    }
+    for (; k < ke; k += KT) {
+      uint4 a[2], b[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        a[i] = frag(D, units, m0 + 16 * i + pt, k);
+        b[i] = frag(A, CLOSURE_HIDDEN, n0 + 16 * i + pt, k);
+        if (k + fk >= ke) a[i] = b[i] = make_uint4(0, 0, 0, 0);  // eight rows past the batch
+      }
+      step(a, b);
+    }
+    float* P = g.part + int64_t(z) * CLOSURE_PARAMS + (layer == 0 ? OFF_W1 : layer == 1 ? OFF_W2 : OFF_W3);
+    const int M = layer == 2 ? CLOSURE_OUT : CLOSURE_HIDDEN;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int m = m0 + 16 * i + 4 * (lane >> 4) + r, n = n0 + 16 * j + pt;
+          if (m < M) P[m * CLOSURE_HIDDEN + n] = acc[i][j][r];
+        }
+    return;
+  }
+  id -= g.splits * GRAD_TILES;
+  const int chunk = id / SUM_TILES, part = id - chunk * SUM_TILES;
+  const float* X = part < 2 ? g.dz1 : part < 4 ? g.dz2 : g.dy;
+  const int N = part < 4 ? CLOSURE_HIDDEN : CLOSURE_OUT;
+  const int c = (part < 4 ? (part & 1) * 64 : 0) + lane;
+  const int r0 = chunk * CS_ROWS, r1 = min(g.B, r0 + CS_ROWS);
   float a = 0.f;
-  if (c < N)
-    for (int r = r0 + ph; r < r1; r += 4) a += X[int64_t(r) * ld + c];
-  s[ph][threadIdx.x & 63] = a;
+  if (c < N) a = sum_strided(X + int64_t(r0 + w) * N + c, r1 > r0 + w ? (r1 - r0 - w + 3) / 4 : 0, 4 * N);
+  s[w][lane] = a;
   __syncthreads();
-  if (ph == 0 && c < N) part[int64_t(blockIdx.y) * N + c] = ((s[0][threadIdx.x] + s[1][threadIdx.x]) + s[2][threadIdx.x]) + s[3][threadIdx.x];
-}
-
-__global__ void __launch_bounds__(256) colsum_final_kernel(const float* part, int chunks, int N, float* out) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= N) return;
-  float a = 0.f;
-  for (int z = 0; z < chunks; ++z) a += part[int64_t(z) * N + c];
-  out[c] = a;
-}
-
-// dY = 2 (Y - T) / count and per-block partial sums of (Y - T)^2 in FP64.
-__global__ void __launch_bounds__(256) mse_kernel(const float* Y, const float* T, int64_t count, float* dY,
-                                                  double* part) {
-  __shared__ double s[256];
-  double a = 0.0;
-  const float scale = 2.0f / float(count);
-  for (int64_t t = blockIdx.x * int64_t(256) + threadIdx.x; t < count; t += int64_t(gridDim.x) * 256) {
-    const float d = Y[t] - T[t];
-    dY[t] = scale * d;
-    a += double(d) * double(d);
-  }
-  s[threadIdx.x] = a;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) part[blockIdx.x] = s[0];
-}
-
-__global__ void __launch_bounds__(256) sum_final_kernel(const double* part, int n, double scale, double* out) {
-  __shared__ double s[256];
-  double a = 0.0;
-  for (int i = threadIdx.x; i < n; i += 256) a += part[i];
-  s[threadIdx.x] = a;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[0] = s[0] * scale;
+  if (w == 0 && c < N)
+    g.cpart[int64_t(chunk) * SUM_COLS + (part >> 1) * CLOSURE_HIDDEN + c] =
+        ((s[0][lane] + s[1][lane]) + s[2][lane]) + s[3][lane];
 }
 
 // Adam with bias correction; c1 = 1 - beta1^t, c2 = 1 - beta2^t.
-__global__ void __launch_bounds__(256) adam_kernel(float* p, const float* g, float* m, float* v, int64_t n, float lr,
-                                                   float b1, float b2, float eps, float c1, float c2) {
-  for (int64_t i = blockIdx.x * int64_t(256) + threadIdx.x; i < n; i += int64_t(gridDim.x) * 256) {
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.f - b1) * gi;
-    const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+__device__ __forceinline__ void adam(const MlpAdam& a, int i, float gi) {
+  const float mi = a.b1 * a.m[i] + (1.f - a.b1) * gi;
+  const float vi = a.b2 * a.v[i] + (1.f - a.b2) * gi * gi;
+  a.m[i] = mi;
+  a.v[i] = vi;
+  a.p[i] -= a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
+}
+__global__ void __launch_bounds__(256) adam_kernel(const MlpAdam a, const float* grads) {
+  const int i = int(blockIdx.x) * 256 + int(threadIdx.x);
+  if (i < CLOSURE_PARAMS) adam(a, i, grads[i]);
+}
+
+// Sums of the partials in split (chunk) order: the gradient, then (with a.p) the
+// Adam update; the last workgroup sums the loss.
+__global__ void __launch_bounds__(256) mlp_update_kernel(const MlpGrad g, float* __restrict__ grads, const MlpAdam a,
+                                                         const double* __restrict__ lpart, const int nloss,
+                                                         double* __restrict__ loss) {
+  if (blockIdx.x == gridDim.x - 1) {
+    __shared__ double s[256];
+    double v = 0.0;
+    for (int i = int(threadIdx.x); i < nloss; i += 256) v += lpart[i];
+    s[threadIdx.x] = v;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+      if (int(threadIdx.x) < w) s[threadIdx.x] += s[threadIdx.x + w];
+      __syncthreads();
+    }
+    if (threadIdx.x == 0) loss[0] = s[0] * (1.0 / double(int64_t(g.B) * CLOSURE_OUT));
+    return;
   }
+  const int i = int(blockIdx.x) * 256 + int(threadIdx.x);
+  if (i >= CLOSURE_PARAMS) return;
+  // biases lie behind their layer's weights
+  int col = -1;
+  if (i >= OFF_B3)
+    col = 2 * CLOSURE_HIDDEN + i - OFF_B3;
+  else if (i >= OFF_B2 && i < OFF_W3)
+    col = CLOSURE_HIDDEN + i - OFF_B2;
+  else if (i >= OFF_B1 && i < OFF_W2)
+    col = i - OFF_B1;
+  const float* q = col < 0 ? g.part + i : g.cpart + col;
+  const int n = col < 0 ? g.splits : (g.B + CS_ROWS - 1) / CS_ROWS, step = col < 0 ? CLOSURE_PARAMS : SUM_COLS;
+  const float acc = sum_strided(q, n, step);
+  grads[i] = acc;
+  if (a.p) adam(a, i, acc);
 }
 
 // ------------------------------------------------------------ closure inputs
@@ -645,42 +871,49 @@ __global__ void __launch_bounds__(256, 3) closure_infer_kernel(T* __restrict__ U
 }
 
 // ------------------------------------------------------------ launches
-hipError_t launch_gemm(const GemmArgs& g, int splits, const EpiArgs& e, hipStream_t stream) {
-  if (g.M <= 0 || g.N <= 0 || g.K < 0 || splits < 1) return hipErrorInvalidValue;
-  dim3 grid((g.N + GT - 1) / GT, (g.M + GT - 1) / GT, splits);
-  hipLaunchKernelGGL(gemm_bf16_kernel, grid, dim3(256), 0, stream, g);
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
-  const int64_t total = int64_t(g.M) * g.N;
-  const int blocks = int(std::min<int64_t>((total + 255) / 256, 4096));
-  hipLaunchKernelGGL(gemm_epilogue_kernel, dim3(blocks), dim3(256), 0, stream, e);
+namespace {
+int device_cus() {
+  static int cus = 0;
+  if (!cus) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+      cus = 256;
+  }
+  return cus;
+}
+}  // namespace
+
+int mlp_row_blocks(int B) { return std::min((B + TR - 1) / TR, 2 * device_cus()); }
+int mlp_sum_chunks(int B) { return (B + CS_ROWS - 1) / CS_ROWS; }
+
+hipError_t launch_mlp_rows(const MlpRows& g, bool train, hipStream_t stream) {
+  if (g.B < 1) return hipErrorInvalidValue;
+  const dim3 grid(mlp_row_blocks(g.B));
+  if (train)
+    hipLaunchKernelGGL(mlp_rows_kernel<true>, grid, dim3(256), 0, stream, g);
+  else
+    hipLaunchKernelGGL(mlp_rows_kernel<false>, grid, dim3(256), 0, stream, g);
   return hipGetLastError();
 }
 
-hipError_t launch_colsum(const float* X, int M, int N, int64_t ld, float* part, float* out, hipStream_t stream) {
-  const int chunks = (M + CS_ROWS - 1) / CS_ROWS;
-  hipLaunchKernelGGL(colsum_partial_kernel, dim3((N + 63) / 64, chunks), dim3(256), 0, stream, X, M, N, ld, part);
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(colsum_final_kernel, dim3((N + 255) / 256), dim3(256), 0, stream, part, chunks, N, out);
+hipError_t launch_mlp_grad(const MlpGrad& g, hipStream_t stream) {
+  if (g.B < 1 || g.splits < 1 || g.kchunk < KT || g.kchunk % KT) return hipErrorInvalidValue;
+  const int64_t blocks = int64_t(g.splits) * GRAD_TILES + int64_t(mlp_sum_chunks(g.B)) * SUM_TILES;
+  hipLaunchKernelGGL(mlp_grad_kernel, dim3(unsigned(blocks)), dim3(256), 0, stream, g);
   return hipGetLastError();
 }
 
-int colsum_part_floats(int M, int N) { return ((M + CS_ROWS - 1) / CS_ROWS) * N; }
-
-hipError_t launch_mse(const float* Y, const float* T, int64_t count, float* dY, double* part, int nblocks,
-                      double* out, hipStream_t stream) {
-  hipLaunchKernelGGL(mse_kernel, dim3(nblocks), dim3(256), 0, stream, Y, T, count, dY, part);
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
-  hipLaunchKernelGGL(sum_final_kernel, dim3(1), dim3(256), 0, stream, part, nblocks, 1.0 / double(count), out);
+hipError_t launch_mlp_update(const MlpGrad& g, float* grads, const MlpAdam& a, const double* lpart, double* loss,
+                             hipStream_t stream) {
+  const int blocks = (CLOSURE_PARAMS + 255) / 256 + 1;
+  hipLaunchKernelGGL(mlp_update_kernel, dim3(blocks), dim3(256), 0, stream, g, grads, a, lpart, mlp_row_blocks(g.B),
+                     loss);
   return hipGetLastError();
 }
 
-hipError_t launch_adam(float* p, const float* g, float* m, float* v, int64_t n, float lr, float b1, float b2,
-                       float eps, float c1, float c2, hipStream_t stream) {
-  const int blocks = int(std::min<int64_t>((n + 255) / 256, 1024));
-  hipLaunchKernelGGL(adam_kernel, dim3(blocks), dim3(256), 0, stream, p, g, m, v, n, lr, b1, b2, eps, c1, c2);
+hipError_t launch_adam(const MlpAdam& a, const float* grads, hipStream_t stream) {
+  hipLaunchKernelGGL(adam_kernel, dim3((CLOSURE_PARAMS + 255) / 256), dim3(256), 0, stream, a, grads);
   return hipGetLastError();
 }
 
@@ -728,17 +961,6 @@ hipError_t launch_infer_t(void* U, const void* in5, void* out5, const void* deca
                      static_cast<T*>(U), static_cast<const T*>(in5), static_cast<T*>(out5),
                      static_cast<const C*>(decay), G, net, odd, insts, bfirst, n_active, j);
   return hipGetLastError();
-}
-
-int device_cus() {
-  static int cus = 0;
-  if (!cus) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-      cus = 256;
-  }
-  return cus;
 }
 
 // a few workgroups per compute unit, each looping over blocks of points with

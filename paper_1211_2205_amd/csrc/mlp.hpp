@@ -20,6 +20,15 @@ constexpr double CLOSURE_EPS = 1e-20; // added to the stencil norm
 constexpr int CLOSURE_PARAMS = CLOSURE_HIDDEN * CLOSURE_IN + CLOSURE_HIDDEN + CLOSURE_HIDDEN * CLOSURE_HIDDEN +
                                CLOSURE_HIDDEN + CLOSURE_OUT * CLOSURE_HIDDEN + CLOSURE_OUT;
 
+// offsets of its parts
+constexpr int OFF_W1 = 0;
+constexpr int OFF_B1 = OFF_W1 + CLOSURE_HIDDEN * CLOSURE_IN;
+constexpr int OFF_W2 = OFF_B1 + CLOSURE_HIDDEN;
+constexpr int OFF_B2 = OFF_W2 + CLOSURE_HIDDEN * CLOSURE_HIDDEN;
+constexpr int OFF_W3 = OFF_B2 + CLOSURE_HIDDEN;
+constexpr int OFF_B3 = OFF_W3 + CLOSURE_OUT * CLOSURE_HIDDEN;
+static_assert(OFF_B3 + CLOSURE_OUT == CLOSURE_PARAMS, "parameter blob layout");
+
 // Network as the fused kernel reads it: bfloat16 weight rows of W1, W2 and W3
 // (padded to 16 rows of zeros), then FP32 biases (b3 padded to 16).
 struct ClosureNet {
@@ -86,37 +95,44 @@ struct ClosureInst {
   ClosureOdd odd;
 };
 
-struct GemmArgs {
-  const float* A;
-  int64_t sam, sak;
-  const float* B;
-  int64_t sbk, sbn;
-  float* P;   // split partials, splits x M x N
-  int M, N, K;
-  int kchunk; // K per split, a multiple of 32
+// A batch's rows through the network.  Training also writes dY, dZ1 and dZ2
+// (B x 6, B x 128, FP32), the operands of the weight gradients as transposed
+// bfloat16 (blocks of 32 rows: [unit][row]; 128 units, dyt 8) and the loss's
+// partial sums, one per workgroup.
+struct MlpRows {
+  const float* x;       // B x 128
+  const float* t;       // B x 6 (training)
+  const float* params;
+  int B;
+  float* y;             // B x 6 (forward only)
+  float *dy, *dz1, *dz2;
+  uint16_t *xt, *h1t, *h2t, *dz1t, *dz2t, *dyt;
+  double* lpart;
 };
+int mlp_row_blocks(int B);  // workgroups of launch_mlp_rows
+hipError_t launch_mlp_rows(const MlpRows& g, bool train, hipStream_t stream);
 
-enum EpiMode : int { EPI_STORE = 0, EPI_GELU = 1, EPI_GELU_GRAD = 2 };
-
-struct EpiArgs {
-  const float* P;
-  int splits, M, N;
-  const float* bias;  // may be null
-  int mode;
-  const float* aux;   // EPI_GELU_GRAD: pre-activations
-  int64_t ldaux;
-  float* out;         // EPI_STORE: sum (+ bias); EPI_GELU: pre-activation; EPI_GELU_GRAD: sum * gelu'(aux)
-  int64_t ldo;
-  float* out2;        // EPI_GELU: gelu(pre-activation)
+// The weight gradients' partials (splits of kchunk rows, a multiple of 32, each
+// in the parameter blob's layout) and the column sums' (per 256 rows).
+constexpr int SUM_COLS = 2 * CLOSURE_HIDDEN + CLOSURE_OUT;
+struct MlpGrad {
+  const float *dy, *dz1, *dz2;
+  const uint16_t *xt, *h1t, *h2t, *dz1t, *dz2t, *dyt;
+  float *part, *cpart;
+  int B, splits, kchunk;
 };
+int mlp_sum_chunks(int B);
+hipError_t launch_mlp_grad(const MlpGrad& g, hipStream_t stream);
 
-hipError_t launch_gemm(const GemmArgs& g, int splits, const EpiArgs& e, hipStream_t stream);
-hipError_t launch_colsum(const float* X, int M, int N, int64_t ld, float* part, float* out, hipStream_t stream);
-int colsum_part_floats(int M, int N);
-hipError_t launch_mse(const float* Y, const float* T, int64_t count, float* dY, double* part, int nblocks,
-                      double* out, hipStream_t stream);
-hipError_t launch_adam(float* p, const float* g, float* m, float* v, int64_t n, float lr, float b1, float b2,
-                       float eps, float c1, float c2, hipStream_t stream);
+// Adam state and constants; p = null: no update.
+struct MlpAdam {
+  float *p, *m, *v;
+  float lr, b1, b2, eps, c1, c2;
+};
+// Sums of the partials into grads (in their order), the update, the loss.
+hipError_t launch_mlp_update(const MlpGrad& g, float* grads, const MlpAdam& a, const double* lpart, double* loss,
+                             hipStream_t stream);
+hipError_t launch_adam(const MlpAdam& a, const float* grads, hipStream_t stream);
 hipError_t launch_closure_samples(int storage, const void* U, const void* decay, const ClosureGeo& G,
                                   const int* pts, int count, float* feat, float* targ, float* nu,
                                   hipStream_t stream);
