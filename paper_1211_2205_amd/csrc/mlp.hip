@@ -25,7 +25,9 @@
 namespace starmap {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 // ------------------------------------------------------------ scalar helpers
 __device__ __forceinline__ uint32_t bf16_bits(float v) { return from_c<bf16>(v).bits; }
@@ -47,17 +49,24 @@ __device__ __forceinline__ uint32_t bf16_hw(float v) {
 __device__ __forceinline__ uint32_t bf16_in(float v) { return bf16_hw(v); }
 __device__ __forceinline__ uint32_t bf16_in(double v) { return bf16_bits(v); }
 
+// Two of them, packed.
+__device__ __forceinline__ uint32_t bf16_hw2(float lo, float hi) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{lo, hi}), bf16x2));
+}
+
 // GELU z Phi(z), Phi the standard normal distribution function, with erf
 // from Abramowitz & Stegun, Handbook of Mathematical Functions, formula 7.1.26
 // (|error| <= 1.5e-7 on the real line).  Training and inference use this one
-// definition.
+// definition.  The formula's coefficients are halved (exactly), so that erf / 2
+// comes out without a multiplication by a half.
 __device__ __forceinline__ float normal_cdf(float z) {
   const float x = fabsf(z) * 0.70710678118654752f;
   const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, x, 1.0f));
-  const float poly =
-      t * fmaf(t, fmaf(t, fmaf(t, fmaf(t, 1.061405429f, -1.453152027f), 1.421413741f), -0.284496736f), 0.254829592f);
-  const float erf_abs = 1.0f - poly * __expf(-x * x);
-  return 0.5f * (1.0f + copysignf(erf_abs, z));
+  const float half_poly =
+      t * fmaf(t, fmaf(t, fmaf(t, fmaf(t, 0.5f * 1.061405429f, 0.5f * -1.453152027f), 0.5f * 1.421413741f),
+                       0.5f * -0.284496736f), 0.5f * 0.254829592f);
+  const float half_erf_abs = fmaf(-half_poly, __expf(-x * x), 0.5f);
+  return 0.5f + copysignf(half_erf_abs, z);
 }
 __device__ __forceinline__ float gelu(float z) { return z * normal_cdf(z); }
 // d/dz z Phi(z) = Phi(z) + z phi(z)
@@ -544,17 +553,231 @@ __global__ void __launch_bounds__(256) closure_samples_kernel(const T* __restric
   }
 }
 
+// ------------------------------------------------------------ closure network
+// The closure terms g = nu y / dx of every evaluation point of the
+// (nx + 1) x (ny + 1) index domain, into the closure planes of the order-5
+// moments (which the odd sweep then reads like source planes).
+//
+// One workgroup of 16 waves per compute unit keeps the network in LDS; every
+// wave takes blocks of 16 points through all of it by itself: gather and
+// normalise the inputs, three layers of MFMA products, the outputs.  The layers
+// are computed transposed, H^T = W X^T: the weights are the A operand, the
+// activations the B operand, read from the wave's own LDS rows [point][unit],
+// and each lane's four outputs (consecutive units of one point) go back there
+// with one 8-byte write.  Once the weights are staged no wave waits for
+// another, and the stencil's values stay in registers between the sum of their
+// squares and their normalisation.
+//
+// What bounds it: the GELUs' vector instructions, 256 per point of some 18
+// instructions and two transcendentals, 7200 of the 9300 cycles that a block
+// takes of its SIMD when there are many (15.5 us per 4096 blocks); launching,
+// staging and the first gather take 5 us more.  At 257^2 points, FP32, 23 us,
+// where blocks of 64 points by four waves with the weights in registers, a
+// barrier between the layers and three workgroups per compute unit took 33: two
+// rounds of blocks where 1.3 were needed, each wave waiting for the slowest.
+//
+// BATCH: every running instance of a batch of closure solvers sharing one
+// network; instance i (of the n_active still running) owns the blocks of CB
+// points [bfirst[i], bfirst[i + 1]) and brings its own state and geometry
+// (insts[i]); the arguments U0, decay0 and G0 are unused.
+constexpr int CB = 64;               // evaluation points per block of the fused kernel and of batches' tables
+constexpr int LDW = CLOSURE_IN + 8;  // LDS row of one point's activations or one unit's weights (bf16), padded
+constexpr int NW = 16;               // waves per workgroup
+constexpr int NPT = 16;              // points per wave
+constexpr int NROWS = 2 * CLOSURE_HIDDEN + 16;  // weight rows: W1, W2, W3 (padded to 16)
+constexpr size_t kNetLds = size_t(NROWS + NW * NPT) * LDW * 2 + size_t(2 * CLOSURE_HIDDEN + 16) * 4 + NW * 40 * 4;
+
+// A pointer read from a table, as one to global memory.
+template <typename T>
+__device__ __forceinline__ T* in_global(T* p) {
+  return (T*)(__attribute__((address_space(1))) T*)p;
+}
+
+template <typename T, bool BATCH>
+__global__ void __launch_bounds__(64 * NW) closure_net_kernel(T* __restrict__ U0,
+                                                              const typename ComputeOf<T>::type* __restrict__ decay0,
+                                                              const ClosureGeo G0, const ClosureNet* __restrict__ net,
+                                                              const ClosureInst* __restrict__ insts,
+                                                              const int* __restrict__ bfirst, const int n_active) {
+  using C = typename ComputeOf<T>::type;
+  extern __shared__ __align__(16) unsigned char smem[];
+  uint16_t* const Ws = reinterpret_cast<uint16_t*>(smem);  // [NROWS][LDW]
+  float* const bias = reinterpret_cast<float*>(Ws + NROWS * LDW);  // b1, b2, b3
+  const int tid = int(threadIdx.x), lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int pt = lane & 15, grp = lane >> 4, fk = 8 * grp;
+  uint16_t* const X = reinterpret_cast<uint16_t*>(bias + 2 * CLOSURE_HIDDEN + 16) + w * NPT * LDW;  // this wave's rows
+  int* const otab =  // this wave's output geometry: plane, extents, nodal flags by output
+      reinterpret_cast<int*>(reinterpret_cast<uint16_t*>(bias + 2 * CLOSURE_HIDDEN + 16) + NW * NPT * LDW) + w * 40;
+
+  {
+    const uint4* wv = reinterpret_cast<const uint4*>(net->w);  // rows of CLOSURE_IN / 8
+    constexpr int Q = CLOSURE_IN / 8;
+    for (int e = tid; e < NROWS * Q; e += 64 * NW)
+      *reinterpret_cast<uint4*>(&Ws[(e / Q) * LDW + (e % Q) * 8]) = wv[e];
+    for (int e = tid; e < 2 * CLOSURE_HIDDEN + 16; e += 64 * NW)
+      bias[e] = e < CLOSURE_HIDDEN       ? net->b1[e]
+                : e < 2 * CLOSURE_HIDDEN ? net->b2[e - CLOSURE_HIDDEN]
+                                         : net->b3[e - 2 * CLOSURE_HIDDEN];
+  }
+  bool staged = false;
+
+  // this workgroup's blocks of 16 points, round robin over its waves
+  constexpr int SUB = CB / NPT;
+  const int total0 = (G0.nx + 1) * (G0.ny + 1);
+  const int nblk = BATCH ? SUB * bfirst[n_active] : (total0 + NPT - 1) / NPT;
+  const int first = int(int64_t(nblk) * blockIdx.x / gridDim.x), last = int(int64_t(nblk) * (blockIdx.x + 1) / gridDim.x);
+  int inst_now = -1;
+  int kin[3], node[3];  // this lane's input moments: plane, nodal flags (1: x, 2: y)
+  for (int gblk = first + w; gblk < last; gblk += NW) {
+    int inst = 0;
+    if constexpr (BATCH) {
+      int lo = 0, hi = n_active - 1;  // last instance with bfirst[i] <= gblk / SUB
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (bfirst[mid] <= gblk / SUB) lo = mid; else hi = mid - 1;
+      }
+      inst = __builtin_amdgcn_readfirstlane(lo);
+    }
+    const int blk = BATCH ? gblk - SUB * bfirst[inst] : gblk;
+    const ClosureGeo& G = BATCH ? insts[inst].G : G0;
+    T* const U = BATCH ? in_global(static_cast<T*>(insts[inst].u)) : U0;
+    const C* const decay = BATCH ? in_global(static_cast<const C*>(insts[inst].decay)) : decay0;
+    if (inst != inst_now) {
+      // (indexed per lane: dependent loads, once per instance).  Lane group g
+      // has moments g, g + 4, g + 8; the twelfth does not exist: group 3 reads
+      // the fourth again, uncounted.
+#pragma unroll
+      for (int t = 0; t < 3; ++t) {
+        const int p = grp + 4 * t < CLOSURE_PLANES ? grp + 4 * t : 3;
+        kin[t] = G.k[p];
+        node[t] = (G.nodex[p] ? 1 : 0) | (G.nodey[p] ? 2 : 0);
+      }
+      if (lane < 40) {
+        const int f = lane >> 3, o = lane & 7;
+        int v = 0;
+        if (o < CLOSURE_OUT)
+          v = f == 0 ? G.q[o] : f == 1 ? G.out_nx[o] : f == 2 ? G.out_ny[o] : f == 3 ? G.out_nodex[o] : G.out_nodey[o];
+        otab[lane] = v;
+      }
+      inst_now = inst;
+    }
+    const int NXE = G.nx + 1, total = NXE * (G.ny + 1);
+    // 1. inputs: lane group g gathers moments g, g + 4, g + 8 of point pt
+    // (group 3: two moments and the material inputs)
+    const int p0 = blk * NPT + pt;
+    const bool live = p0 < total;
+    const int i = live ? p0 % NXE : 0, j = live ? p0 / NXE : 0;
+    // clamped (or wrapped) columns and rows of the stencil, per axis class:
+    // [0] cell-centred, [1] nodal
+    int colx[2][3], rowy[2][3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      colx[0][a] = min(max(i + a - 1, 0), G.nx - 1);
+      const int xn = min(max(i + a - 1, 0), G.nx - G.px);
+      colx[1][a] = G.px ? (xn + 1 == G.nx ? 0 : xn + 1) : xn;
+      rowy[0][a] = min(max(j + a - 1, 0), G.ny - 1) * G.pitch;
+      const int yn = min(max(j + a - 1, 0), G.ny - G.py);
+      rowy[1][a] = (G.py ? (yn + 1 == G.ny ? 0 : yn + 1) : yn) * G.pitch;
+    }
+    C v[3][9];
+    C ss = C(0);
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      const T* up = U + int64_t(kin[t]) * G.plane_stride;
+      int cx[3], ry[3];
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        cx[a] = node[t] & 1 ? colx[1][a] : colx[0][a];
+        ry[a] = node[t] & 2 ? rowy[1][a] : rowy[0][a];
+      }
+#pragma unroll
+      for (int q = 0; q < 9; ++q) v[t][q] = to_c(up[ry[q / 3] + cx[q % 3]]);
+    }
+    C sig_a = C(0), sig_t = C(0);
+    if (grp == 3) {
+      const int64_t o = int64_t(min(j, G.ny - 1)) * G.pitch + min(i, G.nx - 1);
+      sig_a = decay[int64_t(G.dk_a) * G.plane_stride + o];
+      sig_t = decay[int64_t(G.dk_t) * G.plane_stride + o];
+    }
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+      for (int q = 0; q < 9; ++q)
+        if (t < 2 || grp < 3) ss += v[t][q] * v[t][q];
+    const C nu = sqrt(((__shfl(ss, pt) + __shfl(ss, 16 + pt)) + __shfl(ss, 32 + pt)) + __shfl(ss, 48 + pt)) + C(CLOSURE_EPS);
+    const C rnu = C(1) / nu;
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+      for (int q = 0; q < 9; ++q)
+        if (t < 2 || grp < 3) X[pt * LDW + 9 * (grp + 4 * t) + q] = uint16_t(bf16_in(v[t][q] * rnu));
+    if (grp == 3) {
+      const C fa = log10(sig_a + C(0.01)), fs = log10((sig_t - sig_a) + C(0.01));
+      X[pt * LDW + 99] = uint16_t(bf16_bits(fa));
+      X[pt * LDW + 100] = uint16_t(bf16_bits(fs));
+      X[pt * LDW + 101] = 0;
+#pragma unroll
+      for (int q = 102; q < CLOSURE_IN; q += 2) *reinterpret_cast<uint32_t*>(&X[pt * LDW + q]) = 0;
+    }
+    if (!staged) {
+      __syncthreads();  // the weights are in LDS
+      staged = true;
+    }
+    // (a wave's LDS accesses keep their order; the fences keep the compiler's)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+
+    // 2. hidden layers: H^T (units x points) = W X^T, in place in the wave's rows
+#pragma unroll
+    for (int layer = 0; layer < 2; ++layer) {
+      uint4 xf[4];
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) xf[ks] = *reinterpret_cast<const uint4*>(&X[pt * LDW + 32 * ks + fk]);
+#pragma unroll sizeof(C) == 8 ? 4 : 8
+      for (int mi = 0; mi < CLOSURE_HIDDEN / 16; ++mi) {
+        f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+          acc = mfma16(*reinterpret_cast<const uint4*>(&Ws[(layer * CLOSURE_HIDDEN + 16 * mi + pt) * LDW + 32 * ks + fk]),
+                       xf[ks], acc);
+        // rows: units 16 mi + 4 grp + r; column: point pt
+        const int n = 16 * mi + 4 * grp;
+        const float4 bv = *reinterpret_cast<const float4*>(&bias[layer * CLOSURE_HIDDEN + n]);
+        *reinterpret_cast<uint2*>(&X[pt * LDW + n]) =
+            make_uint2(bf16_hw2(gelu(acc[0] + bv.x), gelu(acc[1] + bv.y)),
+                       bf16_hw2(gelu(acc[2] + bv.z), gelu(acc[3] + bv.w)));
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+
+    // 3. output layer: Y^T (16 x points) = W3 X^T
+    f32x4 y = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+      y = mfma16(*reinterpret_cast<const uint4*>(&Ws[(2 * CLOSURE_HIDDEN + pt) * LDW + 32 * ks + fk]),
+                 *reinterpret_cast<const uint4*>(&X[pt * LDW + 32 * ks + fk]), y);
+    if (live && grp < 2) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int o = 4 * grp + r;  // output of this lane
+        if (o >= CLOSURE_OUT || i >= otab[8 + o] || j >= otab[16 + o]) continue;
+        const int xo = internal_index(i, otab[24 + o], G.px, G.nx);
+        const int yo = internal_index(j, otab[32 + o], G.py, G.ny);
+        const C g = nu * C(y[r] + bias[2 * CLOSURE_HIDDEN + o]) / C(G.dx);
+        U[int64_t(otab[o]) * G.plane_stride + int64_t(yo) * G.pitch + xo] = from_c<T>(g);
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  }
+  if (!staged) __syncthreads();
+}
+
 // ------------------------------------------------------------ fused closure
-// Every workgroup keeps the network and loops over blocks of 64 evaluation
-// points of the (nx + 1) x (ny + 1) index domain: gather and normalise the
-// inputs, three MFMA layers, then nu * y / dx into the closure planes of the
-// order-5 moments.  The layers are computed transposed, H^T = W X^T: the
-// weights are the A operand and stay in registers (wave w owns hidden units
-// [32 w, 32 w + 32)), the activations are the B operand, read from LDS as
-// [point][unit] rows, and each lane's four outputs (consecutive units of one
-// point) go back with one 8-byte LDS write.
-constexpr int CB = 64;               // evaluation points per block
-constexpr int LDW = CLOSURE_IN + 8;  // LDS row of one point's activations (bf16), padded
+// The network and the odd sweep of P_5 in one kernel.  Every workgroup loops
+// over blocks of 64 evaluation points: gather and normalise the inputs, three
+// MFMA layers, then the odd update of the block's points.  The layers are
+// computed transposed as in the kernel above, but the weights stay in registers
+// (wave w owns hidden units [32 w, 32 w + 32)) and the activations go through
+// LDS as [point][unit] rows.
 
 // The odd update of one odd moment of P_5 at the internal point (X, Y) of its
 // grid, with the couplings in the order of the sweep kernel (x terms, then y
@@ -589,22 +812,18 @@ __device__ __forceinline__ C closure_odd_update(const T* __restrict__ U, const C
   return sub_step(u, W, c, E, tau);
 }
 
-// FUSED = false: the closure terms g = nu y / dx of every evaluation point go
-// to the closure planes, which the odd sweep then reads like source planes.
-// FUSED = true: the same network, then the odd sweep of P_5 at the block's
-// points in the same workgroup (every odd moment at every evaluation point
-// that lies on its grid), the order-5 moments read from in5 and written to
-// out5 (out of place, so every workgroup's stencils see the state of the
-// start of the sweep), orders 1 and 3 in place (nothing else reads them).
+// The network, then the odd sweep at the block's points in the same workgroup
+// (every odd moment at every evaluation point that lies on its grid), the
+// order-5 moments read from in5 and written to out5 (out of place, so every
+// workgroup's stencils see the state of the start of the sweep), orders 1 and 3
+// in place (nothing else reads them).
 //
 // BATCH = true: odd sweep number j of a batched run of closure solvers
 // sharing one network; instance i (of the n_active still running, sorted by
 // their sweep counts) owns the evaluation blocks [bfirst[i], bfirst[i + 1])
 // and brings its own state, geometry and odd rows (insts[i]); the arguments
-// U .. odd are unused.  With FUSED the kernel performs the odd sweeps as
-// above; without, it writes every instance's closure planes, and a batched
-// odd sweep follows.
-template <typename T, bool FUSED, bool BATCH>
+// U0 .. odd0 are unused.
+template <typename T, bool BATCH>
 __global__ void __launch_bounds__(256, 3) closure_infer_kernel(T* __restrict__ U0, const T* __restrict__ in5_0,
                                                             T* __restrict__ out5_0,
                                                             const typename ComputeOf<T>::type* __restrict__ decay0,
@@ -620,24 +839,9 @@ __global__ void __launch_bounds__(256, 3) closure_infer_kernel(T* __restrict__ U
   uint16_t* W3 = Xb + CB * LDW;                      // [16][LDW] output layer, rows >= 6 zero
   C* nu_s = reinterpret_cast<C*>(W3 + 16 * LDW);     // [64]
   C* part = nu_s + CB;                                    // [4][64] partial sums of squares per wave
-  int* otab = reinterpret_cast<int*>(part + 4 * CB);  // [5][8] output plane, extents, nodal flags
-  C* gsh = reinterpret_cast<C*>(otab + 5 * 8);        // FUSED: [6][64] closure terms of the block
+  C* gsh = part + 4 * CB;                                 // [6][64] closure terms of the block
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int fk = 8 * (lane >> 4);
-
-  // the output geometry, indexed per lane below, from LDS (indexing the
-  // kernel argument per lane would turn every access into a dependent load);
-  // batched: each block's instance's, written at the start of the block
-  auto fill_otab = [&](const ClosureGeo& G) {
-    if (tid < 5 * 8) {
-      const int f = tid >> 3, o = tid & 7;
-      int v = 0;
-      if (o < CLOSURE_OUT)
-        v = f == 0 ? G.q[o] : f == 1 ? G.out_nx[o] : f == 2 ? G.out_ny[o] : f == 3 ? G.out_nodex[o] : G.out_nodey[o];
-      otab[tid] = v;
-    }
-  };
-  if constexpr (!FUSED && !BATCH) fill_otab(G0);
 
   // this wave's weight fragments: rows 32 w + 16 mi + (lane % 16), k = 32 ks + fk
   const uint4* wv = reinterpret_cast<const uint4*>(net->w);  // rows of CLOSURE_IN / 8 uint4
@@ -675,11 +879,10 @@ __global__ void __launch_bounds__(256, 3) closure_infer_kernel(T* __restrict__ U
     const ClosureOdd& odd = BATCH ? insts[inst].odd : odd0;
     T* const U = BATCH ? static_cast<T*>(insts[inst].u) : U0;
     const C* const decay = BATCH ? static_cast<const C*>(insts[inst].decay) : decay0;
-    // fused: the order-5 moments move between the state planes and the
-    // closure planes at every odd sweep, and odd sweep j of a batched run
-    // reads them where j / 2 earlier odd sweeps left them (the network alone
-    // reads them in the state planes)
-    const bool flip = BATCH && FUSED && ((jsweep >> 1) & 1);
+    // the order-5 moments move between the state planes and the closure planes
+    // at every odd sweep, and odd sweep j of a batched run reads them where
+    // j / 2 earlier odd sweeps left them
+    const bool flip = BATCH && ((jsweep >> 1) & 1);
     const T* const in5 = BATCH ? static_cast<const T*>(flip ? insts[inst].b5 : insts[inst].a5) : in5_0;
     T* const out5 = BATCH ? static_cast<T*>(flip ? insts[inst].a5 : insts[inst].b5) : out5_0;
     const C tau = BATCH ? C((jsweep == 0 || jsweep == insts[inst].nsweeps - 1) ? insts[inst].tau_half
@@ -735,9 +938,8 @@ __global__ void __launch_bounds__(256, 3) closure_infer_kernel(T* __restrict__ U
 #pragma unroll
       for (int q = 0; q < 9; ++q) v0[q] = to_c(up[rowy[cy][q / 3] + colx[cx][q % 3]]);
     }
-    __syncthreads();  // the previous block's reads of Xa, nu_s, part and otab are done
+    __syncthreads();  // the previous block's reads of Xa, nu_s and part are done
     part[w * CB + lane] = ss;
-    if constexpr (!FUSED && BATCH) fill_otab(G);
     __syncthreads();
     const C nu = sqrt(((part[lane] + part[CB + lane]) + part[2 * CB + lane]) + part[3 * CB + lane]) + C(CLOSURE_EPS);
     const C rnu = C(1) / nu;
@@ -792,14 +994,11 @@ __global__ void __launch_bounds__(256, 3) closure_infer_kernel(T* __restrict__ U
           // rows: units 32 w + 16 mi + 4 (lane / 16) + r; column: point 16 nj + lane % 16
           const float4 bv = *reinterpret_cast<const float4*>((layer == 0 ? net->b1 : net->b2) + 32 * w + 16 * mi +
                                                              4 * (lane >> 4));
-          uint32_t h[4];
-          h[0] = bf16_hw(gelu(acc[mi][nj][0] + bv.x));
-          h[1] = bf16_hw(gelu(acc[mi][nj][1] + bv.y));
-          h[2] = bf16_hw(gelu(acc[mi][nj][2] + bv.z));
-          h[3] = bf16_hw(gelu(acc[mi][nj][3] + bv.w));
+          const uint32_t h01 = bf16_hw2(gelu(acc[mi][nj][0] + bv.x), gelu(acc[mi][nj][1] + bv.y));
+          const uint32_t h23 = bf16_hw2(gelu(acc[mi][nj][2] + bv.z), gelu(acc[mi][nj][3] + bv.w));
           const int m = 16 * nj + (lane & 15);
           const int n = 32 * w + 16 * mi + 4 * (lane >> 4);
-          *reinterpret_cast<uint2*>(&Xout[m * LDW + n]) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+          *reinterpret_cast<uint2*>(&Xout[m * LDW + n]) = make_uint2(h01, h23);
         }
       __syncthreads();
     }
@@ -813,23 +1012,7 @@ __global__ void __launch_bounds__(256, 3) closure_infer_kernel(T* __restrict__ U
       y = mfma16(af, xf, y);
     }
     const int m = 16 * w + (lane & 15);  // point of this lane
-    const int p2 = blk * CB + m;
-    if (!FUSED) {
-      if (p2 < total) {
-        const int pi = p2 % NXE, pj = p2 / NXE;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int o = 4 * (lane >> 4) + r;  // output of this lane
-          if (o >= CLOSURE_OUT || pi >= otab[8 + o] || pj >= otab[16 + o]) continue;
-          const int X = internal_index(pi, otab[24 + o], G.px, G.nx);
-          const int Y = internal_index(pj, otab[32 + o], G.py, G.ny);
-          const C g = nu_s[m] * C(y[r] + b3[r]) / C(G.dx);
-          U[int64_t(otab[o]) * G.plane_stride + int64_t(Y) * G.pitch + X] = from_c<T>(g);
-        }
-      }
-      continue;
-    }
-    // 4. (fused) the closure terms of the block into LDS, then the odd update:
+    // 4. the closure terms of the block into LDS, then the odd update:
     // wave w takes odd rows w, w + 4, w + 8, lane = point of the block
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -940,59 +1123,60 @@ hipError_t launch_closure_samples(int storage, const void* U, const void* decay,
 }
 
 size_t closure_infer_lds_bytes() {
-  return size_t(2 * CB + 16) * LDW * 2 + size_t(5 * CB) * 8 + 5 * 8 * sizeof(int) + size_t(CLOSURE_OUT * CB) * 8;
+  return size_t(2 * CB + 16) * LDW * 2 + size_t(5 * CB) * 8 + size_t(CLOSURE_OUT * CB) * 8;
 }
 
 namespace {
-template <typename T, bool FUSED, bool BATCH>
+// Opts a kernel in to its LDS (once).
+template <auto kernel>
+hipError_t opt_in_lds(size_t lds) {
+  static bool done = false;
+  if (done) return hipSuccess;
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+  done = e == hipSuccess;
+  return e;
+}
+
+template <typename T, bool BATCH>
 hipError_t launch_infer_t(void* U, const void* in5, void* out5, const void* decay, const ClosureGeo& G,
                           const ClosureNet* net, const ClosureOdd& odd, const ClosureInst* insts, const int* bfirst,
-                          int n_active, int j, int blocks, hipStream_t stream) {
+                          int n_active, int j, int nblk, hipStream_t stream) {
   using C = typename ComputeOf<T>::type;
-  static bool attr = false;
   const size_t lds = closure_infer_lds_bytes();
-  if (!attr) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&closure_infer_kernel<T, FUSED, BATCH>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
-  hipLaunchKernelGGL((closure_infer_kernel<T, FUSED, BATCH>), dim3(blocks), dim3(256), lds, stream,
-                     static_cast<T*>(U), static_cast<const T*>(in5), static_cast<T*>(out5),
-                     static_cast<const C*>(decay), G, net, odd, insts, bfirst, n_active, j);
+  const hipError_t e = opt_in_lds<&closure_infer_kernel<T, BATCH>>(lds);
+  if (e != hipSuccess) return e;
+  // a few workgroups per compute unit, each looping over blocks of points with
+  // the weights loaded once
+  const int grid = std::min(nblk, 3 * device_cus());
+  hipLaunchKernelGGL((closure_infer_kernel<T, BATCH>), dim3(grid), dim3(256), lds, stream, static_cast<T*>(U),
+                     static_cast<const T*>(in5), static_cast<T*>(out5), static_cast<const C*>(decay), G, net, odd,
+                     insts, bfirst, n_active, j);
   return hipGetLastError();
 }
 
-// a few workgroups per compute unit, each looping over blocks of points with
-// the weights loaded once
-int infer_blocks(const ClosureGeo& G) {
-  const int total = (G.nx + 1) * (G.ny + 1);
-  const int nblk = (total + CB - 1) / CB;
-  return std::min(nblk, 3 * device_cus());
+template <typename T, bool BATCH>
+hipError_t launch_net_t(void* U, const void* decay, const ClosureGeo& G, const ClosureNet* net,
+                        const ClosureInst* insts, const int* bfirst, int n_active, int nblk, hipStream_t stream) {
+  using C = typename ComputeOf<T>::type;
+  const hipError_t e = opt_in_lds<&closure_net_kernel<T, BATCH>>(kNetLds);
+  if (e != hipSuccess) return e;
+  const int grid = std::min(nblk, device_cus());  // one workgroup per compute unit
+  hipLaunchKernelGGL((closure_net_kernel<T, BATCH>), dim3(grid), dim3(64 * NW), kNetLds, stream, static_cast<T*>(U),
+                     static_cast<const C*>(decay), G, net, insts, bfirst, n_active);
+  return hipGetLastError();
 }
+
+int points_of(const ClosureGeo& G) { return (G.nx + 1) * (G.ny + 1); }
 }  // namespace
 
 hipError_t launch_closure_infer(int storage, void* U, const void* decay, const ClosureGeo& G, const ClosureNet* net,
                                 hipStream_t stream) {
-  const int blocks = infer_blocks(G);
-  ClosureOdd none{};
-  // the order-5 inputs sit in U (moments G.k[5 ..], consecutive)
+  const int nblk = (points_of(G) + NPT - 1) / NPT;
   switch (storage) {
-    case STORE_FP64: {
-      double* u = static_cast<double*>(U);
-      return launch_infer_t<double, false, false>(U, u + int64_t(G.k[5]) * G.plane_stride, nullptr, decay, G, net,
-                                                  none, nullptr, nullptr, 0, 0, blocks, stream);
-    }
-    case STORE_FP32: {
-      float* u = static_cast<float*>(U);
-      return launch_infer_t<float, false, false>(U, u + int64_t(G.k[5]) * G.plane_stride, nullptr, decay, G, net,
-                                                 none, nullptr, nullptr, 0, 0, blocks, stream);
-    }
-    case STORE_BF16: {
-      bf16* u = static_cast<bf16*>(U);
-      return launch_infer_t<bf16, false, false>(U, u + int64_t(G.k[5]) * G.plane_stride, nullptr, decay, G, net,
-                                                none, nullptr, nullptr, 0, 0, blocks, stream);
-    }
+    case STORE_FP64: return launch_net_t<double, false>(U, decay, G, net, nullptr, nullptr, 0, nblk, stream);
+    case STORE_FP32: return launch_net_t<float, false>(U, decay, G, net, nullptr, nullptr, 0, nblk, stream);
+    case STORE_BF16: return launch_net_t<bf16, false>(U, decay, G, net, nullptr, nullptr, 0, nblk, stream);
   }
   return hipErrorInvalidValue;
 }
@@ -1000,17 +1184,14 @@ hipError_t launch_closure_infer(int storage, void* U, const void* decay, const C
 hipError_t launch_closure_sweep(int storage, void* U, const void* in5, void* out5, const void* decay,
                                 const ClosureGeo& G, const ClosureNet* net, const ClosureOdd& odd,
                                 hipStream_t stream) {
-  const int blocks = infer_blocks(G);
+  const int nblk = (points_of(G) + CB - 1) / CB;
   switch (storage) {
     case STORE_FP64:
-      return launch_infer_t<double, true, false>(U, in5, out5, decay, G, net, odd, nullptr, nullptr, 0, 0, blocks,
-                                                 stream);
+      return launch_infer_t<double, false>(U, in5, out5, decay, G, net, odd, nullptr, nullptr, 0, 0, nblk, stream);
     case STORE_FP32:
-      return launch_infer_t<float, true, false>(U, in5, out5, decay, G, net, odd, nullptr, nullptr, 0, 0, blocks,
-                                                stream);
+      return launch_infer_t<float, false>(U, in5, out5, decay, G, net, odd, nullptr, nullptr, 0, 0, nblk, stream);
     case STORE_BF16:
-      return launch_infer_t<bf16, true, false>(U, in5, out5, decay, G, net, odd, nullptr, nullptr, 0, 0, blocks,
-                                               stream);
+      return launch_infer_t<bf16, false>(U, in5, out5, decay, G, net, odd, nullptr, nullptr, 0, 0, nblk, stream);
   }
   return hipErrorInvalidValue;
 }
@@ -1018,19 +1199,12 @@ hipError_t launch_closure_sweep(int storage, void* U, const void* in5, void* out
 hipError_t launch_closure_batch_net(int storage, const ClosureInst* insts, const int* bfirst, int n_active, int blocks,
                                     const ClosureNet* net, hipStream_t stream) {
   if (n_active < 1 || blocks < 1) return hipErrorInvalidValue;
-  const int grid = std::min(blocks, 3 * device_cus());
+  const int nblk = int(std::min<int64_t>(int64_t(blocks) * (CB / NPT), 1 << 30));
   const ClosureGeo G{};
-  const ClosureOdd odd{};
   switch (storage) {
-    case STORE_FP64:
-      return launch_infer_t<double, false, true>(nullptr, nullptr, nullptr, nullptr, G, net, odd, insts, bfirst,
-                                                 n_active, 0, grid, stream);
-    case STORE_FP32:
-      return launch_infer_t<float, false, true>(nullptr, nullptr, nullptr, nullptr, G, net, odd, insts, bfirst,
-                                                n_active, 0, grid, stream);
-    case STORE_BF16:
-      return launch_infer_t<bf16, false, true>(nullptr, nullptr, nullptr, nullptr, G, net, odd, insts, bfirst,
-                                               n_active, 0, grid, stream);
+    case STORE_FP64: return launch_net_t<double, true>(nullptr, nullptr, G, net, insts, bfirst, n_active, nblk, stream);
+    case STORE_FP32: return launch_net_t<float, true>(nullptr, nullptr, G, net, insts, bfirst, n_active, nblk, stream);
+    case STORE_BF16: return launch_net_t<bf16, true>(nullptr, nullptr, G, net, insts, bfirst, n_active, nblk, stream);
   }
   return hipErrorInvalidValue;
 }
@@ -1038,19 +1212,18 @@ hipError_t launch_closure_batch_net(int storage, const ClosureInst* insts, const
 hipError_t launch_closure_batch(int storage, const ClosureInst* insts, const int* bfirst, int n_active, int blocks,
                                 int j, const ClosureNet* net, hipStream_t stream) {
   if (n_active < 1 || blocks < 1) return hipErrorInvalidValue;
-  const int grid = std::min(blocks, 3 * device_cus());
   const ClosureGeo G{};
   const ClosureOdd odd{};
   switch (storage) {
     case STORE_FP64:
-      return launch_infer_t<double, true, true>(nullptr, nullptr, nullptr, nullptr, G, net, odd, insts, bfirst,
-                                                n_active, j, grid, stream);
+      return launch_infer_t<double, true>(nullptr, nullptr, nullptr, nullptr, G, net, odd, insts, bfirst, n_active, j,
+                                          blocks, stream);
     case STORE_FP32:
-      return launch_infer_t<float, true, true>(nullptr, nullptr, nullptr, nullptr, G, net, odd, insts, bfirst,
-                                               n_active, j, grid, stream);
+      return launch_infer_t<float, true>(nullptr, nullptr, nullptr, nullptr, G, net, odd, insts, bfirst, n_active, j,
+                                         blocks, stream);
     case STORE_BF16:
-      return launch_infer_t<bf16, true, true>(nullptr, nullptr, nullptr, nullptr, G, net, odd, insts, bfirst,
-                                              n_active, j, grid, stream);
+      return launch_infer_t<bf16, true>(nullptr, nullptr, nullptr, nullptr, G, net, odd, insts, bfirst, n_active, j,
+                                        blocks, stream);
   }
   return hipErrorInvalidValue;
 }

@@ -29,7 +29,7 @@ constexpr int OFF_W3 = OFF_B2 + CLOSURE_HIDDEN;
 constexpr int OFF_B3 = OFF_W3 + CLOSURE_OUT * CLOSURE_HIDDEN;
 static_assert(OFF_B3 + CLOSURE_OUT == CLOSURE_PARAMS, "parameter blob layout");
 
-// Network as the fused kernel reads it: bfloat16 weight rows of W1, W2 and W3
+// Network as the closure kernels read it: bfloat16 weight rows of W1, W2 and W3
 // (padded to 16 rows of zeros), then FP32 biases (b3 padded to 16).
 struct ClosureNet {
   uint16_t w[(2 * CLOSURE_HIDDEN + 16) * CLOSURE_IN];
@@ -145,7 +145,7 @@ hipError_t launch_closure_infer(int storage, void* U, const void* decay, const C
 hipError_t launch_closure_sweep(int storage, void* U, const void* in5, void* out5, const void* decay,
                                 const ClosureGeo& G, const ClosureNet* net, const ClosureOdd& odd,
                                 hipStream_t stream);
-// Odd sweep j of a batched run of closure solvers (FUSED kernel, BATCH mode):
+// Odd sweep j of a batched run of closure solvers (one kernel, as launch_closure_sweep):
 // the first n_active instances of insts, evaluation blocks numbered from
 // bfirst[i]; one network for all.
 hipError_t launch_closure_batch(int storage, const ClosureInst* insts, const int* bfirst, int n_active, int blocks,
