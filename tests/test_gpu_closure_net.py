@@ -40,3 +40,24 @@ def test_network_kernel_equals_the_fused_one(precision, n, bc):
         s.close()
     for k, (a, b) in enumerate(zip(*runs)):
         assert np.array_equal(a, b), (k, float(np.max(np.abs(a - b))))
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "bf16"])
+@pytest.mark.parametrize("count", [1, 3, 4, 5, 63])
+def test_samples_do_not_depend_on_their_number(precision, count):
+    """Four samples per workgroup: the first `count` rows of 64 samples, to the
+    bit, and nothing past them."""
+    torch = pytest.importorskip("torch")
+    s = pa.Solver.from_problem(_state_problem(7, (19, 23), (P, X), 61, precision=precision))
+    s.advance(4)
+    pts = np.random.default_rng(7).integers(0, 19, (64, 2)).astype(np.int32)
+    out = []
+    for n in (64, count):
+        feat = torch.full((64, 128), -7.0, device="cuda")
+        targ = torch.full((64, 6), -7.0, device="cuda")
+        s.closure_samples(pts[:n], feat, targ)
+        out.append((feat.cpu().numpy(), targ.cpu().numpy()))
+    for all_, some in zip(*out):
+        assert np.array_equal(some[:count], all_[:count]) and np.all(some[count:] == -7.0)
+        assert np.isfinite(all_).all() and np.any(all_ != 0)
+    s.close()
