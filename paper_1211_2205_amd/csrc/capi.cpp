@@ -650,22 +650,25 @@ int program_slots(const starmap_solver* s, int v) {
   return slots;
 }
 
+// Bytes of the state's points.
+double swept_bytes(const starmap_solver* s) {
+  return double(s->nmom) * double(s->nx + 1 - s->px) * double(s->ny + 1 - s->py) * double(s->ssize);
+}
+
 // Tile of a solver that was given none (and, unless it was given one, its
 // m-range width), from the sizes alone.
 int default_variant(starmap_solver* s) {
-  const double state = double(s->nmom) * double(s->plane_bytes_state());
-  int v = sweep_default_variant(s->storage, s->nx + 1 - s->px, s->ny + 1 - s->py, state);
-  if (!s->width_given) {
-    // (register windows of eight-byte values hold no more than four indices)
-    const bool narrow = s->storage == STORE_FP64 && sweep_in_registers(s->storage, v);
-    s->chunk_width = narrow ? 4 : sweep_default_width(s->N);
-  }
+  const int cols = s->nx + 1 - s->px, rows = s->ny + 1 - s->py;
+  int v = sweep_default_variant(s->storage, s->N, cols, rows, swept_bytes(s));
+  if (!s->width_given) s->chunk_width = sweep_default_width(s->storage, v, s->N, cols, rows);
   if (s->storage != STORE_FP64) return v;
-  // (a given width of eight: the tile of the same shape that holds ten planes)
-  if (!sweep_in_registers(s->storage, v) && s->chunk_width + 2 > sweep_variant(s->storage, v).cap) v = 2;
+  // (a given width that the tile's registers do not hold the planes of: the
+  // tile of its shape that holds ten)
+  if (s->width_given && !sweep_in_registers(s->storage, v) && s->chunk_width + 2 > sweep_variant(s->storage, v).cap)
+    v = v == 7 ? 5 : 2;
   if (!sweep_in_registers(s->storage, v) &&
       sweep_lds_bytes(v, program_slots(s, v), s->storage) > size_t(max_lds_bytes()))
-    v = sweep_default_variant(s->storage, 1, 1, 0.0);  // a tile without LDS
+    v = sweep_default_variant(s->storage, s->N, 1, 1, 0.0);  // a tile without LDS
   return v;
 }
 
@@ -870,6 +873,7 @@ int launch_one(starmap_solver* s, int parity, double tau) {
     w.parity = parity;
     w.strip = s->tile_strip;
     w.general = s->win_general;
+    w.streaming = sweep_streams(swept_bytes(s));
     w.top_shift = from_b ? closure_plane_b(s) - closure_plane_a(s) : 0;
     w.tau = tau;
     HIP_TRY(launch_window(s->storage, w, s->stream));
@@ -1904,6 +1908,7 @@ struct starmap_batch {
   // odd sweep
   bool closure_fused = false;
   void* ctab = nullptr;
+  double state_bytes = 0.0;  // of all instances with sweeps left at the start of the run
   std::vector<int> cfirst;
   // captured run
   hipGraph_t graph = nullptr;
@@ -2046,6 +2051,9 @@ int batch_table(starmap_batch* b, const std::vector<int>& sweeps, bool zero_tau)
   }
   if (b->merged && ng > 1 && !sweep_in_registers(b->storage, b->plans[0].variant))
     HIP_TRY(prepare_sweep(b->plans[0].variant, b->plans[0].slots));
+  b->state_bytes = 0.0;
+  for (int i = 0; i < count; ++i)
+    if (sweeps[i] > 0) b->state_bytes += swept_bytes(b->inst[i]);
   std::vector<BatchEntry> tab;
   std::vector<WindowEntry> wtab;
   std::vector<int> firsts;
@@ -2182,7 +2190,7 @@ int launch_plan(starmap_batch* b, const BatchPlan& g, int na, int j, hipStream_t
   if (sweep_in_registers(b->storage, g.variant)) {
     const TileShape ts = sweep_variant(b->storage, g.variant);
     const WindowEntry* tab = reinterpret_cast<const WindowEntry*>(base + batch_window_offset(count)) + g.tab0;
-    HIP_TRY(launch_window_batch(b->storage, tab, first, na, g.first[na], j, ts.tx, ts.ty, g.general, stream));
+    HIP_TRY(launch_window_batch(b->storage, tab, first, na, g.first[na], j, ts.tx, ts.ty, g.general, sweep_streams(b->state_bytes), stream));
   } else {
     const BatchEntry* tab = reinterpret_cast<const BatchEntry*>(base) + g.tab0;
     HIP_TRY(launch_sweep_batch(g.variant, tab, first, na, g.first[na], j, g.slots, stream));
@@ -2455,6 +2463,7 @@ int starmap_batch_run(starmap_batch* b, int32_t use_graph) {
       // the graph depends on every group's tile (kernel, LDS, programs) and
       // on the launch plans
       std::vector<int> key{b->merged ? 1 : 0, b->closure_fused ? 1 : 0};
+      key.push_back(sweep_streams(b->state_bytes) ? 1 : 0);
       for (const auto& g : b->plans) key.push_back(g.general ? 1 : 0);
       for (const auto& g : b->groups) key.insert(key.end(), {g.variant, g.width, g.slots});
       for (const auto& g : b->plans) {

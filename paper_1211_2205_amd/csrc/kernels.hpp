@@ -19,10 +19,12 @@ struct TileShape {
 int sweep_variant_count();
 TileShape sweep_variant(int storage, int v);
 inline bool sweep_in_registers(int storage, int v) { return sweep_variant(storage, v).cap == 0; }
-// Variant of a solver that was given none, by its points per axis and the bytes
-// of its state, and its m-range width.
-int sweep_default_variant(int storage, int cols, int rows, double state_bytes);
-int sweep_default_width(int N);
+// Variant of a solver that was given none, by its order, points per axis and
+// the bytes of its state, and its m-range width.
+int sweep_default_variant(int storage, int N, int cols, int rows, double state_bytes);
+int sweep_default_width(int storage, int variant, int N, int cols, int rows);
+// Whether states of these bytes are swept past the last-level cache.
+bool sweep_streams(double state_bytes);
 
 // Kernel arguments of one FP64 parity sweep with the window in LDS.
 struct SweepArgs {
@@ -83,6 +85,7 @@ struct WindowArgs {
   int N, nm;          // order; m ranges of 2 nm indices (nm = 2, 3 or 4)
   int parity, strip;
   int general;        // decay planes that differ between orders >= 1, or sources beyond the zeroth moment's
+  int streaming;      // the state does not fit the last-level cache
   int top_shift;      // planes from an order-N input to where it is read
   double tau;
 };
@@ -104,9 +107,9 @@ struct WindowEntry {
   int pitch, nx, ny, px, py, N, nm, nchunks, ntx, nty, strip, nsweeps, top_shift, pad;
 };
 // Sweep number j over the first n_active instances (arguments as
-// launch_sweep_batch); general: one of them needs it.
+// launch_sweep_batch); general: one of them needs it; streaming: as for all together.
 hipError_t launch_window_batch(int storage, const WindowEntry* table, const int* first, int n_active, int items, int j,
-                               int tx, int ty, bool general, hipStream_t stream);
+                               int tx, int ty, bool general, bool streaming, hipStream_t stream);
 
 // Opts the kernels of an LDS variant in to the LDS it needs (outside any stream
 // capture).  Returns a HIP error.

@@ -1,7 +1,7 @@
 // Parity sweep of the staggered-grid P_N scheme on gfx950 with the window of
 // input orders staged in LDS: the sweep of FP64 states larger than the
-// last-level cache (window.hip holds the sweep of the others and of FP32 and
-// BF16 storage).
+// last-level cache, and of few orders on large grids (window.hip holds the sweep
+// of the others and of FP32 and BF16 storage).
 //
 // One sweep applies the half-step operator S^p_tau of one parity p
 // (Seibold & Frank, Sect. 4.3, eqs. solution_operator_even/_odd): for every
@@ -622,32 +622,57 @@ TileShape sweep_variant(int storage, int v) {
 }
 
 // The rules behind a solver that was given no tile, from timing every variant
-// and width on 25 sizes (P_3 .. P_39, 48^2 .. 1400^2); each is within 5% of the
-// best of its size (10% for small BF16 states, where runs differ by as much).
-//   FP64: states in the last-level cache run with the window in registers on
-//   64 x 2 tiles (P_7 280^2 14.3 us per sweep, LDS 15.8; P_39 150^2, 149 MB,
-//   66 against 71); states beyond it, and grids large enough to fill the
-//   machine with LDS tiles, with the LDS window on 32 x 8 (P_15 447^2 77
-//   against 92 us; P_9 400^2 35 against 39; P_39 1000^2 2035 against 2285).
-//   FP32, BF16: large states on wide tiles, which read the fewest lines twice,
-//   where the grid fills them (P_39 1000^2 FP32: 128 x 2 1021 us, 64 x 4
-//   1092), else 64 wide (P_31 447^2, 448 columns: 64 x 8 116 us, 128 x 2 132).
-int sweep_default_variant(int storage, int cols, int rows, double state_bytes) {
+// and width on 88 sizes (P_1 .. P_39, 48^2 .. 1400^2).  Where two are given,
+// microseconds per sweep of the choice, then of the other.
+//
+// The last-level cache holds 256 MB: P_31 345^2 FP32 (253 MB) 77 us with the
+// output rows kept in it, 82 past it; 360^2 (275 MB) 95 and 90.
+constexpr double kCache = 2.56e8;
+bool sweep_streams(double state_bytes) { return state_bytes > kCache; }
+
+// FP64.  With the window in registers, 64 x 2 tiles (P_7 280^2 13.4, LDS 16;
+// P_9 400^2 32, LDS 35; P_39 180^2 65, LDS 92), but in LDS, 32 x 8
+//   - where few orders cannot hide the loads of a large grid (P_5 400^2 14.5,
+//     registers 16; P_7 500^2 27 and 29; P_9 550^2 is 57 and 52), with more
+//     points per tile where the window is smallest (P_1 700^2: 64 x 8 10,
+//     32 x 8 11.6; P_3 1000^2 34 and 36);
+//   - beyond the cache, where the y neighbours' lines leave the L1 before they
+//     are asked for (P_39 1000^2 2040, registers 2285; P_9 850^2 119 and 156),
+//     unless the LDS tiles are too few to fill the chip (P_39 200^2 118,
+//     registers 106; 300^2 are 216 both).
+// FP32, BF16.  Large states on wide tiles, which read the fewest lines twice,
+// where the grid fills them (P_39 1000^2 FP32: 128 x 2 1014, 64 x 4 1028), else
+// 64 wide (P_31 447^2, 448 columns: 64 x 8 116, 128 x 2 126).  States in the
+// cache: FP32 64 x 2 (P_7 512^2 15.6, 64 x 4 17.2), from P_8 on 64 x 4
+// (P_9 317 x 203 7.8 and 8.3, P_31 256^2 40 and 42); BF16 128 x 4 (P_31 345^2
+// 42, 64 x 4 51).
+int sweep_default_variant(int storage, int N, int cols, int rows, double state_bytes) {
+  const double points = double(cols) * rows;
+  const bool cached = !sweep_streams(state_bytes);
   if (storage == STORE_FP64) {
-    const bool lds = state_bytes > 2.0e8 || (double(cols) * rows > 1.25e5 && state_bytes > 3.2e7);
-    return lds ? 8 : 12;
+    const bool lds = cached ? N <= 7 && points > 1.2e5 : points > 6.0e4;
+    return !lds ? 12 : N <= 3 && points > 2.0e5 ? 7 : 8;
   }
   const int wide = storage == STORE_FP32 ? 128 : 256;
   const int padded = (cols + wide - 1) / wide * wide;
   const bool fills = padded - cols <= cols / 20;
-  if (storage == STORE_FP32) return state_bytes <= 2.56e8 ? 0 : fills ? 1 : 5;
-  return state_bytes > 2.56e8 && fills ? 6 : 4;
+  if (storage == STORE_FP32) return cached ? (N < 8 ? 8 : 0) : fills ? 1 : 5;
+  return !cached && fills ? 6 : 4;
 }
 
-// P_4, P_5: one range of six holds every index.  From P_13 on ranges of six
-// (LDS at P_39 1000^2: 4.32 ms per sweep pair against 4.43 at eight, 4.6 at four),
-// below it ranges of four: more workgroups.
-int sweep_default_width(int N) { return N == 4 || N == 5 || N >= 13 ? 6 : 4; }
+// m ranges.  One range where it holds every index (P_5, LDS 400^2: 14.5, at
+// four 19.7; P_7, LDS 1000^2: eight 89, four 121).  From P_16 on (with the LDS
+// window from P_13) ranges of six (LDS P_39 1000^2: 2040, eight 2200, four
+// 2110), below it four: more workgroups, and no idle rows in P_15 (FP32 447^2
+// 30, six 31); of grids that fill the chip anyway, six (P_9 1000^2 FP32 57,
+// four 61).  Register windows of eight-byte values hold no more than four.
+int sweep_default_width(int storage, int variant, int N, int cols, int rows) {
+  const bool registers = sweep_in_registers(storage, variant);
+  if (storage == STORE_FP64 && registers) return 4;
+  if (N == 4 || N == 5) return 6;
+  if (!registers) return N == 6 || N == 7 ? 8 : N >= 13 ? 6 : 4;
+  return N >= 16 || (N >= 8 && double(cols) * rows > 5.0e5) ? 6 : 4;
+}
 
 size_t sweep_lds_bytes(int v, int slots, int storage) {
   const TileShape t = sweep_variant(storage, v);

@@ -1,7 +1,7 @@
 // Parity sweep of the staggered-grid P_N scheme on gfx950 with the window of
-// input orders in registers: the sweep of FP32 and BF16 storage, and of FP64
-// states that stay in the last-level cache (sweep.hip holds the FP64 kernel
-// for larger ones, and says what a sweep computes).
+// input orders in registers: the sweep of FP32 and BF16 storage, and of most
+// FP64 states that stay in the last-level cache (sweep.hip holds the FP64 kernel
+// for the others, the rule, and what a sweep computes).
 //
 // Work decomposition: the outputs of a sweep are split into ranges of 2 NM
 // azimuthal indices m (an output (l, m) couples only to inputs
@@ -22,9 +22,9 @@
 // L1 cache serves as well (the neighbour loads hit lines that the wave or its
 // neighbours in the workgroup have just loaded).  Per sweep, LDS kernel with
 // its best tile -> this kernel with its default one: P_39 1000^2 BF16 838 ->
-// 529 us, FP32 1107 -> 1021 us; P_31 256^2 FP32 76 -> 48 us, BF16 71 -> 33 us;
-// P_9 317 x 203 FP32 15.5 -> 8.1 us; P_7 280^2 FP64 16.2 -> 14.3 us; P_3 100^2
-// FP64 7.4 -> 4.2 us.  P_39 1000^2 FP32 moves 4.9 GB per sweep at 4.8 TB/s; with
+// 518 us, FP32 1107 -> 1014 us; P_31 256^2 FP32 76 -> 40 us, BF16 71 -> 29 us;
+// P_9 317 x 203 FP32 15.5 -> 7.9 us; P_7 280^2 FP64 16.2 -> 13.5 us; P_3 100^2
+// FP64 7.4 -> 4.1 us.  P_39 1000^2 FP32 moves 4.9 GB per sweep at 4.8 TB/s; with
 // every neighbour load left out it takes 1020 us, so the memory's rate for this
 // mix of reads and writes bounds it.  FP64 states beyond the cache are slower
 // here (P_39 1000^2 2285 against 2035 us): eight-byte loads of three points per
@@ -51,8 +51,11 @@ namespace {
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-// Output rows are read once and written once per sweep: non-temporal (without
-// it P_39 1000^2 takes 5% longer).
+// Output rows are read once and written once per sweep.  With a state larger
+// than the last-level cache they are accessed non-temporally (S; without it
+// P_39 1000^2 FP32 takes 7% longer, P_31 447^2 14%), with a smaller one not, so
+// that the next sweep finds them there (P_31 256^2 FP32 47 -> 40 us, P_39 150^2
+// FP64 66 -> 52).
 constexpr int kStream = 2;
 // a byte offset past every plane (planes stay below 2^31 bytes)
 constexpr uint32_t kOutside = 0x80000000u;
@@ -77,14 +80,14 @@ __device__ __forceinline__ W buf_load(__amdgpu_buffer_rsrc_t r, uint32_t off) {
   else
     return __builtin_amdgcn_raw_buffer_load_b16(r, off, 0, AUX);
 }
-template <typename W>
+template <typename W, int AUX>
 __device__ __forceinline__ void buf_store(W v, __amdgpu_buffer_rsrc_t r, uint32_t off) {
   if constexpr (sizeof(W) == 8)
-    __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, kStream);
+    __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, AUX);
   else if constexpr (sizeof(W) == 4)
-    __builtin_amdgcn_raw_buffer_store_b32(v, r, off, 0, kStream);
+    __builtin_amdgcn_raw_buffer_store_b32(v, r, off, 0, AUX);
   else
-    __builtin_amdgcn_raw_buffer_store_b16(v, r, off, 0, kStream);
+    __builtin_amdgcn_raw_buffer_store_b16(v, r, off, 0, AUX);
 }
 
 // Value e of a thread's word.
@@ -133,8 +136,9 @@ struct WindowScalars {
 // against 1026 us, P_31 256^2 53 against 48 us.  One group over the whole of a
 // large grid loses the overlap of the ranges' shared planes: 1040 us.
 constexpr int kGroup = 512;
+constexpr int kXcds = 8;
 
-template <typename T, int NM, int P, bool G>
+template <typename T, int NM, int P, bool G, bool S>
 __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename ComputeOf<T>::type* __restrict__ decay,
                                             cptr<typename ComputeOf<T>::type> coef, cptr<int> tab,
                                             const WindowScalars<typename ComputeOf<T>::type>& a, int item) {
@@ -145,6 +149,7 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
   using W1 = Word<T, 1>;
   typedef C C8 __attribute__((ext_vector_type(8)));
   constexpr uint32_t TS = sizeof(T);
+  constexpr int AUX = S ? kStream : 0;
   constexpr int NB = NM + 1;  // input planes of one order that the range needs, R and I each
 
   // work item -> run of orders, m range, tile
@@ -154,7 +159,11 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
   const int grp = item / per, within = item - grp * per;
   const int gtiles = min(kGroup, a.ntx * a.nty - grp * kGroup);
   const int chunk = within / gtiles;
-  const int tile = grp * kGroup + within - chunk * gtiles;
+  // consecutive workgroups run on the chip's XCDs in turn: each takes a run of
+  // neighbouring tiles, whose shared rows its L2 then holds (P_9 317 x 203 FP32
+  // 8.2 -> 7.5 us, P_7 280^2 FP64 14.6 -> 14.0, P_39 1000^2 BF16 528 -> 517)
+  const int tl = within - chunk * gtiles, xcd = tl & (kXcds - 1);
+  const int tile = grp * kGroup + xcd * (gtiles / kXcds) + min(xcd, gtiles % kXcds) + tl / kXcds;
   int m0 = chunk * 2 * NM;
   const int ltop = a.N - ((a.N - P) & 1), lbot = m0 + P;
   if (lbot > ltop) return;  // no output rows in this m range
@@ -277,8 +286,8 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
     const int m = m0 + P + 2 * q;
     const int n = recs(m, lm);
     const int ni = P == 0 && q == 0 ? n & first : n;
-    uR[q] = buf_load<W, kStream>(plane(p, n), sR);
-    uI[q] = buf_load<W, kStream>(plane(p + uint32_t(pbytes), ni), sI);
+    uR[q] = buf_load<W, AUX>(plane(p, n), sR);
+    uI[q] = buf_load<W, AUX>(plane(p + uint32_t(pbytes), ni), sI);
     if constexpr (G) {
       const int r = n ? tab[2 * (a.N + 1) + k] : -1, i = ni ? tab[2 * (a.N + 1) + k + 1] : -1;
       qR[q] = buf_load<W>(plane(plane_addr(r), r >= 0 ? pbytes : 0), sR);
@@ -411,7 +420,7 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
             // (a lane's second point past the grid keeps the padding's value)
             nv_[e] = e == 0 || X + e < (z ? vxI : vxR) ? r : u;
           }
-          buf_store<W>(word<T, V>(nv_), plane(ps, P == 0 && z && b == 0 ? n & first : n), z ? sI : sR);
+          buf_store<W, AUX>(word<T, V>(nv_), plane(ps, P == 0 && z && b == 0 ? n & first : n), z ? sI : sR);
           ps += uint32_t(pbytes);
         }
         load_row(b, pn, ln, kn + j);
@@ -440,7 +449,7 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
       const C r = sub_step(u, w, c0[e], expm1div(-c0[e] * a.tau), a.tau);
       nv_[e] = e == 0 || X + e < vxR ? r : u;
     }
-    buf_store<W>(word<T, V>(nv_), plane(plane_addr(0), pbytes), sR);
+    buf_store<W, AUX>(word<T, V>(nv_), plane(plane_addr(0), pbytes), sR);
   }
 }
 
@@ -448,13 +457,13 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
 template <typename T>
 constexpr int kMaxThreads = sizeof(T) == 8 ? 256 : 512;
 
-template <typename T, int NM, int P, bool G>
+template <typename T, int NM, int P, bool G, bool S>
 __global__ void __launch_bounds__(kMaxThreads<T>)
 window_kernel(T* __restrict__ U, const typename ComputeOf<T>::type* __restrict__ decay,
               const typename ComputeOf<T>::type* __restrict__ coef, const int* __restrict__ tab,
               const WindowScalars<typename ComputeOf<T>::type> a) {
   using C = typename ComputeOf<T>::type;
-  window_tile<T, NM, P, G>(U, decay, (cptr<C>)coef, (cptr<int>)tab, a, int(blockIdx.x));
+  window_tile<T, NM, P, G, S>(U, decay, (cptr<C>)coef, (cptr<int>)tab, a, int(blockIdx.x));
 }
 
 // WindowEntry as the device reads it (pointers with their address space, as
@@ -474,7 +483,7 @@ static_assert(sizeof(WindowEntryG) == sizeof(WindowEntry), "device view of Windo
 
 // Sweep number j of a batched run (instances and workgroup prefix as for the
 // LDS kernel); each instance brings its own width of m ranges.
-template <typename T, int P, bool G>
+template <typename T, int P, bool G, bool S>
 __global__ void __launch_bounds__(kMaxThreads<T>)
 window_batch_kernel(const WindowEntry* __restrict__ table, const int* __restrict__ first, const int n_active,
                     const int j, const int bw) {
@@ -512,11 +521,21 @@ window_batch_kernel(const WindowEntry* __restrict__ table, const int* __restrict
   const cptr<int> tab = (cptr<int>)e.tab;
   const int nm = e.nm, it = item - first[lo];
   if (nm == 2)
-    window_tile<T, 2, P, G>(u, dec, cf, tab, a, it);
+    window_tile<T, 2, P, G, S>(u, dec, cf, tab, a, it);
   else if (nm == 3)
-    window_tile<T, 3, P, G>(u, dec, cf, tab, a, it);
+    window_tile<T, 3, P, G, S>(u, dec, cf, tab, a, it);
   else
-    window_tile<T, 4, P, G>(u, dec, cf, tab, a, it);
+    window_tile<T, 4, P, G, S>(u, dec, cf, tab, a, it);
+}
+
+// f with the parity and the two flags as types.
+template <typename F>
+hipError_t by_flags(bool parity, bool general, bool streaming, F f) {
+  using No = std::integral_constant<int, 0>;
+  using Yes = std::integral_constant<int, 1>;
+  auto with = [&](auto p, auto g) { return streaming ? f(p, g, Yes{}) : f(p, g, No{}); };
+  if (parity) return general ? with(Yes{}, Yes{}) : with(Yes{}, No{});
+  return general ? with(No{}, Yes{}) : with(No{}, No{});
 }
 
 template <typename T, int NM>
@@ -552,15 +571,13 @@ hipError_t launch_t(const WindowArgs& w, hipStream_t stream) {
   if (blocks < 1 || blocks >= (int64_t(1) << 31)) return hipErrorInvalidValue;
   T* u = static_cast<T*>(w.u);
   const C *d = static_cast<const C*>(w.decay), *cf = static_cast<const C*>(w.coef);
-#define STARMAP_WINDOW(P, G) \
-  hipLaunchKernelGGL((window_kernel<T, NM, P, G>), dim3(unsigned(blocks)), dim3(a.threads), 0, stream, u, d, cf, w.tab, a)
-  if (w.parity) {
-    if (w.general) STARMAP_WINDOW(1, true); else STARMAP_WINDOW(1, false);
-  } else {
-    if (w.general) STARMAP_WINDOW(0, true); else STARMAP_WINDOW(0, false);
-  }
-#undef STARMAP_WINDOW
-  return hipGetLastError();
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(unsigned(blocks)), dim3(a.threads), 0, stream, u, d, cf, w.tab, a);
+    return hipGetLastError();
+  };
+  return by_flags(w.parity, w.general, w.streaming, [&](auto p, auto g, auto s) {
+    return launch(&window_kernel<T, NM, decltype(p)::value, decltype(g)::value, decltype(s)::value>);
+  });
 }
 
 template <typename T>
@@ -575,18 +592,16 @@ hipError_t launch_nm(const WindowArgs& w, hipStream_t stream) {
 
 template <typename T>
 hipError_t launch_batch_t(const WindowEntry* table, const int* first, int n_active, int items, int j, int tx, int ty,
-                          bool general, hipStream_t stream) {
+                          bool general, bool streaming, hipStream_t stream) {
   const int bw = tx / kPoints<T>, threads = bw * ty;
   if (bw < 1 || threads < 64 || threads > kMaxThreads<T>) return hipErrorInvalidValue;
-#define STARMAP_WINDOW(P, G) \
-  hipLaunchKernelGGL((window_batch_kernel<T, P, G>), dim3(items), dim3(threads), 0, stream, table, first, n_active, j, bw)
-  if (j & 1) {
-    if (general) STARMAP_WINDOW(0, true); else STARMAP_WINDOW(0, false);
-  } else {
-    if (general) STARMAP_WINDOW(1, true); else STARMAP_WINDOW(1, false);
-  }
-#undef STARMAP_WINDOW
-  return hipGetLastError();
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(items), dim3(threads), 0, stream, table, first, n_active, j, bw);
+    return hipGetLastError();
+  };
+  return by_flags(!(j & 1), general, streaming, [&](auto p, auto g, auto s) {
+    return launch(&window_batch_kernel<T, decltype(p)::value, decltype(g)::value, decltype(s)::value>);
+  });
 }
 
 }  // namespace
@@ -618,12 +633,12 @@ hipError_t launch_window(int storage, const WindowArgs& w, hipStream_t stream) {
 }
 
 hipError_t launch_window_batch(int storage, const WindowEntry* table, const int* first, int n_active, int items, int j,
-                               int tx, int ty, bool general, hipStream_t stream) {
+                               int tx, int ty, bool general, bool streaming, hipStream_t stream) {
   if (n_active < 1 || items < 1) return hipErrorInvalidValue;
   switch (storage) {
-    case STORE_FP64: return launch_batch_t<double>(table, first, n_active, items, j, tx, ty, general, stream);
-    case STORE_FP32: return launch_batch_t<float>(table, first, n_active, items, j, tx, ty, general, stream);
-    case STORE_BF16: return launch_batch_t<bf16>(table, first, n_active, items, j, tx, ty, general, stream);
+    case STORE_FP64: return launch_batch_t<double>(table, first, n_active, items, j, tx, ty, general, streaming, stream);
+    case STORE_FP32: return launch_batch_t<float>(table, first, n_active, items, j, tx, ty, general, streaming, stream);
+    case STORE_BF16: return launch_batch_t<bf16>(table, first, n_active, items, j, tx, ty, general, streaming, stream);
   }
   return hipErrorInvalidValue;
 }
