@@ -521,6 +521,11 @@ int upload_window(starmap_solver* s) {
   HIP_TRY(hipStreamSynchronize(s->stream));
   // decay planes that differ between the orders, or sources beyond the zeroth moment's
   s->win_general = s->anisotropic || s->nsrc > (s->qk[0] >= 0 ? 1 : 0);
+  for (int p = 0; p < 2; ++p) {  // (an even sweep of P_1 has no orders >= 1: any planes)
+    const int l = std::min(p ? 1 : 2, s->N);
+    s->win_planes[p] = {std::max(tab[size_t(2 * l)], 0), std::max(tab[size_t(2 * l) + 1], 0), tab[0],
+                        tab[size_t(2 * (s->N + 1))]};
+  }
   return STARMAP_OK;
 }
 
@@ -873,6 +878,7 @@ int launch_one(starmap_solver* s, int parity, double tau) {
     w.parity = parity;
     w.strip = s->tile_strip;
     w.general = s->win_general;
+    w.planes = s->win_planes[parity];
     w.streaming = sweep_streams(swept_bytes(s));
     w.top_shift = from_b ? closure_plane_b(s) - closure_plane_a(s) : 0;
     w.tau = tau;
@@ -1878,6 +1884,7 @@ struct BatchPlan {
   size_t tab0 = 0;           // first table entry of the plan
   size_t first0 = 0;         // first prefix value of the plan in the table's int array
   bool general = false;      // register-window sweeps: an instance needs the general kernel
+  int nm = 2;                // register-window sweeps: the widest m range's
 };
 }  // namespace detail
 }  // namespace starmap
@@ -2068,6 +2075,7 @@ int batch_table(starmap_batch* b, const std::vector<int>& sweeps, bool zero_tau)
     g.nsweeps.assign(ord.size(), 0);
     g.first.assign(ord.size() + 1, 0);
     g.general = false;
+    g.nm = 2;
     int64_t total = 0;
     for (size_t r = 0; r < ord.size(); ++r) {
       starmap_solver* s = b->inst[ord[r]];
@@ -2092,11 +2100,11 @@ int batch_table(starmap_batch* b, const std::vector<int>& sweeps, bool zero_tau)
         w.py = s->py;
         w.N = s->N;
         w.nm = window_nm(s->N, s->chunk_width);
+        g.nm = std::max(g.nm, w.nm);
         const WindowGrid wg = window_grid(s->nx, s->ny, s->px, s->py, ts.tx, ts.ty, s->N, w.nm);
-        w.nchunks = wg.nchunks;
-        w.ntx = wg.ntx;
-        w.nty = wg.nty;
-        w.strip = s->tile_strip;
+        w.order = window_order(wg, s->tile_strip);
+        w.planes[0] = s->win_planes[0];
+        w.planes[1] = s->win_planes[1];
         w.nsweeps = sweeps[ord[r]];
         w.top_shift = (s->closure && b->closure_fused) ? closure_plane_b(s) - closure_plane_a(s) : 0;
         g.general = g.general || s->win_general;
@@ -2190,7 +2198,7 @@ int launch_plan(starmap_batch* b, const BatchPlan& g, int na, int j, hipStream_t
   if (sweep_in_registers(b->storage, g.variant)) {
     const TileShape ts = sweep_variant(b->storage, g.variant);
     const WindowEntry* tab = reinterpret_cast<const WindowEntry*>(base + batch_window_offset(count)) + g.tab0;
-    HIP_TRY(launch_window_batch(b->storage, tab, first, na, g.first[na], j, ts.tx, ts.ty, g.general, sweep_streams(b->state_bytes), stream));
+    HIP_TRY(launch_window_batch(b->storage, tab, first, na, g.first[na], j, ts.tx, ts.ty, g.nm, g.general, sweep_streams(b->state_bytes), stream));
   } else {
     const BatchEntry* tab = reinterpret_cast<const BatchEntry*>(base) + g.tab0;
     HIP_TRY(launch_sweep_batch(g.variant, tab, first, na, g.first[na], j, g.slots, stream));
@@ -2464,7 +2472,7 @@ int starmap_batch_run(starmap_batch* b, int32_t use_graph) {
       // on the launch plans
       std::vector<int> key{b->merged ? 1 : 0, b->closure_fused ? 1 : 0};
       key.push_back(sweep_streams(b->state_bytes) ? 1 : 0);
-      for (const auto& g : b->plans) key.push_back(g.general ? 1 : 0);
+      for (const auto& g : b->plans) key.insert(key.end(), {g.general ? 1 : 0, g.nm});
       for (const auto& g : b->groups) key.insert(key.end(), {g.variant, g.width, g.slots});
       for (const auto& g : b->plans) {
         key.insert(key.end(), {g.variant, g.slots, int(g.nsweeps.size())});

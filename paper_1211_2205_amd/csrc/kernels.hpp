@@ -73,6 +73,11 @@ struct BatchEntry {
   int64_t even_b_delta;
 };
 
+// Planes of a sweep whose orders >= 1 share their decay planes: those of the
+// R and I rows, the zeroth moment's, and its source plane or -1.
+struct WindowPlanes {
+  int r = 0, i = 0, zeroth = 0, source = -1;
+};
 // One parity sweep with the window of input orders in registers (window.hip).
 struct WindowArgs {
   void* u;            // state planes, then source planes, storage type
@@ -86,6 +91,7 @@ struct WindowArgs {
   int parity, strip;
   int general;        // decay planes that differ between orders >= 1, or sources beyond the zeroth moment's
   int streaming;      // the state does not fit the last-level cache
+  WindowPlanes planes;  // unless general
   int top_shift;      // planes from an order-N input to where it is read
   double tau;
 };
@@ -95,6 +101,18 @@ struct WindowGrid {
   int ntx, nty, nchunks;
 };
 WindowGrid window_grid(int nx, int ny, int px, int py, int tx, int ty, int N, int nm);
+// Division of 0 <= n < 2^31 by a constant: n / d = n m >> s.
+struct Divisor {
+  uint32_t m = 0, s = 0;
+};
+// How a workgroup's number becomes an m range and a tile: numbers per group of
+// tiles, tiles of the last group, and the divisors of the tile order.
+struct WindowOrder {
+  Divisor per, tail;          // numbers per group; tiles of the last group
+  Divisor band, rows, last;   // tiles per strip; a strip's width, the last strip's
+  int ntx, nty, nchunks, strip;
+};
+WindowOrder window_order(const WindowGrid& g, int strip);
 hipError_t launch_window(int storage, const WindowArgs& w, hipStream_t stream);
 // One instance of a batched run of register-window sweeps.
 struct WindowEntry {
@@ -104,12 +122,14 @@ struct WindowEntry {
   const int* tab;
   int64_t plane_stride;
   double tau_full, tau_half;
-  int pitch, nx, ny, px, py, N, nm, nchunks, ntx, nty, strip, nsweeps, top_shift, pad;
+  WindowOrder order;
+  WindowPlanes planes[2];  // by parity
+  int pitch, nx, ny, px, py, N, nm, nsweeps, top_shift, pad;
 };
 // Sweep number j over the first n_active instances (arguments as
-// launch_sweep_batch); general: one of them needs it; streaming: as for all together.
+// launch_sweep_batch); nm: the largest of them; general: one of them needs it; streaming: as for all together.
 hipError_t launch_window_batch(int storage, const WindowEntry* table, const int* first, int n_active, int items, int j,
-                               int tx, int ty, bool general, bool streaming, hipStream_t stream);
+                               int tx, int ty, int nm, bool general, bool streaming, hipStream_t stream);
 
 // Opts the kernels of an LDS variant in to the LDS it needs (outside any stream
 // capture).  Returns a HIP error.

@@ -39,6 +39,7 @@
 // under a branch makes the compiler wait for all earlier ones).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <type_traits>
 
@@ -123,11 +124,37 @@ template <typename C>
 struct WindowScalars {
   uint32_t ps;  // plane stride in elements
   int pitch, nx, ny, px, py;
-  int bw, threads, ntx, nty, strip;  // lanes per tile row, threads per tile, tiles, tile order
-  int nchunks, nseg;                 // m ranges, runs of output orders
+  int lbw, threads;  // lanes per tile row (logarithm), threads per tile
+  int nseg;          // runs of output orders
+  Divisor by_nseg;
+  WindowOrder o;     // m ranges and tiles
+  WindowPlanes planes;
   int N, top_shift;                  // order; planes from an order-N input to where it is read
   C tau;
 };
+
+// Quotients by constants of a launch as multiplications: the six divisions
+// between a workgroup's number and its first load, each some 28 dependent
+// instructions, had been a tenth of a small sweep (P_3 100^2 FP64 4.14 -> 3.78
+// us, P_9 317 x 203 FP32 8.1 -> 7.5; with the plane numbers as arguments, not
+// read from a table first, 3.63 and 7.2).
+__device__ __forceinline__ int divide(int n, const Divisor& d) { return int((uint64_t(uint32_t(n)) * d.m) >> d.s); }
+
+// Tile number t of the order (tile_xy of device.hpp with its divisors).
+__device__ __forceinline__ int2 tile_at(int t, const WindowOrder& o) {
+  const int band = divide(t, o.band);
+  if (o.strip >= 2) {
+    const int row0 = band * o.strip, rows = min(o.strip, o.nty - row0);
+    const int r = t - band * (o.strip * o.ntx), q = divide(r, rows == o.strip ? o.rows : o.last);
+    return make_int2(q, row0 + (r - q * rows));
+  }
+  if (o.strip <= -2) {
+    const int w = -o.strip, col0 = band * w, cols = min(w, o.ntx - col0);
+    const int r = t - band * (w * o.nty), q = divide(r, cols == w ? o.rows : o.last);
+    return make_int2(col0 + (r - q * cols), q);
+  }
+  return make_int2(t - band * o.ntx, band);
+}
 
 // Tiles of one group: the work items of a group are numbered range by range,
 // and the ranges of low m, which have the most orders, come first.  Ranges as
@@ -153,32 +180,40 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
   constexpr int NB = NM + 1;  // input planes of one order that the range needs, R and I each
 
   // work item -> run of orders, m range, tile
-  const int seg = item % a.nseg;
-  item /= a.nseg;
-  const int per = kGroup * a.nchunks;
-  const int grp = item / per, within = item - grp * per;
-  const int gtiles = min(kGroup, a.ntx * a.nty - grp * kGroup);
-  const int chunk = within / gtiles;
+  int seg = 0;
+  if (a.nseg > 1) {
+    const int q = divide(item, a.by_nseg);
+    seg = item - q * a.nseg;
+    item = q;
+  }
+  const int per = kGroup * a.o.nchunks, grp = divide(item, a.o.per), within = item - grp * per;
+  const int ntiles = a.o.ntx * a.o.nty, gtiles = min(kGroup, ntiles - grp * kGroup);
+  const int chunk = gtiles == kGroup ? within / kGroup : divide(within, a.o.tail);
   // consecutive workgroups run on the chip's XCDs in turn: each takes a run of
   // neighbouring tiles, whose shared rows its L2 then holds (P_9 317 x 203 FP32
   // 8.2 -> 7.5 us, P_7 280^2 FP64 14.6 -> 14.0, P_39 1000^2 BF16 528 -> 517)
-  const int tl = within - chunk * gtiles, xcd = tl & (kXcds - 1);
+  const int tl = within - chunk * gtiles, xcd = tl % kXcds;
   const int tile = grp * kGroup + xcd * (gtiles / kXcds) + min(xcd, gtiles % kXcds) + tl / kXcds;
   int m0 = chunk * 2 * NM;
   const int ltop = a.N - ((a.N - P) & 1), lbot = m0 + P;
   if (lbot > ltop) return;  // no output rows in this m range
   const int nord = (ltop - lbot) / 2 + 1;
-  const int o0 = nord * seg / a.nseg, o1 = nord * (seg + 1) / a.nseg;
+  int o0 = 0, o1 = nord;
+  if (a.nseg > 1) {
+    o0 = divide(nord * seg, a.by_nseg);
+    o1 = divide(nord * (seg + 1), a.by_nseg);
+  }
   if (o0 >= o1) return;
   const int lfirst = ltop - 2 * o0, llast = ltop - 2 * (o1 - 1);
 
   // this thread's points (X .. X + V - 1, Y); lanes past the tile or the grid
   // stand at the origin and store nothing
-  const int2 txy = tile_xy(tile, a.ntx, a.nty, a.strip);
+  const int2 txy = tile_at(tile, a.o);
+  const int bw = 1 << a.lbw;
   const int f = txy.y * a.threads + int(threadIdx.x);
-  int Y = f / a.bw;
-  const int col = f - Y * a.bw;
-  int X = (txy.x * a.bw + col) * V;
+  int Y = f >> a.lbw;
+  const int col = f & (bw - 1);
+  int X = (txy.x * bw + col) * V;
   const int rows = a.ny + 1 - a.py, cols = a.nx + 1 - a.px;
   const bool in = Y < rows && X < cols;
   if (!in) X = Y = 0;
@@ -208,7 +243,7 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
   // against 56 us).
   const int lane = int(threadIdx.x) & 63;
   const bool endL = V == 1 || lane == 0 || col == 0 || !in || X == 0;
-  const bool endH = V == 1 || lane == 63 || col == a.bw - 1 || !in || X + V >= cols;
+  const bool endH = V == 1 || lane == 63 || col == bw - 1 || !in || X + V >= cols;
   const uint32_t rowR = uint32_t(ycR * a.pitch), rowI = uint32_t(Y * a.pitch);
   const uint32_t cR = (rowR + xcR) * TS, bR = uint32_t(ynR * a.pitch + xcR) * TS;
   const uint32_t cI = (rowI + xcI) * TS, bI = uint32_t(ynI * a.pitch + xcI) * TS;
@@ -296,12 +331,12 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
   };
 
   // decay coefficients c and E(-c tau) of the two output grids.  Without G one
-  // plane per grid serves every order but the zeroth (tab[2 l], tab[2 l + 1]:
-  // planes of the order's R and I rows), so E is formed once, before the loop.
+  // plane per grid serves every order but the zeroth, so E is formed once,
+  // before the loop; with G order l's planes are tab[2 l] and tab[2 l + 1].
   C cR_[V], eR_[V], cI_[V], eI_[V], ldR[V], ldI[V];
   auto load_decay = [&](int l) {
-    const C* d0 = plane_at(decay, max(tab[2 * l], 0), a.ps);
-    const C* d1 = plane_at(decay, max(tab[2 * l + 1], 0), a.ps);
+    const C* d0 = plane_at(decay, G ? max(tab[2 * l], 0) : a.planes.r, a.ps);
+    const C* d1 = plane_at(decay, G ? max(tab[2 * l + 1], 0) : a.planes.i, a.ps);
 #pragma unroll
     for (int e = 0; e < V; ++e) {
       ldR[e] = d0[go + e];
@@ -326,6 +361,7 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
     const int r0 = l * (l + 1) / 2 + l - (m0 + P);
     const int kh = r0 + l + 3, kl = r0 - l;  // planes b = 0 of orders l + 1 and l - 1
     const int shift = l + 1 == a.N ? a.top_shift : 0;
+    load_decay(l);
 #pragma unroll
     for (int b = NM; b >= 0; --b) load_planes(b, plane_addr(kh + shift - 2 * b), l < a.N ? l + 1 : -1);
     In pR[NB], pI[NB];
@@ -338,7 +374,7 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
     for (int b = NM; b >= 0; --b) load_planes(b, plane_addr(kl - 2 * b), l - 1);
 #pragma unroll
     for (int q = NM - 1; q >= 0; --q) load_row(q, plane_addr(r0 - 2 * q), l, r0 - 2 * q);
-    load_decay(G || l > 0 ? l : min(1, a.N));
+    apply_decay();  // (while the planes arrive)
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
       diff(pR[b], hR[b], P == 1, true);
@@ -351,13 +387,12 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
   C c0[V] = {};
   W q0{};
   if (zeroth) {
-    const C* d = plane_at(decay, tab[0], a.ps);
+    const C* d = plane_at(decay, a.planes.zeroth, a.ps);
 #pragma unroll
     for (int e = 0; e < V; ++e) c0[e] = d[go + e];
-    const int src = tab[2 * (a.N + 1)];
+    const int src = a.planes.source;
     q0 = buf_load<W>(plane(plane_addr(src), src >= 0 ? pbytes : 0), sR);
   }
-  apply_decay();
 
   const int lend = zeroth ? 2 : llast;
   for (; l >= lend; l -= 2) {
@@ -477,16 +512,21 @@ struct WindowEntryG {
   gptr<const int> tab;
   int64_t plane_stride;
   double tau_full, tau_half;
-  int pitch, nx, ny, px, py, N, nm, nchunks, ntx, nty, strip, nsweeps, top_shift, pad;
+  WindowOrder order;
+  WindowPlanes planes[2];
+  int pitch, nx, ny, px, py, N, nm, nsweeps, top_shift, pad;
 };
 static_assert(sizeof(WindowEntryG) == sizeof(WindowEntry), "device view of WindowEntry");
 
 // Sweep number j of a batched run (instances and workgroup prefix as for the
-// LDS kernel); each instance brings its own width of m ranges.
-template <typename T, int P, bool G, bool S>
+// LDS kernel); each instance brings its own width of m ranges, up to NMAX (a
+// batch of narrow ones needs fewer registers: 24 media of P_3 .. P_9 on 64^2 ..
+// 256^2 cells, FP32, 88 -> 75: with the shorter way to the first load 28 -> 26
+// us per sweep).
+template <typename T, int NMAX, int P, bool G, bool S>
 __global__ void __launch_bounds__(kMaxThreads<T>)
 window_batch_kernel(const WindowEntry* __restrict__ table, const int* __restrict__ first, const int n_active,
-                    const int j, const int bw) {
+                    const int j, const int lbw) {
   using C = typename ComputeOf<T>::type;
   const int item = int(blockIdx.x);
   int lo = 0, hi = n_active - 1;  // last instance with first[i] <= item
@@ -503,12 +543,10 @@ window_batch_kernel(const WindowEntry* __restrict__ table, const int* __restrict
   a.ny = e.ny;
   a.px = e.px;
   a.py = e.py;
-  a.bw = bw;
+  a.lbw = lbw;
   a.threads = int(blockDim.x);
-  a.ntx = e.ntx;
-  a.nty = e.nty;
-  a.strip = e.strip;
-  a.nchunks = e.nchunks;
+  a.o = e.order;
+  a.planes = e.planes[P];
   a.nseg = 1;
   a.N = e.N;
   // closure solvers: before even sweep j, (j + 1) / 2 odd sweeps have moved
@@ -520,12 +558,30 @@ window_batch_kernel(const WindowEntry* __restrict__ table, const int* __restrict
   const cptr<C> cf = (cptr<C>)(gptr<const C>)e.coef;
   const cptr<int> tab = (cptr<int>)e.tab;
   const int nm = e.nm, it = item - first[lo];
-  if (nm == 2)
+  if (NMAX == 2 || nm == 2)
     window_tile<T, 2, P, G, S>(u, dec, cf, tab, a, it);
-  else if (nm == 3)
-    window_tile<T, 3, P, G, S>(u, dec, cf, tab, a, it);
+  else if (NMAX == 3 || nm == 3)
+    window_tile<T, NMAX < 3 ? 2 : 3, P, G, S>(u, dec, cf, tab, a, it);
   else
-    window_tile<T, 4, P, G, S>(u, dec, cf, tab, a, it);
+    window_tile<T, NMAX < 4 ? 2 : 4, P, G, S>(u, dec, cf, tab, a, it);
+}
+
+// 2^s / d rounded up, with s so large (2^31 d at least) that the error, below
+// one part in 2^31, changes no quotient of a number below 2^31.
+Divisor divisor(int d) {
+  Divisor r;
+  d = d < 1 ? 1 : d;
+  r.s = 31;
+  while ((int64_t(1) << (r.s - 31)) < d) ++r.s;
+  r.m = uint32_t((uint64_t(1) << r.s) / uint32_t(d) + 1);
+  return r;
+}
+
+// The logarithm of a power of two, -1 of another number.
+int log2_of(int n) {
+  int l = 0;
+  while ((1 << l) < n) ++l;
+  return n >= 1 && (1 << l) == n ? l : -1;
 }
 
 // f with the parity and the two flags as types.
@@ -548,13 +604,11 @@ hipError_t launch_t(const WindowArgs& w, hipStream_t stream) {
   a.ny = w.ny;
   a.px = w.px;
   a.py = w.py;
-  a.bw = w.tx / kPoints<T>;
-  a.threads = a.bw * w.ty;
+  const int bw = w.tx / kPoints<T>;
+  a.lbw = log2_of(bw);
+  a.threads = bw * w.ty;
   const WindowGrid g = window_grid(w.nx, w.ny, w.px, w.py, w.tx, w.ty, w.N, w.nm);
-  a.ntx = g.ntx;
-  a.nty = g.nty;
-  a.strip = w.strip;
-  a.nchunks = g.nchunks;
+  a.o = window_order(g, w.strip);
   // A launch of fewer workgroups than compute units is a chain of memory
   // round trips, one per order: its orders are split into runs that start
   // their own chains (one more window to load each).  P_3 100^2 FP64 5.7 ->
@@ -563,10 +617,12 @@ hipError_t launch_t(const WindowArgs& w, hipStream_t stream) {
   const int blocks1 = g.ntx * g.nty * g.nchunks, orders = w.N / 2 + 1;
   a.nseg = blocks1 > 0 ? 256 / blocks1 : 1;
   a.nseg = a.nseg < 1 ? 1 : a.nseg > orders ? orders : a.nseg;
+  a.by_nseg = divisor(a.nseg);
+  a.planes = w.planes;
   a.N = w.N;
   a.top_shift = w.top_shift;
   a.tau = C(w.tau);
-  if (a.bw < 1 || a.threads < 64 || a.threads > kMaxThreads<T>) return hipErrorInvalidValue;
+  if (a.lbw < 0 || a.threads < 64 || a.threads > kMaxThreads<T>) return hipErrorInvalidValue;
   const int64_t blocks = int64_t(blocks1) * a.nseg;
   if (blocks < 1 || blocks >= (int64_t(1) << 31)) return hipErrorInvalidValue;
   T* u = static_cast<T*>(w.u);
@@ -590,18 +646,28 @@ hipError_t launch_nm(const WindowArgs& w, hipStream_t stream) {
   return hipErrorInvalidValue;
 }
 
-template <typename T>
+template <typename T, int NMAX>
 hipError_t launch_batch_t(const WindowEntry* table, const int* first, int n_active, int items, int j, int tx, int ty,
                           bool general, bool streaming, hipStream_t stream) {
-  const int bw = tx / kPoints<T>, threads = bw * ty;
-  if (bw < 1 || threads < 64 || threads > kMaxThreads<T>) return hipErrorInvalidValue;
+  const int lbw = log2_of(tx / kPoints<T>), threads = tx / kPoints<T> * ty;
+  if (lbw < 0 || threads < 64 || threads > kMaxThreads<T>) return hipErrorInvalidValue;
   auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(items), dim3(threads), 0, stream, table, first, n_active, j, bw);
+    hipLaunchKernelGGL(kernel, dim3(items), dim3(threads), 0, stream, table, first, n_active, j, lbw);
     return hipGetLastError();
   };
   return by_flags(!(j & 1), general, streaming, [&](auto p, auto g, auto s) {
-    return launch(&window_batch_kernel<T, decltype(p)::value, decltype(g)::value, decltype(s)::value>);
+    return launch(&window_batch_kernel<T, NMAX, decltype(p)::value, decltype(g)::value, decltype(s)::value>);
   });
+}
+
+template <typename T, typename... A>
+hipError_t launch_batch_nm(int nm, A... args) {
+  switch (nm) {
+    case 2: return launch_batch_t<T, 2>(args...);
+    case 3: return launch_batch_t<T, 3>(args...);
+    case 4: return launch_batch_t<T, 4>(args...);
+  }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace
@@ -623,6 +689,23 @@ WindowGrid window_grid(int nx, int ny, int px, int py, int tx, int ty, int N, in
   return g;
 }
 
+WindowOrder window_order(const WindowGrid& g, int strip) {
+  WindowOrder o;
+  o.ntx = g.ntx;
+  o.nty = g.nty;
+  o.nchunks = g.nchunks;
+  o.strip = strip;
+  const int ntiles = g.ntx * g.nty, tail = ntiles % kGroup;
+  o.per = divisor(kGroup * g.nchunks);
+  o.tail = divisor(tail);
+  const int w = strip >= 2 ? strip : strip <= -2 ? -strip : 1;
+  const int across = strip <= -2 ? g.nty : g.ntx, along = strip <= -2 ? g.ntx : g.nty;
+  o.band = divisor(int(std::min<int64_t>(int64_t(w) * across, 0x7FFFFFFF)));
+  o.rows = divisor(w);
+  o.last = divisor(along % w);
+  return o;
+}
+
 hipError_t launch_window(int storage, const WindowArgs& w, hipStream_t stream) {
   switch (storage) {
     case STORE_FP64: return launch_nm<double>(w, stream);
@@ -633,12 +716,12 @@ hipError_t launch_window(int storage, const WindowArgs& w, hipStream_t stream) {
 }
 
 hipError_t launch_window_batch(int storage, const WindowEntry* table, const int* first, int n_active, int items, int j,
-                               int tx, int ty, bool general, bool streaming, hipStream_t stream) {
+                               int tx, int ty, int nm, bool general, bool streaming, hipStream_t stream) {
   if (n_active < 1 || items < 1) return hipErrorInvalidValue;
   switch (storage) {
-    case STORE_FP64: return launch_batch_t<double>(table, first, n_active, items, j, tx, ty, general, streaming, stream);
-    case STORE_FP32: return launch_batch_t<float>(table, first, n_active, items, j, tx, ty, general, streaming, stream);
-    case STORE_BF16: return launch_batch_t<bf16>(table, first, n_active, items, j, tx, ty, general, streaming, stream);
+    case STORE_FP64: return launch_batch_nm<double>(nm, table, first, n_active, items, j, tx, ty, general, streaming, stream);
+    case STORE_FP32: return launch_batch_nm<float>(nm, table, first, n_active, items, j, tx, ty, general, streaming, stream);
+    case STORE_BF16: return launch_batch_nm<bf16>(nm, table, first, n_active, items, j, tx, ty, general, streaming, stream);
   }
   return hipErrorInvalidValue;
 }

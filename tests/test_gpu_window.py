@@ -32,6 +32,7 @@ CASES = [
     (13, (191, 130), (X, X), False),
     (16, (62, 17), (P, P), True),
     (21, (31, 64), (X, X), True),
+    (3, (700, 531), (X, P), False),  # several groups of 512 tiles, the last a partial one
 ]
 
 
