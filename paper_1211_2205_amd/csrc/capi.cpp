@@ -2018,7 +2018,7 @@ int batch_ready(starmap_batch* b) {
 int items_of(const starmap_solver* s) {
   const TileShape ts = sweep_variant(s->storage, s->variant);
   if (sweep_in_registers(s->storage, s->variant)) {
-    const WindowGrid g = window_grid(s->nx, s->ny, s->px, s->py, ts.tx, ts.ty, s->N, window_nm(s->N, s->chunk_width));
+    const WindowGrid g = window_grid(s->storage, s->nx, s->ny, s->px, s->py, ts.tx, ts.ty, s->N, window_nm(s->N, s->chunk_width));
     return g.ntx * g.nty * g.nchunks;
   }
   const int ntx = (s->nx + 1 + ts.tx - 1) / ts.tx, nty = (s->ny + 1 + ts.ty - 1) / ts.ty;
@@ -2101,7 +2101,7 @@ int batch_table(starmap_batch* b, const std::vector<int>& sweeps, bool zero_tau)
         w.N = s->N;
         w.nm = window_nm(s->N, s->chunk_width);
         g.nm = std::max(g.nm, w.nm);
-        const WindowGrid wg = window_grid(s->nx, s->ny, s->px, s->py, ts.tx, ts.ty, s->N, w.nm);
+        const WindowGrid wg = window_grid(s->storage, s->nx, s->ny, s->px, s->py, ts.tx, ts.ty, s->N, w.nm);
         w.order = window_order(wg, s->tile_strip);
         w.planes[0] = s->win_planes[0];
         w.planes[1] = s->win_planes[1];

@@ -100,7 +100,7 @@ int window_nm(int N, int width);
 struct WindowGrid {
   int ntx, nty, nchunks;
 };
-WindowGrid window_grid(int nx, int ny, int px, int py, int tx, int ty, int N, int nm);
+WindowGrid window_grid(int storage, int nx, int ny, int px, int py, int tx, int ty, int N, int nm);
 // Division of 0 <= n < 2^31 by a constant: n / d = n m >> s.
 struct Divisor {
   uint32_t m = 0, s = 0;

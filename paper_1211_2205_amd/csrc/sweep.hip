@@ -630,16 +630,15 @@ TileShape sweep_variant(int storage, int v) {
 constexpr double kCache = 2.56e8;
 bool sweep_streams(double state_bytes) { return state_bytes > kCache; }
 
-// FP64.  With the window in registers, 64 x 2 tiles (P_7 280^2 13.4, LDS 16;
-// P_9 400^2 32, LDS 35; P_39 180^2 65, LDS 92), but in LDS, 32 x 8
-//   - where few orders cannot hide the loads of a large grid (P_5 400^2 14.5,
-//     registers 16; P_7 500^2 27 and 29; P_9 550^2 is 57 and 52), with more
-//     points per tile where the window is smallest (P_1 700^2: 64 x 8 10,
-//     32 x 8 11.6; P_3 1000^2 34 and 36);
+// FP64.  With the window in registers, 64 x 2 tiles (P_7 280^2 11.6, LDS 16;
+// P_3 1000^2 34 and 36; P_5 400^2 14.3 and 15.3; P_9 550^2 44 and 58; P_15 447^2
+// 62 and 77; P_31 150^2 36 and 59), but in LDS
+//   - where one or two orders cannot hide the loads of a large grid: 64 x 8
+//     (P_1 400^2 6.5, registers 6.9; 1000^2 17 and 24);
 //   - beyond the cache, where the y neighbours' lines leave the L1 before they
-//     are asked for (P_39 1000^2 2040, registers 2285; P_9 850^2 119 and 156),
-//     unless the LDS tiles are too few to fill the chip (P_39 200^2 118,
-//     registers 106; 300^2 are 216 both).
+//     are asked for: 32 x 8 (P_39 500^2 557, registers 687; P_9 850^2 119 and
+//     142; P_7 1000^2 89 and 132), unless the LDS tiles are too few to fill the
+//     chip (P_39 200^2 118, registers 108).
 // FP32, BF16.  Large states on wide tiles, which read the fewest lines twice,
 // where the grid fills them (P_39 1000^2 FP32: 128 x 2 1014, 64 x 4 1028), else
 // 64 wide (P_31 447^2, 448 columns: 64 x 8 116, 128 x 2 126).  States in the
@@ -650,8 +649,8 @@ int sweep_default_variant(int storage, int N, int cols, int rows, double state_b
   const double points = double(cols) * rows;
   const bool cached = !sweep_streams(state_bytes);
   if (storage == STORE_FP64) {
-    const bool lds = cached ? N <= 7 && points > 1.2e5 : points > 6.0e4;
-    return !lds ? 12 : N <= 3 && points > 2.0e5 ? 7 : 8;
+    if (cached) return N <= 2 && points > 1.2e5 ? 7 : 12;
+    return points > 6.0e4 ? (N <= 3 ? 7 : 8) : 12;
   }
   const int wide = storage == STORE_FP32 ? 128 : 256;
   const int padded = (cols + wide - 1) / wide * wide;
@@ -665,10 +664,12 @@ int sweep_default_variant(int storage, int N, int cols, int rows, double state_b
 // window from P_13) ranges of six (LDS P_39 1000^2: 2040, eight 2200, four
 // 2110), below it four: more workgroups, and no idle rows in P_15 (FP32 447^2
 // 30, six 31); of grids that fill the chip anyway, six (P_9 1000^2 FP32 57,
-// four 61).  Register windows of eight-byte values hold no more than four.
+// four 61).  Register windows of eight-byte values: four, for P_4 and P_5 six,
+// one range, once the workgroups fill the chip (P_5 150^2 5.3, six 5.7; 300^2
+// 9.7 and 8.7; 700^2 36 and 32).
 int sweep_default_width(int storage, int variant, int N, int cols, int rows) {
   const bool registers = sweep_in_registers(storage, variant);
-  if (storage == STORE_FP64 && registers) return 4;
+  if (storage == STORE_FP64 && registers) return (N == 4 || N == 5) && double(cols) * rows > 4.0e4 ? 6 : 4;
   if (N == 4 || N == 5) return 6;
   if (!registers) return N == 6 || N == 7 ? 8 : N >= 13 ? 6 : 4;
   return N >= 16 || (N >= 8 && double(cols) * rows > 5.0e5) ? 6 : 4;

@@ -11,8 +11,8 @@
 // the x and y differences of the NM + 1 R and I planes of the input orders
 // l + 1 and l - 1 in the range.  The differences of order l + 1 are in
 // registers from the rows before; of each plane of order l - 1 the thread has
-// loaded its own points, the x neighbour and the y neighbour: it forms the
-// plane's two differences, at once reloads the plane's registers with the
+// loaded its own points, the y neighbour and, but with FP64, the x neighbour
+// (kOverlap): it forms the plane's two differences, at once reloads the plane's registers with the
 // order two below, and updates the row whose last input that plane was.
 // Nothing is shared between threads: no LDS, no barrier, and every wave has a
 // whole order's planes and rows in flight while it computes the order before.
@@ -23,12 +23,12 @@
 // neighbours in the workgroup have just loaded).  Per sweep, LDS kernel with
 // its best tile -> this kernel with its default one: P_39 1000^2 BF16 838 ->
 // 518 us, FP32 1107 -> 1014 us; P_31 256^2 FP32 76 -> 40 us, BF16 71 -> 29 us;
-// P_9 317 x 203 FP32 15.5 -> 7.9 us; P_7 280^2 FP64 16.2 -> 13.5 us; P_3 100^2
-// FP64 7.4 -> 4.1 us.  P_39 1000^2 FP32 moves 4.9 GB per sweep at 4.8 TB/s; with
+// P_9 317 x 203 FP32 15.5 -> 7.9 us; P_7 280^2 FP64 16.2 -> 10.8 us; P_3 100^2
+// FP64 7.4 -> 3.6 us.  P_39 1000^2 FP32 moves 4.9 GB per sweep at 4.8 TB/s; with
 // every neighbour load left out it takes 1020 us, so the memory's rate for this
 // mix of reads and writes bounds it.  FP64 states beyond the cache are slower
-// here (P_39 1000^2 2285 against 2035 us): eight-byte loads of three points per
-// plane need twice the L1 lines in flight, so the y neighbours' lines are gone
+// here (P_39 500^2 687 against 557 us): eight-byte loads need twice the L1 lines
+// in flight, so the y neighbours' lines are gone
 // before they are asked for.
 //
 // Boundary conditions enter through the offsets of the neighbour loads (wrap
@@ -58,8 +58,9 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // that the next sweep finds them there (P_31 256^2 FP32 47 -> 40 us, P_39 150^2
 // FP64 66 -> 52).
 constexpr int kStream = 2;
-// a byte offset past every plane (planes stay below 2^31 bytes)
-constexpr uint32_t kOutside = 0x80000000u;
+// a byte offset past every pair of planes (planes stay below 2^31 bytes and are
+// a multiple of 256)
+constexpr uint32_t kOutside = 0xFFFFFF00u;
 
 // x-adjacent points per thread: two BF16 values make one 32-bit access (one
 // value per thread: half the bytes per instruction, four: 2% slower on P_39
@@ -67,6 +68,15 @@ constexpr uint32_t kOutside = 0x80000000u;
 // (P_31 256^2: 83 against 53 us, fewer waves of eight-byte loads).
 template <typename T>
 constexpr int kPoints = sizeof(T) == 2 ? 2 : 1;
+
+// Whether the x neighbours are the values of the lanes next to each lane, in
+// tiles whose rows overlap by the lanes at their ends, or loads of their own.
+// An eight-byte load holds the address unit for 16 cycles: with three per plane
+// it was busy for 70% of a sweep (P_7 280^2 12.7 -> 10.8 us).  Four-byte loads
+// take 6 cycles, less than two lane shifts and the overlap's idle lanes (P_9
+// 317 x 203 FP32 7.2 -> 8.5).
+template <typename T>
+constexpr bool kOverlap = sizeof(T) == 8;
 
 // A thread's V stored values of a row segment as one memory access.
 template <typename T, int V>
@@ -111,12 +121,18 @@ __device__ __forceinline__ Word<T, V> word(const typename ComputeOf<T>::type (&v
     return __builtin_bit_cast(Word<T, V>, v[0]);
 }
 
-// The value of the lane before (BEFORE) or after this one; every lane of the
-// wave must take part.
+// The value of the lane before (BEFORE) or after this one, in the wave's first
+// or last lane its own; every lane of the wave must take part.
 template <bool BEFORE>
 __device__ __forceinline__ float lane_near(float v) {
-  return __uint_as_float(
-      uint32_t(__builtin_amdgcn_update_dpp(0, int(__float_as_uint(v)), BEFORE ? 0x138 : 0x130, 0xF, 0xF, true)));
+  const int w = int(__float_as_uint(v));
+  return __uint_as_float(uint32_t(__builtin_amdgcn_update_dpp(w, w, BEFORE ? 0x138 : 0x130, 0xF, 0xF, false)));
+}
+template <bool BEFORE>
+__device__ __forceinline__ double lane_near(double v) {
+  const u32x2 w = __builtin_bit_cast(u32x2, v);
+  return __builtin_bit_cast(double, u32x2{__float_as_uint(lane_near<BEFORE>(__uint_as_float(w.x))),
+                                          __float_as_uint(lane_near<BEFORE>(__uint_as_float(w.y)))});
 }
 
 // Scalars of one sweep.
@@ -206,17 +222,31 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
   if (o0 >= o1) return;
   const int lfirst = ltop - 2 * o0, llast = ltop - 2 * (o1 - 1);
 
-  // this thread's points (X .. X + V - 1, Y); lanes past the tile or the grid
-  // stand at the origin and store nothing
+  // this thread's points (X .. X + V - 1, Y)
   const int2 txy = tile_at(tile, a.o);
   const int bw = 1 << a.lbw;
   const int f = txy.y * a.threads + int(threadIdx.x);
   int Y = f >> a.lbw;
   const int col = f & (bw - 1);
-  int X = (txy.x * bw + col) * V;
   const int rows = a.ny + 1 - a.py, cols = a.nx + 1 - a.px;
-  const bool in = Y < rows && X < cols;
-  if (!in) X = Y = 0;
+  int X;
+  bool in;
+  if constexpr (kOverlap<T>) {
+    // a piece of a row lies in one wave, and its end lanes stand on the points
+    // next to it; the last point of an axis that does not wrap needs none, nor
+    // does its first one, if it is a wave's first lane
+    const int lp = min(a.lbw, 6), last = (1 << lp) - 1, q = col & last;
+    const int lead = a.px || lp < 6 ? 1 : 0, x0 = ((txy.x << (a.lbw - lp)) + (col >> lp)) * (last - 1);
+    X = x0 + q - lead;
+    in = Y < rows && X < cols && (q > 0 || (!lead && X == 0)) && (q < last || (!a.px && X == a.nx)) &&
+         (x0 == 0 || x0 < cols - (a.px ? 0 : 2 - lead));  // (a piece that is one too many)
+    Y = min(Y, rows - 1);
+  } else {
+    // lanes past the tile or the grid stand at the origin and store nothing
+    X = (txy.x * bw + col) * V;
+    in = Y < rows && X < cols;
+    if (!in) X = Y = 0;
+  }
   // points of the lane on the two output grids: R rows are cell-centred along
   // y (and along x in even sweeps), I rows nodal along y (and along x in even
   // sweeps); R inputs are cell-centred along y (and along x in odd sweeps),
@@ -234,34 +264,37 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
   const int nv = min(V, a.nx - X);
   const int xq = X + max(nv, 1);
   const int xhi = a.px ? (xq >= a.nx ? xq - a.nx : xq) : min(xq, a.nx);
-  const int xcc = V == 1 ? min(X, a.nx - 1) : X;
-  const int xcR = P ? xcc : X, xcI = P ? X : xcc;
-  // With two points per thread the x neighbour is a value of the next lane
-  // (no load: P_39 1000^2 BF16 587 -> 532 us, the address unit had been the limit),
-  // except in the lanes at the ends of a wave, a tile row or the grid, which
-  // load it; single points are faster with the load (P_31 256^2 FP32 53
-  // against 56 us).
+  // columns that the lane loads of node and cell planes
+  const int wrapped = X < 0 ? X + a.nx : X >= a.nx ? X - a.nx : X;
+  const int xn = !kOverlap<T> ? X : a.px ? min(wrapped, a.nx - 1) : max(min(X, a.nx), 0);
+  const int xc = V > 1 ? X : min(xn, a.nx - 1);
+  const int xcR = P ? xc : xn, xcI = P ? xn : xc;
+  // The x neighbour is a value of the next lane (no load: P_39 1000^2 BF16 587
+  // -> 532 us, the address unit had been the limit).  With two points per
+  // thread the lanes at the ends of a wave, a tile row or the grid load it.
   const int lane = int(threadIdx.x) & 63;
   const bool endL = V == 1 || lane == 0 || col == 0 || !in || X == 0;
   const bool endH = V == 1 || lane == 63 || col == bw - 1 || !in || X + V >= cols;
   const uint32_t rowR = uint32_t(ycR * a.pitch), rowI = uint32_t(Y * a.pitch);
   const uint32_t cR = (rowR + xcR) * TS, bR = uint32_t(ynR * a.pitch + xcR) * TS;
-  const uint32_t cI = (rowI + xcI) * TS, bI = uint32_t(ynI * a.pitch + xcI) * TS;
+  // (an I plane follows its R plane: one descriptor serves both)
+  const uint32_t pbytes = a.ps * TS;
+  const uint32_t cI = (rowI + xcI) * TS + pbytes, bI = uint32_t(ynI * a.pitch + xcI) * TS + pbytes;
   const uint32_t nR = (P ? endL : endH) ? (rowR + (P ? xlo : xhi)) * TS : kOutside;
-  const uint32_t nI = (P ? endH : endL) ? (rowI + (P ? xhi : xlo)) * TS : kOutside;
-  const uint32_t go = uint32_t(Y * a.pitch + X);
-  const uint32_t sR = okR ? go * TS : kOutside, sI = okI ? go * TS : kOutside;
+  const uint32_t nI = (P ? endH : endL) ? (rowI + (P ? xhi : xlo)) * TS + pbytes : kOutside;
+  const uint32_t go = uint32_t(Y * a.pitch + xn);
+  const uint32_t sR = okR ? go * TS : kOutside, sI = okI ? go * TS + pbytes : kOutside;
 
   // address of plane k, and the descriptor of a plane at an address
-  const int pbytes = int(a.ps * TS);
   auto plane_addr = [&](int k) { return uint64_t(U) + uint64_t(int64_t(k) * int64_t(pbytes)); };
-  auto plane = [&](uint64_t p, int records) {
-    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(p), 0, records, 0x00020000);
+  auto plane = [&](uint64_t p, uint32_t records) {
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(p), 0, int(records), 0x00020000);
   };
-  // records of a plane of index m in an order of highest index lm: none past
-  // it (as bit operations: a comparison would travel as a 64-lane mask)
-  auto recs = [&](int m, int lm) { return pbytes & ~((lm - m) >> 31); };
-  const int first = m0 > 0 ? -1 : 0;  // the range of m = 0 has no planes of m < 0 and no I_0
+  // records of the pair of planes of index m in an order of highest index lm:
+  // none past it (as bit operations: a comparison would travel as a 64-lane
+  // mask).  The range of m = 0 has no planes of m < 0 and no I_0.
+  const uint32_t pair = 2 * pbytes, pair0 = m0 > 0 ? pair : pbytes, none0 = m0 > 0 ? pair : 0;
+  auto recs = [&](uint32_t of, int m, int lm) { return of & ~uint32_t((lm - m) >> 31); };
 
   // raw words of the input planes: centre, x neighbour, y neighbour
   struct In {
@@ -275,15 +308,13 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
   // planes number b (m = m0 + P - 1 + 2 b) of an order, R at address p and I
   // after it, existing for m <= lm
   auto load_planes = [&](int b, uint64_t p, int lm) {
-    const int n = recs(m0 + P - 1 + 2 * b, lm);
-    const auto r = plane(p, P == 0 && b == 0 ? n & first : n);
+    const auto r = plane(p, recs(b ? pair : P ? pair0 : none0, m0 + P - 1 + 2 * b, lm));
     rR[b].c = buf_load<W>(r, cR);
-    rR[b].n = buf_load<W1>(r, nR);
+    if constexpr (!kOverlap<T>) rR[b].n = buf_load<W1>(r, nR);
     rR[b].b = buf_load<W>(r, bR);
-    const auto i = plane(p + uint32_t(pbytes), b == 0 ? n & first : n);
-    rI[b].c = buf_load<W>(i, cI);
-    rI[b].n = buf_load<W1>(i, nI);
-    rI[b].b = buf_load<W>(i, bI);
+    rI[b].c = buf_load<W>(r, cI);
+    if constexpr (!kOverlap<T>) rI[b].n = buf_load<W1>(r, nI);
+    rI[b].b = buf_load<W>(r, bI);
   };
   // differences of a plane: along x centre - lower (cells) or upper - centre
   // (nodes), along y likewise (R planes are cells, I planes nodes)
@@ -292,16 +323,18 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
 #pragma unroll
     for (int e = 0; e < V; ++e) v[e] = value<T, V>(w.c, e);
     C nb = value<T, 1>(w.n, 0);
-    if constexpr (V > 1) {
+    if constexpr (kOverlap<T> || V > 1) {
       const C near = cell ? lane_near<true>(v[V - 1]) : lane_near<false>(v[0]);
-      nb = (cell ? endL : endH) ? nb : near;
+      nb = kOverlap<T> || !(cell ? endL : endH) ? near : nb;
     }
 #pragma unroll
     for (int e = 0; e < V; ++e) {
       const C q = value<T, V>(w.b, e);
       d.y[e] = isR ? v[e] - q : q - v[e];
     }
-    if (cell) {
+    if constexpr (V == 1) {
+      d.x[0] = cell ? v[0] - nb : nb - v[0];
+    } else if (cell) {
       if constexpr (V > 1) {  // the point past the last cell repeats it
         v[V - 1] = !a.px && X + 1 == a.nx ? v[0] : v[V - 1];
         v[0] = !a.px && X == a.nx ? nb : v[0];
@@ -318,15 +351,14 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
   // tab[2 (N + 1) + k]; none: zeros)
   W uR[NM], uI[NM], qR[G ? NM : 1], qI[G ? NM : 1];
   auto load_row = [&](int q, uint64_t p, int lm, int k) {
-    const int m = m0 + P + 2 * q;
-    const int n = recs(m, lm);
-    const int ni = P == 0 && q == 0 ? n & first : n;
-    uR[q] = buf_load<W, AUX>(plane(p, n), sR);
-    uI[q] = buf_load<W, AUX>(plane(p + uint32_t(pbytes), ni), sI);
+    const uint32_t n = recs(P == 0 && q == 0 ? pair0 : pair, m0 + P + 2 * q, lm);
+    const auto u = plane(p, n);
+    uR[q] = buf_load<W, AUX>(u, sR);
+    uI[q] = buf_load<W, AUX>(u, sI);
     if constexpr (G) {
-      const int r = n ? tab[2 * (a.N + 1) + k] : -1, i = ni ? tab[2 * (a.N + 1) + k + 1] : -1;
+      const int r = n ? tab[2 * (a.N + 1) + k] : -1, i = n > pbytes ? tab[2 * (a.N + 1) + k + 1] : -1;
       qR[q] = buf_load<W>(plane(plane_addr(r), r >= 0 ? pbytes : 0), sR);
-      qI[q] = buf_load<W>(plane(plane_addr(i), i >= 0 ? pbytes : 0), sI);
+      qI[q] = buf_load<W>(plane(plane_addr(i - 1), i >= 0 ? pair : 0), sI);
     }
   };
 
@@ -422,7 +454,7 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
 #pragma unroll
       for (int e = 0; e < V; ++e) asm volatile("" : "+v"(dR.x[e]), "+v"(dR.y[e]), "+v"(dI.x[e]), "+v"(dI.y[e]));
       load_planes(b, pl, lm);
-      pl += 2 * uint64_t(uint32_t(pbytes));
+      pl += 2 * uint64_t(pbytes);
       if (b < NM) {  // the rows of index m0 + P + 2 b
         const int j = 2 * (NM - 1 - b);
         C8 crn{}, cin{};
@@ -430,7 +462,8 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
           crn = cf[j + 2];
           cin = cf[j + 3];
         }
-        const int n = recs(m0 + P + 2 * b, l);
+        const auto out = plane(ps, recs(P == 0 && b == 0 ? pair0 : pair, m0 + P + 2 * b, l));
+        ps += 2 * uint64_t(pbytes);
 #pragma unroll
         for (int z = 0; z < 2; ++z) {
           // an R row takes the x differences of R planes and the y differences
@@ -455,11 +488,10 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
             // (a lane's second point past the grid keeps the padding's value)
             nv_[e] = e == 0 || X + e < (z ? vxI : vxR) ? r : u;
           }
-          buf_store<W, AUX>(word<T, V>(nv_), plane(ps, P == 0 && z && b == 0 ? n & first : n), z ? sI : sR);
-          ps += uint32_t(pbytes);
+          buf_store<W, AUX>(word<T, V>(nv_), out, z ? sI : sR);
         }
         load_row(b, pn, ln, kn + j);
-        pn += 2 * uint64_t(uint32_t(pbytes));
+        pn += 2 * uint64_t(pbytes);
         hR[b + 1] = lR;
         hI[b + 1] = lI;
         cr = crn;
@@ -595,7 +627,7 @@ hipError_t by_flags(bool parity, bool general, bool streaming, F f) {
 }
 
 template <typename T, int NM>
-hipError_t launch_t(const WindowArgs& w, hipStream_t stream) {
+hipError_t launch_t(int storage, const WindowArgs& w, hipStream_t stream) {
   using C = typename ComputeOf<T>::type;
   WindowScalars<C> a;
   a.ps = uint32_t(w.plane_stride);
@@ -607,7 +639,7 @@ hipError_t launch_t(const WindowArgs& w, hipStream_t stream) {
   const int bw = w.tx / kPoints<T>;
   a.lbw = log2_of(bw);
   a.threads = bw * w.ty;
-  const WindowGrid g = window_grid(w.nx, w.ny, w.px, w.py, w.tx, w.ty, w.N, w.nm);
+  const WindowGrid g = window_grid(storage, w.nx, w.ny, w.px, w.py, w.tx, w.ty, w.N, w.nm);
   a.o = window_order(g, w.strip);
   // A launch of fewer workgroups than compute units is a chain of memory
   // round trips, one per order: its orders are split into runs that start
@@ -637,11 +669,11 @@ hipError_t launch_t(const WindowArgs& w, hipStream_t stream) {
 }
 
 template <typename T>
-hipError_t launch_nm(const WindowArgs& w, hipStream_t stream) {
+hipError_t launch_nm(int storage, const WindowArgs& w, hipStream_t stream) {
   switch (w.nm) {
-    case 2: return launch_t<T, 2>(w, stream);
-    case 3: return launch_t<T, 3>(w, stream);
-    case 4: return launch_t<T, 4>(w, stream);
+    case 2: return launch_t<T, 2>(storage, w, stream);
+    case 3: return launch_t<T, 3>(storage, w, stream);
+    case 4: return launch_t<T, 4>(storage, w, stream);
   }
   return hipErrorInvalidValue;
 }
@@ -680,10 +712,20 @@ int window_nm(int N, int width) {
   return nm < 2 ? 2 : nm > 4 ? 4 : nm;
 }
 
-WindowGrid window_grid(int nx, int ny, int px, int py, int tx, int ty, int N, int nm) {
-  // tiles of tx x ty points over every point that lies on one of the grids
+WindowGrid window_grid(int storage, int nx, int ny, int px, int py, int tx, int ty, int N, int nm) {
+  // tiles over every point that lies on one of the grids.  With FP64 the end lanes of a row's pieces (64 lanes at most) stand on the points
+  // next to the piece, except at an end of the grid (window_tile).
   WindowGrid g;
-  g.ntx = (nx + 1 - px + tx - 1) / tx;
+  const int cols = nx + 1 - px;
+  if (storage == STORE_FP64) {
+    const int piece = tx < 64 ? tx : 64, own = piece - 2;
+    const int ends = px ? 0 : piece < 64 ? 1 : 2;
+    const int pieces = std::max(1, (cols - ends + own - 1) / own);
+    const int across = tx / piece;
+    g.ntx = (pieces + across - 1) / across;
+  } else {
+    g.ntx = (cols + tx - 1) / tx;
+  }
   g.nty = (ny + 1 - py + ty - 1) / ty;
   g.nchunks = (N + 1 + 2 * nm - 1) / (2 * nm);
   return g;
@@ -708,9 +750,9 @@ WindowOrder window_order(const WindowGrid& g, int strip) {
 
 hipError_t launch_window(int storage, const WindowArgs& w, hipStream_t stream) {
   switch (storage) {
-    case STORE_FP64: return launch_nm<double>(w, stream);
-    case STORE_FP32: return launch_nm<float>(w, stream);
-    case STORE_BF16: return launch_nm<bf16>(w, stream);
+    case STORE_FP64: return launch_nm<double>(storage, w, stream);
+    case STORE_FP32: return launch_nm<float>(storage, w, stream);
+    case STORE_BF16: return launch_nm<bf16>(storage, w, stream);
   }
   return hipErrorInvalidValue;
 }

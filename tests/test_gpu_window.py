@@ -148,3 +148,16 @@ def test_refused_tiles_stay_refused_after_a_register_window(monkeypatch):
         s.advance(1)
         s.synchronize()
         s.close()
+
+
+@pytest.mark.parametrize("bc", [(X, X), (P, X)])
+@pytest.mark.parametrize("nx", [29, 30, 31, 60, 61, 62, 63, 64, 122, 123, 124, 125, 126, 186])
+def test_fp64_tiles_that_overlap_by_their_end_lanes(nx, bc):
+    """Rows one point below, at and above whole pieces of 62 points: every
+    point is updated once, from the neighbours the LDS window gives it."""
+    prob = _problem(3, (nx, 5), bc, nx % 2 == 0)
+    init = _init(prob)
+    ref = _run(prob, init, LDS, 8)
+    for v in WINDOW:
+        for k, (a, b) in enumerate(zip(_run(prob, init, v, 4), ref)):
+            assert np.array_equal(a, b), (v, k)
