@@ -2019,7 +2019,7 @@ int items_of(const starmap_solver* s) {
   const TileShape ts = sweep_variant(s->storage, s->variant);
   if (sweep_in_registers(s->storage, s->variant)) {
     const WindowGrid g = window_grid(s->storage, s->nx, s->ny, s->px, s->py, ts.tx, ts.ty, s->N, window_nm(s->N, s->chunk_width));
-    return g.ntx * g.nty * g.nchunks;
+    return window_order(g, s->tile_strip).items;
   }
   const int ntx = (s->nx + 1 + ts.tx - 1) / ts.tx, nty = (s->ny + 1 + ts.ty - 1) / ts.ty;
   return ntx * nty * int(s->prog[0].chunks.size());

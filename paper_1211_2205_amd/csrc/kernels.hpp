@@ -105,12 +105,13 @@ WindowGrid window_grid(int storage, int nx, int ny, int px, int py, int tx, int 
 struct Divisor {
   uint32_t m = 0, s = 0;
 };
-// How a workgroup's number becomes an m range and a tile: numbers per group of
-// tiles, tiles of the last group, and the divisors of the tile order.
+// How a workgroup's number becomes an m range and a tile: groups of gsize tiles
+// (the last may be smaller), a group's ranges one after another, a range's tiles.
 struct WindowOrder {
-  Divisor per, tail;          // numbers per group; tiles of the last group
+  Divisor per, by_gsize;      // numbers per group and per range of a group
   Divisor band, rows, last;   // tiles per strip; a strip's width, the last strip's
-  int ntx, nty, nchunks, strip;
+  int ntx, nty, nchunks, strip, gsize;
+  int items;                  // numbers in all
 };
 WindowOrder window_order(const WindowGrid& g, int strip);
 hipError_t launch_window(int storage, const WindowArgs& w, hipStream_t stream);

@@ -172,19 +172,20 @@ __device__ __forceinline__ int2 tile_at(int t, const WindowOrder& o) {
   return make_int2(t - band * o.ntx, band);
 }
 
-// Tiles of one group: the work items of a group are numbered range by range,
-// and the ranges of low m, which have the most orders, come first.  Ranges as
-// the inner index, as the LDS kernel takes them (its ranges share staged
-// lines), leave the long ranges to the end of a launch: P_39 1000^2 FP32 1100
-// against 1026 us, P_31 256^2 53 against 48 us.  One group over the whole of a
-// large grid loses the overlap of the ranges' shared planes: 1040 us.
+// Tiles of one group, about: the workgroups of a group are numbered range by
+// range, and the ranges of low m, which have the most orders, come first.
+// Ranges as the inner index, as the LDS kernel takes them (its ranges share
+// staged lines), leave the long ranges to the end of a launch: P_39 1000^2 FP32
+// 1100 against 1026 us, P_31 256^2 53 against 48 us.  One group over the whole
+// of a large grid loses the overlap of the ranges' shared planes: 1040 us.
 constexpr int kGroup = 512;
 constexpr int kXcds = 8;
 
 template <typename T, int NM, int P, bool G, bool S>
 __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename ComputeOf<T>::type* __restrict__ decay,
                                             cptr<typename ComputeOf<T>::type> coef, cptr<int> tab,
-                                            const WindowScalars<typename ComputeOf<T>::type>& a, int item) {
+                                            const WindowScalars<typename ComputeOf<T>::type>& a, int grp, int chunk,
+                                            int tl, int seg) {
   using C = typename ComputeOf<T>::type;
   constexpr int V = kPoints<T>;
   static_assert(V <= 2, "a pair at most");
@@ -195,25 +196,17 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
   constexpr int AUX = S ? kStream : 0;
   constexpr int NB = NM + 1;  // input planes of one order that the range needs, R and I each
 
-  // work item -> run of orders, m range, tile
-  int seg = 0;
-  if (a.nseg > 1) {
-    const int q = divide(item, a.by_nseg);
-    seg = item - q * a.nseg;
-    item = q;
-  }
-  const int per = kGroup * a.o.nchunks, grp = divide(item, a.o.per), within = item - grp * per;
-  const int ntiles = a.o.ntx * a.o.nty, gtiles = min(kGroup, ntiles - grp * kGroup);
-  const int chunk = gtiles == kGroup ? within / kGroup : divide(within, a.o.tail);
   // consecutive workgroups run on the chip's XCDs in turn: each takes a run of
   // neighbouring tiles, whose shared rows its L2 then holds (P_9 317 x 203 FP32
   // 8.2 -> 7.5 us, P_7 280^2 FP64 14.6 -> 14.0, P_39 1000^2 BF16 528 -> 517)
-  const int tl = within - chunk * gtiles, xcd = tl % kXcds;
-  const int tile = grp * kGroup + xcd * (gtiles / kXcds) + min(xcd, gtiles % kXcds) + tl / kXcds;
+  const uint32_t gtiles = uint32_t(min(a.o.gsize, a.o.ntx * a.o.nty - grp * a.o.gsize)), xcd = uint32_t(tl) % kXcds;
+  if (uint32_t(tl) >= gtiles) return;  // (the last group may be smaller)
+  const int tile =
+      grp * a.o.gsize + int(xcd * (gtiles / kXcds) + min(xcd, gtiles % kXcds) + uint32_t(tl) / kXcds);
   int m0 = chunk * 2 * NM;
   const int ltop = a.N - ((a.N - P) & 1), lbot = m0 + P;
   if (lbot > ltop) return;  // no output rows in this m range
-  const int nord = (ltop - lbot) / 2 + 1;
+  const int nord = ((ltop - lbot) >> 1) + 1;
   int o0 = 0, o1 = nord;
   if (a.nseg > 1) {
     o0 = divide(nord * seg, a.by_nseg);
@@ -387,25 +380,45 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
 
   // prologue: the input planes of both neighbouring orders and the first rows,
   // all in flight together
+  // planes and rows in memory order, from the highest m of the range down: of
+  // this order the first row, number k0, at ps; of the next one the first row at
+  // pn; the first plane loaded next at pl.  From one order to the next they move
+  // by a distance that shrinks by four planes, so only the first ones take
+  // multiplications (the scalar unit, which a compute unit's waves share, spends
+  // as long on a small sweep as the address unit).
   int l = lfirst;
+  int k0 = int(uint32_t(l * (l + 1)) >> 1) + l - (m0 + P) - 2 * (NM - 1);
+  uint64_t ps = plane_addr(k0), pn = ps - uint64_t(uint32_t(2 * l + 1)) * pbytes,
+           pl = pn - uint64_t(uint32_t(l)) * pbytes;
+  int64_t dn = int64_t(2 * l - 3) * int64_t(pbytes);
   Diff hR[NB], hI[NB];  // differences of input order l + 1
   {
-    const int r0 = l * (l + 1) / 2 + l - (m0 + P);
-    const int kh = r0 + l + 3, kl = r0 - l;  // planes b = 0 of orders l + 1 and l - 1
-    const int shift = l + 1 == a.N ? a.top_shift : 0;
+    const int kh = k0 + l + 1 + (l + 1 == a.N ? a.top_shift : 0);
     load_decay(l);
+    uint64_t p = plane_addr(kh);
 #pragma unroll
-    for (int b = NM; b >= 0; --b) load_planes(b, plane_addr(kh + shift - 2 * b), l < a.N ? l + 1 : -1);
+    for (int b = NM; b >= 0; --b) {
+      load_planes(b, p, l < a.N ? l + 1 : -1);
+      p += pair;
+    }
     In pR[NB], pI[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
       pR[b] = rR[b];
       pI[b] = rI[b];
     }
+    p = ps - uint64_t(uint32_t(l + 2)) * pbytes;
 #pragma unroll
-    for (int b = NM; b >= 0; --b) load_planes(b, plane_addr(kl - 2 * b), l - 1);
+    for (int b = NM; b >= 0; --b) {
+      load_planes(b, p, l - 1);
+      p += pair;
+    }
+    p = ps;
 #pragma unroll
-    for (int q = NM - 1; q >= 0; --q) load_row(q, plane_addr(r0 - 2 * q), l, r0 - 2 * q);
+    for (int q = NM - 1; q >= 0; --q) {
+      load_row(q, p, l, k0 + 2 * (NM - 1 - q));
+      p += pair;
+    }
     apply_decay();  // (while the planes arrive)
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
@@ -435,13 +448,9 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
     // with G: the next rows' decay planes, if they are other ones
     const bool redo = G && more && (tab[2 * l] != tab[2 * l - 4] || tab[2 * l + 1] != tab[2 * l - 3]);
     if (redo) load_decay(l - 2);
-    // planes and rows in memory order, from the highest m of the range down:
-    // the first row of this order, the first row of the next, the first plane
-    // loaded next
-    const int k0 = l * (l + 1) / 2 + l - (m0 + P) - 2 * (NM - 1);
-    const int kn = k0 - (2 * l + 1), kp = kn - l;
-    uint64_t ps = plane_addr(k0), pn = plane_addr(kn), pl = plane_addr(kp);
-    // their coefficients (the table has eight rows of padding on both sides)
+    const int kn = k0 - (2 * l + 1);
+    uint64_t as = ps, an = pn, al = pl;
+    // the rows' coefficients (the table has eight rows of padding on both sides)
     const cptr<C8> cf = reinterpret_cast<cptr<C8>>(cat(coef, uint32_t(k0 + 8) * uint32_t(8 * sizeof(C))));
     C8 cr = cf[0], ci = cf[1];
     Diff lR, lI;  // differences of the plane before (index m + 1 of the next row)
@@ -453,8 +462,8 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
       // (the differences before the loads that overwrite their sources)
 #pragma unroll
       for (int e = 0; e < V; ++e) asm volatile("" : "+v"(dR.x[e]), "+v"(dR.y[e]), "+v"(dI.x[e]), "+v"(dI.y[e]));
-      load_planes(b, pl, lm);
-      pl += 2 * uint64_t(pbytes);
+      load_planes(b, al, lm);
+      al += pair;
       if (b < NM) {  // the rows of index m0 + P + 2 b
         const int j = 2 * (NM - 1 - b);
         C8 crn{}, cin{};
@@ -462,8 +471,8 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
           crn = cf[j + 2];
           cin = cf[j + 3];
         }
-        const auto out = plane(ps, recs(P == 0 && b == 0 ? pair0 : pair, m0 + P + 2 * b, l));
-        ps += 2 * uint64_t(pbytes);
+        const auto out = plane(as, recs(P == 0 && b == 0 ? pair0 : pair, m0 + P + 2 * b, l));
+        as += pair;
 #pragma unroll
         for (int z = 0; z < 2; ++z) {
           // an R row takes the x differences of R planes and the y differences
@@ -490,8 +499,8 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
           }
           buf_store<W, AUX>(word<T, V>(nv_), out, z ? sI : sR);
         }
-        load_row(b, pn, ln, kn + j);
-        pn += 2 * uint64_t(pbytes);
+        load_row(b, an, ln, kn + j);
+        an += pair;
         hR[b + 1] = lR;
         hI[b + 1] = lI;
         cr = crn;
@@ -503,6 +512,11 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
     }
     hR[0] = lR;
     hI[0] = lI;
+    k0 = kn;
+    ps = pn;
+    pn -= uint64_t(dn);
+    pl -= uint64_t(dn) - pair;
+    dn -= 4 * int64_t(pbytes);
     if (redo) apply_decay();
   }
   if (zeroth) {  // R_0^0 couples to R_1^1 and I_1^1 alone
@@ -530,7 +544,9 @@ window_kernel(T* __restrict__ U, const typename ComputeOf<T>::type* __restrict__
               const typename ComputeOf<T>::type* __restrict__ coef, const int* __restrict__ tab,
               const WindowScalars<typename ComputeOf<T>::type> a) {
   using C = typename ComputeOf<T>::type;
-  window_tile<T, NM, P, G, S>(U, decay, (cptr<C>)coef, (cptr<int>)tab, a, int(blockIdx.x));
+  // (a launch of several runs of orders has one group)
+  window_tile<T, NM, P, G, S>(U, decay, (cptr<C>)coef, (cptr<int>)tab, a, a.nseg > 1 ? 0 : int(blockIdx.z),
+                              int(blockIdx.y), int(blockIdx.x), int(blockIdx.z));
 }
 
 // WindowEntry as the device reads it (pointers with their address space, as
@@ -561,10 +577,12 @@ window_batch_kernel(const WindowEntry* __restrict__ table, const int* __restrict
                     const int j, const int lbw) {
   using C = typename ComputeOf<T>::type;
   const int item = int(blockIdx.x);
-  int lo = 0, hi = n_active - 1;  // last instance with first[i] <= item
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (first[mid] <= item) lo = mid; else hi = mid - 1;
+  // the last instance with first[i] <= item, 64 at a time: a bisection's reads
+  // wait for one another
+  int lo = -1;
+  for (int i = 0; i < n_active; i += 64) {
+    const int k = i + (int(threadIdx.x) & 63);
+    lo += __popcll(__ballot(k < n_active && first[min(k, n_active - 1)] <= item));
   }
   lo = __builtin_amdgcn_readfirstlane(lo);
   const WindowEntryG& e = reinterpret_cast<const WindowEntryG*>(table)[lo];
@@ -589,13 +607,15 @@ window_batch_kernel(const WindowEntry* __restrict__ table, const int* __restrict
   const C* const dec = (const C*)(gptr<const C>)e.decay;
   const cptr<C> cf = (cptr<C>)(gptr<const C>)e.coef;
   const cptr<int> tab = (cptr<int>)e.tab;
-  const int nm = e.nm, it = item - first[lo];
+  const int nm = e.nm, it = item - ((cptr<int>)first)[lo];
+  const int grp = divide(it, a.o.per), within = it - grp * (a.o.gsize * a.o.nchunks);
+  const int chunk = divide(within, a.o.by_gsize), tl = within - chunk * a.o.gsize;
   if (NMAX == 2 || nm == 2)
-    window_tile<T, 2, P, G, S>(u, dec, cf, tab, a, it);
+    window_tile<T, 2, P, G, S>(u, dec, cf, tab, a, grp, chunk, tl, 0);
   else if (NMAX == 3 || nm == 3)
-    window_tile<T, NMAX < 3 ? 2 : 3, P, G, S>(u, dec, cf, tab, a, it);
+    window_tile<T, NMAX < 3 ? 2 : 3, P, G, S>(u, dec, cf, tab, a, grp, chunk, tl, 0);
   else
-    window_tile<T, NMAX < 4 ? 2 : 4, P, G, S>(u, dec, cf, tab, a, it);
+    window_tile<T, NMAX < 4 ? 2 : 4, P, G, S>(u, dec, cf, tab, a, grp, chunk, tl, 0);
 }
 
 // 2^s / d rounded up, with s so large (2^31 d at least) that the error, below
@@ -608,6 +628,8 @@ Divisor divisor(int d) {
   r.m = uint32_t((uint64_t(1) << r.s) / uint32_t(d) + 1);
   return r;
 }
+
+int window_groups(const WindowGrid& g) { return std::max(1, (g.ntx * g.nty + kGroup / 2) / kGroup); }
 
 // The logarithm of a power of two, -1 of another number.
 int log2_of(int n) {
@@ -655,12 +677,13 @@ hipError_t launch_t(int storage, const WindowArgs& w, hipStream_t stream) {
   a.top_shift = w.top_shift;
   a.tau = C(w.tau);
   if (a.lbw < 0 || a.threads < 64 || a.threads > kMaxThreads<T>) return hipErrorInvalidValue;
-  const int64_t blocks = int64_t(blocks1) * a.nseg;
-  if (blocks < 1 || blocks >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+  const int groups = window_groups(g);
+  if (blocks1 < 1 || g.nchunks > 65535 || groups > 65535) return hipErrorInvalidValue;
+  const dim3 blocks(unsigned(a.o.gsize), unsigned(g.nchunks), unsigned(a.nseg > 1 ? a.nseg : groups));
   T* u = static_cast<T*>(w.u);
   const C *d = static_cast<const C*>(w.decay), *cf = static_cast<const C*>(w.coef);
   auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(unsigned(blocks)), dim3(a.threads), 0, stream, u, d, cf, w.tab, a);
+    hipLaunchKernelGGL(kernel, blocks, dim3(a.threads), 0, stream, u, d, cf, w.tab, a);
     return hipGetLastError();
   };
   return by_flags(w.parity, w.general, w.streaming, [&](auto p, auto g, auto s) {
@@ -737,9 +760,12 @@ WindowOrder window_order(const WindowGrid& g, int strip) {
   o.nty = g.nty;
   o.nchunks = g.nchunks;
   o.strip = strip;
-  const int ntiles = g.ntx * g.nty, tail = ntiles % kGroup;
-  o.per = divisor(kGroup * g.nchunks);
-  o.tail = divisor(tail);
+  // groups of equal size, in whole turns of the XCDs
+  const int ntiles = g.ntx * g.nty, groups = window_groups(g), per = (ntiles + groups - 1) / groups;
+  o.gsize = groups > 1 ? (per + kXcds - 1) / kXcds * kXcds : ntiles;
+  o.items = groups * o.gsize * g.nchunks;
+  o.per = divisor(o.gsize * g.nchunks);
+  o.by_gsize = divisor(o.gsize);
   const int w = strip >= 2 ? strip : strip <= -2 ? -strip : 1;
   const int across = strip <= -2 ? g.nty : g.ntx, along = strip <= -2 ? g.ntx : g.nty;
   o.band = divisor(int(std::min<int64_t>(int64_t(w) * across, 0x7FFFFFFF)));
