@@ -1884,6 +1884,7 @@ struct BatchPlan {
   size_t tab0 = 0;           // first table entry of the plan
   size_t first0 = 0;         // first prefix value of the plan in the table's int array
   bool general = false;      // register-window sweeps: an instance needs the general kernel
+  int64_t max_stride = 0;    // register-window sweeps: the largest plane stride
   int nm = 2;                // register-window sweeps: the widest m range's
 };
 }  // namespace detail
@@ -2101,6 +2102,7 @@ int batch_table(starmap_batch* b, const std::vector<int>& sweeps, bool zero_tau)
         w.N = s->N;
         w.nm = window_nm(s->N, s->chunk_width);
         g.nm = std::max(g.nm, w.nm);
+        g.max_stride = std::max(g.max_stride, s->plane_stride);
         const WindowGrid wg = window_grid(s->storage, s->nx, s->ny, s->px, s->py, ts.tx, ts.ty, s->N, w.nm);
         w.order = window_order(wg, s->tile_strip);
         w.planes[0] = s->win_planes[0];
@@ -2198,7 +2200,7 @@ int launch_plan(starmap_batch* b, const BatchPlan& g, int na, int j, hipStream_t
   if (sweep_in_registers(b->storage, g.variant)) {
     const TileShape ts = sweep_variant(b->storage, g.variant);
     const WindowEntry* tab = reinterpret_cast<const WindowEntry*>(base + batch_window_offset(count)) + g.tab0;
-    HIP_TRY(launch_window_batch(b->storage, tab, first, na, g.first[na], j, ts.tx, ts.ty, g.nm, g.general, sweep_streams(b->state_bytes), stream));
+    HIP_TRY(launch_window_batch(b->storage, tab, first, na, g.first[na], j, ts.tx, ts.ty, g.nm, g.max_stride, g.general, sweep_streams(b->state_bytes), stream));
   } else {
     const BatchEntry* tab = reinterpret_cast<const BatchEntry*>(base) + g.tab0;
     HIP_TRY(launch_sweep_batch(g.variant, tab, first, na, g.first[na], j, g.slots, stream));

@@ -78,6 +78,10 @@ constexpr int kPoints = sizeof(T) == 2 ? 2 : 1;
 template <typename T>
 constexpr bool kOverlap = sizeof(T) == 8;
 
+// With single points of four bytes and rows of whole waves (EDGE) the x neighbours
+// are the values of the next lanes too, but the tiles do not overlap: one load
+// per order brings the neighbours of the wave's row end, lane by lane a plane.
+
 // A thread's V stored values of a row segment as one memory access.
 template <typename T, int V>
 using Word = std::conditional_t<sizeof(T) * V == 8, u32x2, std::conditional_t<sizeof(T) * V == 4, uint32_t, uint16_t>>;
@@ -122,17 +126,18 @@ __device__ __forceinline__ Word<T, V> word(const typename ComputeOf<T>::type (&v
 }
 
 // The value of the lane before (BEFORE) or after this one, in the wave's first
-// or last lane its own; every lane of the wave must take part.
+// or last lane `end`; every lane of the wave must take part.
 template <bool BEFORE>
-__device__ __forceinline__ float lane_near(float v) {
-  const int w = int(__float_as_uint(v));
-  return __uint_as_float(uint32_t(__builtin_amdgcn_update_dpp(w, w, BEFORE ? 0x138 : 0x130, 0xF, 0xF, false)));
+__device__ __forceinline__ float lane_near(float v, float end) {
+  return __uint_as_float(uint32_t(__builtin_amdgcn_update_dpp(int(__float_as_uint(end)), int(__float_as_uint(v)),
+                                                              BEFORE ? 0x138 : 0x130, 0xF, 0xF, false)));
 }
 template <bool BEFORE>
-__device__ __forceinline__ double lane_near(double v) {
-  const u32x2 w = __builtin_bit_cast(u32x2, v);
-  return __builtin_bit_cast(double, u32x2{__float_as_uint(lane_near<BEFORE>(__uint_as_float(w.x))),
-                                          __float_as_uint(lane_near<BEFORE>(__uint_as_float(w.y)))});
+__device__ __forceinline__ double lane_near(double v, double end) {
+  const u32x2 w = __builtin_bit_cast(u32x2, v), e = __builtin_bit_cast(u32x2, end);
+  return __builtin_bit_cast(
+      double, u32x2{__float_as_uint(lane_near<BEFORE>(__uint_as_float(w.x), __uint_as_float(e.x))),
+                    __float_as_uint(lane_near<BEFORE>(__uint_as_float(w.y), __uint_as_float(e.y)))});
 }
 
 // Scalars of one sweep.
@@ -181,7 +186,7 @@ __device__ __forceinline__ int2 tile_at(int t, const WindowOrder& o) {
 constexpr int kGroup = 512;
 constexpr int kXcds = 8;
 
-template <typename T, int NM, int P, bool G, bool S>
+template <typename T, int NM, int P, bool G, bool S, bool EDGE>
 __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename ComputeOf<T>::type* __restrict__ decay,
                                             cptr<typename ComputeOf<T>::type> coef, cptr<int> tab,
                                             const WindowScalars<typename ComputeOf<T>::type>& a, int grp, int chunk,
@@ -189,6 +194,8 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
   using C = typename ComputeOf<T>::type;
   constexpr int V = kPoints<T>;
   static_assert(V <= 2, "a pair at most");
+  static_assert(!EDGE || (V == 1 && sizeof(T) == 4), "single points of four bytes");
+  constexpr bool SHIFT = kOverlap<T> || EDGE;  // every x neighbour by lane shift
   using W = Word<T, V>;
   using W1 = Word<T, 1>;
   typedef C C8 __attribute__((ext_vector_type(8)));
@@ -234,6 +241,10 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
     in = Y < rows && X < cols && (q > 0 || (!lead && X == 0)) && (q < last || (!a.px && X == a.nx)) &&
          (x0 == 0 || x0 < cols - (a.px ? 0 : 2 - lead));  // (a piece that is one too many)
     Y = min(Y, rows - 1);
+  } else if constexpr (EDGE) {
+    X = txy.x * bw + col;
+    in = Y < rows && X < cols;
+    Y = min(Y, rows - 1);
   } else {
     // lanes past the tile or the grid stand at the origin and store nothing
     X = (txy.x * bw + col) * V;
@@ -259,7 +270,7 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
   const int xhi = a.px ? (xq >= a.nx ? xq - a.nx : xq) : min(xq, a.nx);
   // columns that the lane loads of node and cell planes
   const int wrapped = X < 0 ? X + a.nx : X >= a.nx ? X - a.nx : X;
-  const int xn = !kOverlap<T> ? X : a.px ? min(wrapped, a.nx - 1) : max(min(X, a.nx), 0);
+  const int xn = !SHIFT ? X : a.px ? min(wrapped, a.nx - 1) : max(min(X, a.nx), 0);
   const int xc = V > 1 ? X : min(xn, a.nx - 1);
   const int xcR = P ? xc : xn, xcI = P ? xn : xc;
   // The x neighbour is a value of the next lane (no load: P_39 1000^2 BF16 587
@@ -277,6 +288,20 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
   const uint32_t nI = (P ? endH : endL) ? (rowI + (P ? xhi : xlo)) * TS + pbytes : kOutside;
   const uint32_t go = uint32_t(Y * a.pitch + xn);
   const uint32_t sR = okR ? go * TS : kOutside, sI = okI ? go * TS + pbytes : kOutside;
+
+  // EDGE: lane i < 2 NB reads the neighbour of the wave's row end in plane i & 1
+  // (R or I) of pair i / 2: the cell before the first lane's, the node after the
+  // last one's (offset from the order's first plane in memory, and index m)
+  uint32_t eoff = kOutside;
+  int em = 0;
+  if constexpr (EDGE) {
+    const int first = X - lane, after = first + 64, z = lane & 1, b = lane >> 1;
+    const int lo = first > 0 ? first - 1 : (a.px ? a.nx - 1 : 0);
+    const int hi = a.px ? min(after >= a.nx ? after - a.nx : after, a.nx - 1) : min(after, a.nx);
+    em = m0 + P - 1 + 2 * b;
+    if (b < NB && em >= z)
+      eoff = uint32_t(2 * (NM - b) + z) * pbytes + ((z ? rowI : rowR) + (z == P ? hi : min(lo, a.nx - 1))) * TS;
+  }
 
   // address of plane k, and the descriptor of a plane at an address
   auto plane_addr = [&](int k) { return uint64_t(U) + uint64_t(int64_t(k) * int64_t(pbytes)); };
@@ -303,21 +328,28 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
   auto load_planes = [&](int b, uint64_t p, int lm) {
     const auto r = plane(p, recs(b ? pair : P ? pair0 : none0, m0 + P - 1 + 2 * b, lm));
     rR[b].c = buf_load<W>(r, cR);
-    if constexpr (!kOverlap<T>) rR[b].n = buf_load<W1>(r, nR);
+    if constexpr (!SHIFT) rR[b].n = buf_load<W1>(r, nR);
     rR[b].b = buf_load<W>(r, bR);
     rI[b].c = buf_load<W>(r, cI);
-    if constexpr (!kOverlap<T>) rI[b].n = buf_load<W1>(r, nI);
+    if constexpr (!SHIFT) rI[b].n = buf_load<W1>(r, nI);
     rI[b].b = buf_load<W>(r, bI);
+  };
+  // the row ends' neighbours in the planes of an order whose first one is at p
+  auto load_edge = [&](uint64_t p, int lm) {
+    return EDGE ? buf_load<uint32_t>(plane(p, uint32_t(NB) * pair), em <= lm ? eoff : kOutside) : 0u;
   };
   // differences of a plane: along x centre - lower (cells) or upper - centre
   // (nodes), along y likewise (R planes are cells, I planes nodes)
-  auto diff = [&](const In& w, Diff& d, bool cell, bool isR) {
+  auto diff = [&](const In& w, Diff& d, bool cell, bool isR, uint32_t edge, int b) {
     C v[V];
 #pragma unroll
     for (int e = 0; e < V; ++e) v[e] = value<T, V>(w.c, e);
     C nb = value<T, 1>(w.n, 0);
-    if constexpr (kOverlap<T> || V > 1) {
-      const C near = cell ? lane_near<true>(v[V - 1]) : lane_near<false>(v[0]);
+    if constexpr (EDGE) {
+      const C end = __uint_as_float(uint32_t(__builtin_amdgcn_readlane(int(edge), 2 * b + (isR ? 0 : 1))));
+      nb = cell ? lane_near<true>(v[0], end) : lane_near<false>(v[0], end);
+    } else if constexpr (kOverlap<T> || V > 1) {
+      const C near = cell ? lane_near<true>(v[V - 1], v[V - 1]) : lane_near<false>(v[0], v[0]);
       nb = kOverlap<T> || !(cell ? endL : endH) ? near : nb;
     }
 #pragma unroll
@@ -391,11 +423,13 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
   uint64_t ps = plane_addr(k0), pn = ps - uint64_t(uint32_t(2 * l + 1)) * pbytes,
            pl = pn - uint64_t(uint32_t(l)) * pbytes;
   int64_t dn = int64_t(2 * l - 3) * int64_t(pbytes);
+  uint32_t rE = 0;      // EDGE: row ends of the planes in rR and rI
   Diff hR[NB], hI[NB];  // differences of input order l + 1
   {
     const int kh = k0 + l + 1 + (l + 1 == a.N ? a.top_shift : 0);
     load_decay(l);
     uint64_t p = plane_addr(kh);
+    const uint32_t pE = load_edge(p, l < a.N ? l + 1 : -1);
 #pragma unroll
     for (int b = NM; b >= 0; --b) {
       load_planes(b, p, l < a.N ? l + 1 : -1);
@@ -408,6 +442,7 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
       pI[b] = rI[b];
     }
     p = ps - uint64_t(uint32_t(l + 2)) * pbytes;
+    rE = load_edge(p, l - 1);
 #pragma unroll
     for (int b = NM; b >= 0; --b) {
       load_planes(b, p, l - 1);
@@ -422,8 +457,8 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
     apply_decay();  // (while the planes arrive)
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
-      diff(pR[b], hR[b], P == 1, true);
-      diff(pI[b], hI[b], P == 0, false);
+      diff(pR[b], hR[b], P == 1, true, pE, b);
+      diff(pI[b], hI[b], P == 0, false, pE, b);
     }
   }
   // the zeroth moment, the last row of the even sweep's first range, has a
@@ -450,6 +485,7 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
     if (redo) load_decay(l - 2);
     const int kn = k0 - (2 * l + 1);
     uint64_t as = ps, an = pn, al = pl;
+    const uint32_t nE = load_edge(al, lm);
     // the rows' coefficients (the table has eight rows of padding on both sides)
     const cptr<C8> cf = reinterpret_cast<cptr<C8>>(cat(coef, uint32_t(k0 + 8) * uint32_t(8 * sizeof(C))));
     C8 cr = cf[0], ci = cf[1];
@@ -457,8 +493,8 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
 #pragma unroll
     for (int b = NM; b >= 0; --b) {
       Diff dR, dI;
-      diff(rR[b], dR, P == 1, true);
-      diff(rI[b], dI, P == 0, false);
+      diff(rR[b], dR, P == 1, true, rE, b);
+      diff(rI[b], dI, P == 0, false, rE, b);
       // (the differences before the loads that overwrite their sources)
 #pragma unroll
       for (int e = 0; e < V; ++e) asm volatile("" : "+v"(dR.x[e]), "+v"(dR.y[e]), "+v"(dI.x[e]), "+v"(dI.y[e]));
@@ -512,6 +548,7 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
     }
     hR[0] = lR;
     hI[0] = lI;
+    rE = nE;
     k0 = kn;
     ps = pn;
     pn -= uint64_t(dn);
@@ -538,14 +575,14 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
 template <typename T>
 constexpr int kMaxThreads = sizeof(T) == 8 ? 256 : 512;
 
-template <typename T, int NM, int P, bool G, bool S>
+template <typename T, int NM, int P, bool G, bool S, bool EDGE>
 __global__ void __launch_bounds__(kMaxThreads<T>)
 window_kernel(T* __restrict__ U, const typename ComputeOf<T>::type* __restrict__ decay,
               const typename ComputeOf<T>::type* __restrict__ coef, const int* __restrict__ tab,
               const WindowScalars<typename ComputeOf<T>::type> a) {
   using C = typename ComputeOf<T>::type;
   // (a launch of several runs of orders has one group)
-  window_tile<T, NM, P, G, S>(U, decay, (cptr<C>)coef, (cptr<int>)tab, a, a.nseg > 1 ? 0 : int(blockIdx.z),
+  window_tile<T, NM, P, G, S, EDGE>(U, decay, (cptr<C>)coef, (cptr<int>)tab, a, a.nseg > 1 ? 0 : int(blockIdx.z),
                               int(blockIdx.y), int(blockIdx.x), int(blockIdx.z));
 }
 
@@ -571,7 +608,7 @@ static_assert(sizeof(WindowEntryG) == sizeof(WindowEntry), "device view of Windo
 // batch of narrow ones needs fewer registers: 24 media of P_3 .. P_9 on 64^2 ..
 // 256^2 cells, FP32, 88 -> 75: with the shorter way to the first load 28 -> 26
 // us per sweep).
-template <typename T, int NMAX, int P, bool G, bool S>
+template <typename T, int NMAX, int P, bool G, bool S, bool EDGE>
 __global__ void __launch_bounds__(kMaxThreads<T>)
 window_batch_kernel(const WindowEntry* __restrict__ table, const int* __restrict__ first, const int n_active,
                     const int j, const int lbw) {
@@ -611,11 +648,11 @@ window_batch_kernel(const WindowEntry* __restrict__ table, const int* __restrict
   const int grp = divide(it, a.o.per), within = it - grp * (a.o.gsize * a.o.nchunks);
   const int chunk = divide(within, a.o.by_gsize), tl = within - chunk * a.o.gsize;
   if (NMAX == 2 || nm == 2)
-    window_tile<T, 2, P, G, S>(u, dec, cf, tab, a, grp, chunk, tl, 0);
+    window_tile<T, 2, P, G, S, EDGE>(u, dec, cf, tab, a, grp, chunk, tl, 0);
   else if (NMAX == 3 || nm == 3)
-    window_tile<T, NMAX < 3 ? 2 : 3, P, G, S>(u, dec, cf, tab, a, grp, chunk, tl, 0);
+    window_tile<T, NMAX < 3 ? 2 : 3, P, G, S, EDGE>(u, dec, cf, tab, a, grp, chunk, tl, 0);
   else
-    window_tile<T, NMAX < 4 ? 2 : 4, P, G, S>(u, dec, cf, tab, a, grp, chunk, tl, 0);
+    window_tile<T, NMAX < 4 ? 2 : 4, P, G, S, EDGE>(u, dec, cf, tab, a, grp, chunk, tl, 0);
 }
 
 // 2^s / d rounded up, with s so large (2^31 d at least) that the error, below
@@ -638,12 +675,29 @@ int log2_of(int n) {
   return n >= 1 && (1 << l) == n ? l : -1;
 }
 
-// f with the parity and the two flags as types.
-template <typename F>
-hipError_t by_flags(bool parity, bool general, bool streaming, F f) {
+// Whether a sweep's x neighbours at row ends come by one load per order: rows of
+// whole waves, an order's planes of a range within a descriptor's reach, and two
+// waves for each of the chip's 1024 SIMDs, so that the address unit is what they
+// wait for (24 media of P_3 .. P_9 34.7 -> 33.1 us per sweep, P_9 317 x 203 7.16
+// -> 7.0, P_31 256^2 40.6 -> 40.0; the 780 waves of a P_7 128^2 run with changing
+// media, which wait for their loads, 28.7 -> 29.5 per step).
+template <typename T>
+bool by_edge(int tx, int nm, int64_t plane_stride, int64_t threads) {
+  return sizeof(T) == 4 && tx >= 64 && threads >= 2048 * 64 &&
+         uint64_t(nm + 1) * 2 * uint64_t(plane_stride) * sizeof(T) < kOutside;
+}
+
+// f with the parity and the flags as types (edge: with four-byte values only).
+template <typename T, typename F>
+hipError_t by_flags(bool parity, bool general, bool streaming, bool edge, F f) {
   using No = std::integral_constant<int, 0>;
   using Yes = std::integral_constant<int, 1>;
-  auto with = [&](auto p, auto g) { return streaming ? f(p, g, Yes{}) : f(p, g, No{}); };
+  auto at = [&](auto p, auto g, auto s) {
+    if constexpr (sizeof(T) == 4)
+      if (edge) return f(p, g, s, Yes{});
+    return f(p, g, s, No{});
+  };
+  auto with = [&](auto p, auto g) { return streaming ? at(p, g, Yes{}) : at(p, g, No{}); };
   if (parity) return general ? with(Yes{}, Yes{}) : with(Yes{}, No{});
   return general ? with(No{}, Yes{}) : with(No{}, No{});
 }
@@ -686,9 +740,11 @@ hipError_t launch_t(int storage, const WindowArgs& w, hipStream_t stream) {
     hipLaunchKernelGGL(kernel, blocks, dim3(a.threads), 0, stream, u, d, cf, w.tab, a);
     return hipGetLastError();
   };
-  return by_flags(w.parity, w.general, w.streaming, [&](auto p, auto g, auto s) {
-    return launch(&window_kernel<T, NM, decltype(p)::value, decltype(g)::value, decltype(s)::value>);
-  });
+  return by_flags<T>(w.parity, w.general, w.streaming, by_edge<T>(w.tx, NM, w.plane_stride, int64_t(blocks1) * a.threads),
+                     [&](auto p, auto g, auto s, auto e) {
+                       return launch(&window_kernel<T, NM, decltype(p)::value, decltype(g)::value, decltype(s)::value,
+                                                    decltype(e)::value>);
+                     });
 }
 
 template <typename T>
@@ -703,16 +759,18 @@ hipError_t launch_nm(int storage, const WindowArgs& w, hipStream_t stream) {
 
 template <typename T, int NMAX>
 hipError_t launch_batch_t(const WindowEntry* table, const int* first, int n_active, int items, int j, int tx, int ty,
-                          bool general, bool streaming, hipStream_t stream) {
+                          int64_t max_stride, bool general, bool streaming, hipStream_t stream) {
   const int lbw = log2_of(tx / kPoints<T>), threads = tx / kPoints<T> * ty;
   if (lbw < 0 || threads < 64 || threads > kMaxThreads<T>) return hipErrorInvalidValue;
   auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(items), dim3(threads), 0, stream, table, first, n_active, j, lbw);
     return hipGetLastError();
   };
-  return by_flags(!(j & 1), general, streaming, [&](auto p, auto g, auto s) {
-    return launch(&window_batch_kernel<T, NMAX, decltype(p)::value, decltype(g)::value, decltype(s)::value>);
-  });
+  return by_flags<T>(!(j & 1), general, streaming, by_edge<T>(tx, NMAX, max_stride, int64_t(items) * threads),
+                     [&](auto p, auto g, auto s, auto e) {
+                       return launch(&window_batch_kernel<T, NMAX, decltype(p)::value, decltype(g)::value,
+                                                          decltype(s)::value, decltype(e)::value>);
+                     });
 }
 
 template <typename T, typename... A>
@@ -784,12 +842,13 @@ hipError_t launch_window(int storage, const WindowArgs& w, hipStream_t stream) {
 }
 
 hipError_t launch_window_batch(int storage, const WindowEntry* table, const int* first, int n_active, int items, int j,
-                               int tx, int ty, int nm, bool general, bool streaming, hipStream_t stream) {
+                               int tx, int ty, int nm, int64_t max_stride, bool general, bool streaming,
+                               hipStream_t stream) {
   if (n_active < 1 || items < 1) return hipErrorInvalidValue;
   switch (storage) {
-    case STORE_FP64: return launch_batch_nm<double>(nm, table, first, n_active, items, j, tx, ty, general, streaming, stream);
-    case STORE_FP32: return launch_batch_nm<float>(nm, table, first, n_active, items, j, tx, ty, general, streaming, stream);
-    case STORE_BF16: return launch_batch_nm<bf16>(nm, table, first, n_active, items, j, tx, ty, general, streaming, stream);
+    case STORE_FP64: return launch_batch_nm<double>(nm, table, first, n_active, items, j, tx, ty, max_stride, general, streaming, stream);
+    case STORE_FP32: return launch_batch_nm<float>(nm, table, first, n_active, items, j, tx, ty, max_stride, general, streaming, stream);
+    case STORE_BF16: return launch_batch_nm<bf16>(nm, table, first, n_active, items, j, tx, ty, max_stride, general, streaming, stream);
   }
   return hipErrorInvalidValue;
 }
