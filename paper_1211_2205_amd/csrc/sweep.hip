@@ -641,10 +641,13 @@ bool sweep_streams(double state_bytes) { return state_bytes > kCache; }
 //     chip (P_39 200^2 118, registers 108).
 // FP32, BF16.  Large states on wide tiles, which read the fewest lines twice,
 // where the grid fills them (P_39 1000^2 FP32: 128 x 2 1014, 64 x 4 1028), else
-// 64 wide (P_31 447^2, 448 columns: 64 x 8 116, 128 x 2 126).  States in the
-// cache: FP32 64 x 2 (P_7 512^2 15.6, 64 x 4 17.2), from P_8 on 64 x 4
-// (P_9 317 x 203 7.8 and 8.3, P_31 256^2 40 and 42); BF16 128 x 4 (P_31 345^2
-// 42, 64 x 4 51).
+// 64 wide (P_31 447^2, 448 columns: 64 x 8 116, 128 x 2 123).  FP32 states in the
+// cache: 64 x 4 (P_9 317 x 203 7.0, 64 x 2 7.2; P_5 256^2 5.2 and 5.4; P_31
+// 256^2 41 and 44), 64 x 2 where those are too few workgroups (P_3 150^2 3.7 and
+// 3.9, P_9 150^2 5.6 and 6.0) and for few orders on large grids (P_3 1000^2 14.9
+// and 15.6).  BF16: 128 x 4 (P_39 250^2 37, 64 x 2 40; P_7 512^2 13.0 and 13.6),
+// small ones 64 x 2 (P_9 150^2 6.6, 128 x 4 7.2; P_21 300^2 19.8 and 20.4; P_31
+// 256^2 29 and 31).
 int sweep_default_variant(int storage, int N, int cols, int rows, double state_bytes) {
   const double points = double(cols) * rows;
   const bool cached = !sweep_streams(state_bytes);
@@ -655,24 +658,26 @@ int sweep_default_variant(int storage, int N, int cols, int rows, double state_b
   const int wide = storage == STORE_FP32 ? 128 : 256;
   const int padded = (cols + wide - 1) / wide * wide;
   const bool fills = padded - cols <= cols / 20;
-  if (storage == STORE_FP32) return cached ? (N < 8 ? 8 : 0) : fills ? 1 : 5;
-  return !cached && fills ? 6 : 4;
+  if (storage == STORE_BF16) return cached ? (points < 1.2e5 && state_bytes < 8.5e7 ? 8 : 4) : fills ? 6 : 4;
+  if (!cached) return fills ? 1 : 5;
+  return points < (N < 8 ? 5.0e4 : 3.0e4) || (N < 8 && points > 6.0e5) ? 8 : 0;
 }
 
-// m ranges.  One range where it holds every index (P_5, LDS 400^2: 14.5, at
-// four 19.7; P_7, LDS 1000^2: eight 89, four 121).  From P_16 on (with the LDS
-// window from P_13) ranges of six (LDS P_39 1000^2: 2040, eight 2200, four
-// 2110), below it four: more workgroups, and no idle rows in P_15 (FP32 447^2
-// 30, six 31); of grids that fill the chip anyway, six (P_9 1000^2 FP32 57,
-// four 61).  Register windows of eight-byte values: four, for P_4 and P_5 six,
-// one range, once the workgroups fill the chip (P_5 150^2 5.3, six 5.7; 300^2
-// 9.7 and 8.7; 700^2 36 and 32).
+// m ranges.  LDS window: one range where it holds every index (P_5 400^2 15.3,
+// at four 20.7; P_7 1000^2 89, at four 122), from P_13 on six (P_39 500^2 557,
+// eight 618, four 580), else four.  Registers: four, more workgroups, while the
+// chip is not full (P_21 150^2 FP32 12, six 15; P_31 128^2 17 and 21.5; P_5 150^2
+// 4.3 and 4.7; BF16 P_31 256^2 29 and 30), and no idle rows in P_15 (FP32 447^2
+// 30.0, six 30.9); of grids that fill it six, which read fewer planes twice
+// (FP32 P_21 300^2 27.6, four 28.2; P_9 1000^2 57.0 and 57.4), which is one
+// range of P_4 and P_5 (FP32 400^2 7.3 and 7.7, FP64 300^2 8.7 and 9.7).
 int sweep_default_width(int storage, int variant, int N, int cols, int rows) {
-  const bool registers = sweep_in_registers(storage, variant);
-  if (storage == STORE_FP64 && registers) return (N == 4 || N == 5) && double(cols) * rows > 4.0e4 ? 6 : 4;
-  if (N == 4 || N == 5) return 6;
-  if (!registers) return N == 6 || N == 7 ? 8 : N >= 13 ? 6 : 4;
-  return N >= 16 || (N >= 8 && double(cols) * rows > 5.0e5) ? 6 : 4;
+  const double points = double(cols) * rows;
+  if (!sweep_in_registers(storage, variant)) return N == 4 || N == 5 ? 6 : N == 6 || N == 7 ? 8 : N >= 13 ? 6 : 4;
+  if (storage == STORE_FP64) return (N == 4 || N == 5) && points > 4.0e4 ? 6 : 4;
+  if (N == 4 || N == 5) return points > (storage == STORE_FP32 ? 1.2e5 : 2.0e5) ? 6 : 4;
+  if (N >= 16) return (storage == STORE_FP32 ? points > 4.0e4 : variant != 8) ? 6 : 4;
+  return N >= 8 && points > 5.0e5 ? 6 : 4;
 }
 
 size_t sweep_lds_bytes(int v, int slots, int storage) {
