@@ -239,8 +239,9 @@ void plan_separable(starmap_solver* s) {
     const int o = int(first.size()) - 1;
     first.push_back(int32_t(entries.size() / 3));
     s->comb_cst.push_back(cst);
-    lists[which].insert(lists[which].end(), {o, dst});
-    if (dynamic) lists[which + 1].insert(lists[which + 1].end(), {o, dst});
+    const int e0 = first[size_t(o)], n = first.back() - e0;
+    lists[which].insert(lists[which].end(), {dst, e0, n, o});
+    if (dynamic) lists[which + 1].insert(lists[which + 1].end(), {dst, e0, n, o});
     dynamic = false;
   };
   // decay: sigma_a (zeroth order), sigma_a + sigma_s0 - sigma_sl (order l >= 1)
@@ -262,13 +263,11 @@ void plan_separable(starmap_solver* s) {
   }
   s->nbasis = int(s->basis.size());
   auto& tab = s->comb_tab;
-  s->tab_first = 0;
-  tab.insert(tab.end(), first.begin(), first.end());
   s->tab_entries = int(tab.size());
   tab.insert(tab.end(), entries.begin(), entries.end());
   for (int w = 0; w < 4; ++w) {
     s->tab_list[w] = int(tab.size());
-    s->nlist[w] = int(lists[w].size() / 2);
+    s->nlist[w] = int(lists[w].size() / 4);
     tab.insert(tab.end(), lists[w].begin(), lists[w].end());
   }
 }
@@ -714,23 +713,17 @@ int combine_materials(starmap_solver* s, double t_eval) {
   }
   const int32_t* tab = reinterpret_cast<const int32_t*>(dptr(s, s->off_comb));
   c.basis = dptr(s, s->off_basis);
-  c.first = tab + s->tab_first;
   c.entries = tab + s->tab_entries;
   c.cst = reinterpret_cast<const double*>(dptr(s, s->off_comb + align256(s->comb_tab.size() * 4)));
   c.plane_stride = s->plane_stride;
   const int w = s->static_done ? 1 : 0;
-  if (s->nlist[w]) {  // decay planes, compute type
-    c.out = dptr(s, s->off_decay);
-    c.list = tab + s->tab_list[w];
-    c.nlist = s->nlist[w];
-    HIP_TRY(launch_combine(s->storage, true, c, s->stream));
+  c.decay = dptr(s, s->off_decay);
+  c.sources = dptr(s, s->off_src);
+  for (int i = 0; i < 2; ++i) {
+    c.list[i] = tab + s->tab_list[2 * i + w];
+    c.nlist[i] = s->nlist[2 * i + w];
   }
-  if (s->nlist[2 + w]) {  // source planes, storage type
-    c.out = dptr(s, s->off_src);
-    c.list = tab + s->tab_list[2 + w];
-    c.nlist = s->nlist[2 + w];
-    HIP_TRY(launch_combine(s->storage, false, c, s->stream));
-  }
+  if (c.nlist[0] + c.nlist[1]) HIP_TRY(launch_combine(s->storage, c, s->stream));
   s->static_done = true;
   s->materials_ready = true;
   return STARMAP_OK;

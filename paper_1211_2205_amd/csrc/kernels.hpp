@@ -142,24 +142,23 @@ hipError_t prepare_sweep(int variant, int slots);
 hipError_t launch_sweep_batch(int variant, const BatchEntry* table, const int* first, int n_active, int items, int j,
                               int slots, hipStream_t stream);
 
-// Linear combination of basis planes (compute type) into decay planes
-// (compute type) or source planes (storage type).  For each pair (o, d) of
-// list: plane d of out = cst[o] + sum over entries e in [first[o], first[o+1])
-// of sign_e * factor_e * basis[b_e], where entries holds (b_e, term_e, sign_e)
+// Linear combinations of basis planes (compute type) into decay planes
+// (compute type) and source planes (storage type).  For each record (d, e0, n,
+// o) of a list: plane d = cst[o] + sum over the n entries e from e0 on of
+// sign_e * factor_e * basis[b_e], where entries holds (b_e, term_e, sign_e)
 // and factor_e = a[term_e] (or 1 when term_e < 0).
 constexpr int COMBINE_MAX_TERMS = 32;
 struct CombineArgs {
   const void* basis;
-  const int* first;
   const int* entries;
-  const double* cst;  // per output: constant added to the sum
-  const int* list;
-  void* out;
+  const double* cst;   // per output: constant added to the sum
+  const int* list[2];  // decay and source outputs: destination plane, first entry, entries, output
+  void *decay, *sources;  // compute type, storage type
   int64_t plane_stride;
-  int nlist;
+  int nlist[2];
   double a[COMBINE_MAX_TERMS];
 };
-hipError_t launch_combine(int storage, bool to_compute_type, const CombineArgs& a, hipStream_t stream);
+hipError_t launch_combine(int storage, const CombineArgs& a, hipStream_t stream);
 
 // Diffusion step of the D_N model on the order-N moments (j = 0..nplanes-1):
 // tmp[j] = u_k + tau kappa_j (second difference along x * rdx2 + along y *

@@ -152,10 +152,10 @@ struct starmap_solver {
   size_t sample_cap = 0;
 
   // time-separable fields on the device: basis planes (compute type) and an
-  // int32 table: per output (every decay plane, then every source plane) the
-  // first of its entries; per entry (basis plane, time factor or -1, sign);
-  // four lists of (output, destination plane) pairs: all decay outputs, decay
-  // outputs with a time factor, all source outputs, source outputs with one.
+  // int32 table: per entry (basis plane, time factor or -1, sign); four lists of
+  // records (destination plane, first entry, entries, output): all decay
+  // outputs, decay outputs with a time factor, all source outputs, source
+  // outputs with one.
   bool separable = false;
   size_t off_basis = 0, off_comb = 0;
   int nbasis = 0;
@@ -168,7 +168,7 @@ struct starmap_solver {
   std::vector<starmap::detail::FieldTerm> time_terms;
   std::vector<int32_t> comb_tab;
   std::vector<double> comb_cst;  // per output: constant term (filter damping of decay planes)
-  int tab_first = 0, tab_entries = 0, tab_list[4] = {}, nlist[4] = {};
+  int tab_entries = 0, tab_list[4] = {}, nlist[4] = {};
   bool basis_ready = false, static_done = false;
 
   // plane_stride is a multiple of 128 elements, so planes of every element

@@ -123,3 +123,35 @@ def test_separable_errors():
     bad.advance(1)
     with pytest.raises(pa.StarmapError):
         bad.run()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "bf16"])
+@pytest.mark.parametrize("terms", [1, 2, 3, 4, 5, 8, 11])
+def test_combined_planes_of_every_number_of_terms(terms, precision):
+    """Outputs of one to eleven terms (read four at a time, then the rest),
+    against the same fields sampled on the host.  The device sums terms that
+    were rounded to the compute type (FP64; FP32 for the others), the host
+    rounds their FP64 sum: with terms of one sign, below (terms + 1) roundings
+    of the coefficients per step, and no more of the state (dt c < 1 here).
+    BF16 rounds the source planes once more, 2^-9 of them, and the states that
+    differ by that at each of 3 sweeps in 3 steps: 12 x 2^-9."""
+    rng = np.random.default_rng(terms)
+    w, ph = rng.uniform(1, 5, terms), rng.uniform(0, 1, terms)
+    fac = [(lambda t, a=a, b=b: 1.5 + math.sin(a * t + b)) for a, b in zip(w, ph)]
+    geo = [(lambda x, y, a=a, b=b: (1.2 + np.cos(3 * a * x + b) * np.sin(2 * y)) / terms) for a, b in zip(w, ph)]
+    both = list(zip(fac, geo))
+    total = lambda t, x, y: sum(f(t) * g(x, y) for f, g in both)  # noqa: E731
+    prob = wl.Problem(
+        name="terms", N=3, n=(37, 30), ax=(-1.0, 1.0, -1.0, 1.0), bc=(wl.BC_PERIODIC, wl.BC_EXTRAPOLATION), cfl=0.5,
+        t_final=1.0, precision=precision, sigma_a=total, sigma_s0=lambda t, x, y: 0.5 + 0 * x, source={0: total},
+        initial={0: lambda t, x, y: np.exp(-4 * (x * x + y * y))}, time_dependent=True,
+        separable={"absorption": both, "source": {0: both}})
+    out = []
+    for p in (prob, _host_path(prob)):
+        s = pa.Solver.from_problem(p, precision=precision)
+        s.bind_torch()
+        s.advance(3)
+        out.append(s.moments())
+        s.close()
+    eps = {"fp64": 2.0 ** -53, "fp32": 2.0 ** -24, "bf16": 2.0 ** -24}[precision]
+    assert rel_l2(*out) <= 3 * (terms + 1) * eps * 4 + (12 * 2.0 ** -9 if precision == "bf16" else 0.0)
