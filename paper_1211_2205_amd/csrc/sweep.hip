@@ -640,8 +640,10 @@ bool sweep_streams(double state_bytes) { return state_bytes > kCache; }
 //     142; P_7 1000^2 89 and 132), unless the LDS tiles are too few to fill the
 //     chip (P_39 200^2 118, registers 108).
 // FP32, BF16.  Large states on wide tiles, which read the fewest lines twice,
-// where the grid fills them (P_39 1000^2 FP32: 128 x 2 1014, 64 x 4 1028), else
-// 64 wide (P_31 447^2, 448 columns: 64 x 8 116, 128 x 2 123).  FP32 states in the
+// where the grid fills them (P_39 1000^2 FP32: 512 x 1 993, 128 x 2 1012; 500^2
+// 236 and 247), else
+// 64 wide (P_31 447^2, 448 columns: 64 x 8 114, 512 x 1 117, 128 x 2 121), P_8 ..
+// P_15 64 x 4 (P_13 900 x 1000 112, 64 x 8 115).  FP32 states in the
 // cache: 64 x 4 (P_9 317 x 203 7.0, 64 x 2 7.2; P_5 256^2 5.2 and 5.4; P_31
 // 256^2 41 and 44), 64 x 2 where those are too few workgroups (P_3 150^2 3.7 and
 // 3.9, P_9 150^2 5.6 and 6.0) and for few orders on large grids (P_3 1000^2 14.9
@@ -655,11 +657,9 @@ int sweep_default_variant(int storage, int N, int cols, int rows, double state_b
     if (cached) return N <= 2 && points > 1.2e5 ? 7 : 12;
     return points > 6.0e4 ? (N <= 3 ? 7 : 8) : 12;
   }
-  const int wide = storage == STORE_FP32 ? 128 : 256;
-  const int padded = (cols + wide - 1) / wide * wide;
-  const bool fills = padded - cols <= cols / 20;
-  if (storage == STORE_BF16) return cached ? (points < 1.2e5 && state_bytes < 8.5e7 ? 8 : 4) : fills ? 6 : 4;
-  if (!cached) return fills ? 1 : 5;
+  auto fills = [&](int wide) { return (cols + wide - 1) / wide * wide - cols <= cols / 20; };
+  if (storage == STORE_BF16) return cached ? (points < 1.2e5 && state_bytes < 8.5e7 ? 8 : 4) : fills(256) ? 6 : 4;
+  if (!cached) return N >= 8 && N < 16 ? 0 : N >= 16 && fills(512) ? 12 : fills(128) ? 1 : 5;
   return points < (N < 8 ? 5.0e4 : 3.0e4) || (N < 8 && points > 6.0e5) ? 8 : 0;
 }
 
@@ -669,15 +669,18 @@ int sweep_default_variant(int storage, int N, int cols, int rows, double state_b
 // chip is not full (P_21 150^2 FP32 12, six 15; P_31 128^2 17 and 21.5; P_5 150^2
 // 4.3 and 4.7; BF16 P_31 256^2 29 and 30), and no idle rows in P_15 (FP32 447^2
 // 30.0, six 30.9); of grids that fill it six, which read fewer planes twice
-// (FP32 P_21 300^2 27.6, four 28.2; P_9 1000^2 57.0 and 57.4), which is one
-// range of P_4 and P_5 (FP32 400^2 7.3 and 7.7, FP64 300^2 8.7 and 9.7).
+// (FP32 P_21 300^2 27.6, four 28.2), which is one
+// range of P_4 and P_5 (FP32 400^2 7.3 and 7.7, FP64 300^2 8.7 and 9.7); eight
+// for P_8 .. P_15 (FP32 P_15 1000^2 155, six 160; P_9 1800^2 221 and 229) and in
+// 512 x 1 tiles (P_39 1000^2 993, six 998).
 int sweep_default_width(int storage, int variant, int N, int cols, int rows) {
   const double points = double(cols) * rows;
   if (!sweep_in_registers(storage, variant)) return N == 4 || N == 5 ? 6 : N == 6 || N == 7 ? 8 : N >= 13 ? 6 : 4;
   if (storage == STORE_FP64) return (N == 4 || N == 5) && points > 4.0e4 ? 6 : 4;
   if (N == 4 || N == 5) return points > (storage == STORE_FP32 ? 1.2e5 : 2.0e5) ? 6 : 4;
-  if (N >= 16) return (storage == STORE_FP32 ? points > 4.0e4 : variant != 8) ? 6 : 4;
-  return N >= 8 && points > 5.0e5 ? 6 : 4;
+  if (storage == STORE_BF16) return N >= 16 ? (variant == 8 ? 4 : 6) : N >= 8 && points > 5.0e5 ? 6 : 4;
+  if (N >= 16) return variant == 12 ? 8 : points > 4.0e4 ? 6 : 4;
+  return N >= 8 && points > 4.7e5 ? 8 : 4;
 }
 
 size_t sweep_lds_bytes(int v, int slots, int storage) {
