@@ -668,6 +668,27 @@ Divisor divisor(int d) {
 
 int window_groups(const WindowGrid& g) { return std::max(1, (g.ntx * g.nty + kGroup / 2) / kGroup); }
 
+// Runs of orders of a launch: one of few waves is a chain of memory round trips,
+// one per order, so its orders are split into runs that start their own chains
+// (one more window to load each) while the chip has room for them: up to 2048
+// waves, with the many orders of P_16 and up 2400, and two runs where that makes
+// 3300.  Microseconds per sweep without -> with: FP32 P_9 64^2 4.8 -> 4.0, P_7
+// 128^2 4.65 -> 4.46, P_13 100^2 6.2 -> 5.45, P_31 64^2 10.9 -> 8.3, P_31 100^2
+// 14.6 -> 11.7; BF16 P_9 64^2 6.0 -> 4.4, P_31 100^2 15.5 -> 11.8.  Beyond it
+// costs (FP32 P_7 128^2 in three 4.67, P_31 64^2 in three 9.0).  FP64, whose waves
+// load twice the bytes, gains with fewer: P_9 64^2 5.6 -> 5.1, P_39 64^2 19.7 ->
+// 16.5, but P_3 150^2 4.3 -> 4.55, P_7 128^2 5.6 -> 6.4.
+int window_runs(int value_bytes, const WindowGrid& g, int waves_per_tile, int N) {
+  const int waves = g.ntx * g.nty * g.nchunks * waves_per_tile;
+  if (waves < 1 || window_groups(g) > 1) return 1;  // (a launch of several runs has one group)
+  int n;
+  if (value_bytes == 8)
+    n = N >= 16 ? (waves <= 1400 ? 2 : 1) : waves <= 400 ? 1200 / waves : 512 / waves;
+  else
+    n = N >= 16 ? std::max(2400 / waves, waves <= 1650 ? 2 : 1) : 2048 / waves;
+  return std::min(std::max(n, 1), N / 2 + 1);
+}
+
 // The logarithm of a power of two, -1 of another number.
 int log2_of(int n) {
   int l = 0;
@@ -717,14 +738,8 @@ hipError_t launch_t(int storage, const WindowArgs& w, hipStream_t stream) {
   a.threads = bw * w.ty;
   const WindowGrid g = window_grid(storage, w.nx, w.ny, w.px, w.py, w.tx, w.ty, w.N, w.nm);
   a.o = window_order(g, w.strip);
-  // A launch of fewer workgroups than compute units is a chain of memory
-  // round trips, one per order: its orders are split into runs that start
-  // their own chains (one more window to load each).  P_3 100^2 FP64 5.7 ->
-  // 5.2 us per sweep when it was put in; with more workgroups it costs (P_7
-  // 280^2 15.0 -> 16.8).
-  const int blocks1 = g.ntx * g.nty * g.nchunks, orders = w.N / 2 + 1;
-  a.nseg = blocks1 > 0 ? 256 / blocks1 : 1;
-  a.nseg = a.nseg < 1 ? 1 : a.nseg > orders ? orders : a.nseg;
+  const int blocks1 = g.ntx * g.nty * g.nchunks;
+  a.nseg = window_runs(int(sizeof(T)), g, a.threads / 64, w.N);
   a.by_nseg = divisor(a.nseg);
   a.planes = w.planes;
   a.N = w.N;

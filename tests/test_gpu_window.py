@@ -161,3 +161,18 @@ def test_fp64_tiles_that_overlap_by_their_end_lanes(nx, bc):
     for v in WINDOW:
         for k, (a, b) in enumerate(zip(_run(prob, init, v, 4), ref)):
             assert np.array_equal(a, b), (v, k)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "bf16"])
+@pytest.mark.parametrize("N", [1, 2, 4, 9, 15, 16, 24])
+def test_runs_of_orders(N, precision):
+    """Launches of few waves split their orders into runs; each output still
+    takes the same operations, so wider tiles of other run counts, down to one,
+    give the same bits."""
+    prob = _problem(N, (70, 61), (X, P), N % 2 == 0, precision)
+    init = _init(prob)
+    ref = _run(prob, init, 12 if precision == "fp64" else 8, 4)
+    others = ((4, 4), (9, 8), (LDS, 8)) if precision == "fp64" else ((5, 4), (0, 8), (12, 6))
+    for v, width in others:
+        for k, (a, b) in enumerate(zip(_run(prob, init, v, width), ref)):
+            assert np.array_equal(a, b), (v, width, k)
