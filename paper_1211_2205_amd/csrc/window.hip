@@ -677,13 +677,18 @@ int window_groups(const WindowGrid& g) { return std::max(1, (g.ntx * g.nty + kGr
 // 14.6 -> 11.7; BF16 P_9 64^2 6.0 -> 4.4, P_31 100^2 15.5 -> 11.8.  Beyond it
 // costs (FP32 P_7 128^2 in three 4.67, P_31 64^2 in three 9.0).  FP64, whose waves
 // load twice the bytes, gains with fewer: P_9 64^2 5.6 -> 5.1, P_39 64^2 19.7 ->
-// 16.5, but P_3 150^2 4.3 -> 4.55, P_7 128^2 5.6 -> 6.4.
-int window_runs(int value_bytes, const WindowGrid& g, int waves_per_tile, int N) {
+// 16.5, but P_3 150^2 4.3 -> 4.55, P_7 128^2 5.6 -> 6.4; an order of the general
+// kernel, with decay planes and sources to look up, takes longer (beam P_7 100^2
+// 7.4 -> 6.3, P_13 100^2 11.4 -> 9.5, P_7 128^2 7.7 -> 7.25; P_9 150^2 9.65 -> 9.9).
+int window_runs(int value_bytes, bool general, const WindowGrid& g, int waves_per_tile, int N) {
   const int waves = g.ntx * g.nty * g.nchunks * waves_per_tile;
   if (waves < 1 || window_groups(g) > 1) return 1;  // (a launch of several runs has one group)
   int n;
   if (value_bytes == 8)
-    n = N >= 16 ? (waves <= 1400 ? 2 : 1) : waves <= 400 ? 1200 / waves : 512 / waves;
+    n = N >= 16                   ? (waves <= 1400 ? 2 : 1)
+        : waves <= 400            ? 1200 / waves
+        : general && waves <= 1000 ? 2
+                                  : 512 / waves;
   else
     n = N >= 16 ? std::max(2400 / waves, waves <= 1650 ? 2 : 1) : 2048 / waves;
   return std::min(std::max(n, 1), N / 2 + 1);
@@ -739,7 +744,7 @@ hipError_t launch_t(int storage, const WindowArgs& w, hipStream_t stream) {
   const WindowGrid g = window_grid(storage, w.nx, w.ny, w.px, w.py, w.tx, w.ty, w.N, w.nm);
   a.o = window_order(g, w.strip);
   const int blocks1 = g.ntx * g.nty * g.nchunks;
-  a.nseg = window_runs(int(sizeof(T)), g, a.threads / 64, w.N);
+  a.nseg = window_runs(int(sizeof(T)), w.general != 0, g, a.threads / 64, w.N);
   a.by_nseg = divisor(a.nseg);
   a.planes = w.planes;
   a.N = w.N;
