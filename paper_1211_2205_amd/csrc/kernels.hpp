@@ -5,6 +5,8 @@
 
 #include <cstdint>
 
+#include "window_order.hpp"
+
 namespace starmap {
 
 enum StorageType : int { STORE_FP64 = 0, STORE_FP32 = 1, STORE_BF16 = 2 };
@@ -97,23 +99,7 @@ struct WindowArgs {
 };
 // nm for m ranges of about the given width, and the tiles and ranges of a sweep.
 int window_nm(int N, int width);
-struct WindowGrid {
-  int ntx, nty, nchunks;
-};
 WindowGrid window_grid(int storage, int nx, int ny, int px, int py, int tx, int ty, int N, int nm);
-// Division of 0 <= n < 2^31 by a constant: n / d = n m >> s.
-struct Divisor {
-  uint32_t m = 0, s = 0;
-};
-// How a workgroup's number becomes an m range and a tile: groups of gsize tiles
-// (the last may be smaller), a group's ranges one after another, a range's tiles.
-struct WindowOrder {
-  Divisor per, by_gsize;      // numbers per group and per range of a group
-  Divisor band, rows, last;   // tiles per strip; a strip's width, the last strip's
-  int ntx, nty, nchunks, strip, gsize;
-  int items;                  // numbers in all
-};
-WindowOrder window_order(const WindowGrid& g, int strip);
 hipError_t launch_window(int storage, const WindowArgs& w, hipStream_t stream);
 // One instance of a batched run of register-window sweeps.
 struct WindowEntry {

@@ -154,38 +154,6 @@ struct WindowScalars {
   C tau;
 };
 
-// Quotients by constants of a launch as multiplications: the six divisions
-// between a workgroup's number and its first load, each some 28 dependent
-// instructions, had been a tenth of a small sweep (P_3 100^2 FP64 4.14 -> 3.78
-// us, P_9 317 x 203 FP32 8.1 -> 7.5; with the plane numbers as arguments, not
-// read from a table first, 3.63 and 7.2).
-__device__ __forceinline__ int divide(int n, const Divisor& d) { return int((uint64_t(uint32_t(n)) * d.m) >> d.s); }
-
-// Tile number t of the order (tile_xy of device.hpp with its divisors).
-__device__ __forceinline__ int2 tile_at(int t, const WindowOrder& o) {
-  const int band = divide(t, o.band);
-  if (o.strip >= 2) {
-    const int row0 = band * o.strip, rows = min(o.strip, o.nty - row0);
-    const int r = t - band * (o.strip * o.ntx), q = divide(r, rows == o.strip ? o.rows : o.last);
-    return make_int2(q, row0 + (r - q * rows));
-  }
-  if (o.strip <= -2) {
-    const int w = -o.strip, col0 = band * w, cols = min(w, o.ntx - col0);
-    const int r = t - band * (w * o.nty), q = divide(r, cols == w ? o.rows : o.last);
-    return make_int2(col0 + (r - q * cols), q);
-  }
-  return make_int2(t - band * o.ntx, band);
-}
-
-// Tiles of one group, about: the workgroups of a group are numbered range by
-// range, and the ranges of low m, which have the most orders, come first.
-// Ranges as the inner index, as the LDS kernel takes them (its ranges share
-// staged lines), leave the long ranges to the end of a launch: P_39 1000^2 FP32
-// 1100 against 1026 us, P_31 256^2 53 against 48 us.  One group over the whole
-// of a large grid loses the overlap of the ranges' shared planes: 1040 us.
-constexpr int kGroup = 512;
-constexpr int kXcds = 8;
-
 template <typename T, int NM, int P, bool G, bool S, bool EDGE>
 __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename ComputeOf<T>::type* __restrict__ decay,
                                             cptr<typename ComputeOf<T>::type> coef, cptr<int> tab,
@@ -203,13 +171,8 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
   constexpr int AUX = S ? kStream : 0;
   constexpr int NB = NM + 1;  // input planes of one order that the range needs, R and I each
 
-  // consecutive workgroups run on the chip's XCDs in turn: each takes a run of
-  // neighbouring tiles, whose shared rows its L2 then holds (P_9 317 x 203 FP32
-  // 8.2 -> 7.5 us, P_7 280^2 FP64 14.6 -> 14.0, P_39 1000^2 BF16 528 -> 517)
-  const uint32_t gtiles = uint32_t(min(a.o.gsize, a.o.ntx * a.o.nty - grp * a.o.gsize)), xcd = uint32_t(tl) % kXcds;
-  if (uint32_t(tl) >= gtiles) return;  // (the last group may be smaller)
-  const int tile =
-      grp * a.o.gsize + int(xcd * (gtiles / kXcds) + min(xcd, gtiles % kXcds) + uint32_t(tl) / kXcds);
+  const int tile = tile_number(a.o, grp, tl);
+  if (tile < 0) return;
   int m0 = chunk * 2 * NM;
   const int ltop = a.N - ((a.N - P) & 1), lbot = m0 + P;
   if (lbot > ltop) return;  // no output rows in this m range
@@ -223,7 +186,7 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
   const int lfirst = ltop - 2 * o0, llast = ltop - 2 * (o1 - 1);
 
   // this thread's points (X .. X + V - 1, Y)
-  const int2 txy = tile_at(tile, a.o);
+  const TileAt txy = tile_at(tile, a.o);
   const int bw = 1 << a.lbw;
   const int f = txy.y * a.threads + int(threadIdx.x);
   int Y = f >> a.lbw;
@@ -655,19 +618,6 @@ window_batch_kernel(const WindowEntry* __restrict__ table, const int* __restrict
     window_tile<T, NMAX < 4 ? 2 : 4, P, G, S, EDGE>(u, dec, cf, tab, a, grp, chunk, tl, 0);
 }
 
-// 2^s / d rounded up, with s so large (2^31 d at least) that the error, below
-// one part in 2^31, changes no quotient of a number below 2^31.
-Divisor divisor(int d) {
-  Divisor r;
-  d = d < 1 ? 1 : d;
-  r.s = 31;
-  while ((int64_t(1) << (r.s - 31)) < d) ++r.s;
-  r.m = uint32_t((uint64_t(1) << r.s) / uint32_t(d) + 1);
-  return r;
-}
-
-int window_groups(const WindowGrid& g) { return std::max(1, (g.ntx * g.nty + kGroup / 2) / kGroup); }
-
 // Runs of orders of a launch: one of few waves is a chain of memory round trips,
 // one per order, so its orders are split into runs that start their own chains
 // (one more window to load each) while the chip has room for them: up to 2048
@@ -680,9 +630,9 @@ int window_groups(const WindowGrid& g) { return std::max(1, (g.ntx * g.nty + kGr
 // 16.5, but P_3 150^2 4.3 -> 4.55, P_7 128^2 5.6 -> 6.4; an order of the general
 // kernel, with decay planes and sources to look up, takes longer (beam P_7 100^2
 // 7.4 -> 6.3, P_13 100^2 11.4 -> 9.5, P_7 128^2 7.7 -> 7.25; P_9 150^2 9.65 -> 9.9).
-int window_runs(int value_bytes, bool general, const WindowGrid& g, int waves_per_tile, int N) {
-  const int waves = g.ntx * g.nty * g.nchunks * waves_per_tile;
-  if (waves < 1 || window_groups(g) > 1) return 1;  // (a launch of several runs has one group)
+int window_runs(int value_bytes, bool general, const WindowOrder& o, int waves_per_tile, int N) {
+  const int waves = o.ntx * o.nty * o.nchunks * waves_per_tile;
+  if (waves < 1 || o.groups > 1) return 1;  // (a launch of several runs has one group)
   int n;
   if (value_bytes == 8)
     n = N >= 16                   ? (waves <= 1400 ? 2 : 1)
@@ -744,16 +694,15 @@ hipError_t launch_t(int storage, const WindowArgs& w, hipStream_t stream) {
   const WindowGrid g = window_grid(storage, w.nx, w.ny, w.px, w.py, w.tx, w.ty, w.N, w.nm);
   a.o = window_order(g, w.strip);
   const int blocks1 = g.ntx * g.nty * g.nchunks;
-  a.nseg = window_runs(int(sizeof(T)), w.general != 0, g, a.threads / 64, w.N);
+  a.nseg = window_runs(int(sizeof(T)), w.general != 0, a.o, a.threads / 64, w.N);
   a.by_nseg = divisor(a.nseg);
   a.planes = w.planes;
   a.N = w.N;
   a.top_shift = w.top_shift;
   a.tau = C(w.tau);
   if (a.lbw < 0 || a.threads < 64 || a.threads > kMaxThreads<T>) return hipErrorInvalidValue;
-  const int groups = window_groups(g);
-  if (blocks1 < 1 || g.nchunks > 65535 || groups > 65535) return hipErrorInvalidValue;
-  const dim3 blocks(unsigned(a.o.gsize), unsigned(g.nchunks), unsigned(a.nseg > 1 ? a.nseg : groups));
+  if (blocks1 < 1 || g.nchunks > 65535 || a.o.groups > 65535) return hipErrorInvalidValue;
+  const dim3 blocks(unsigned(a.o.gsize), unsigned(g.nchunks), unsigned(a.nseg > 1 ? a.nseg : a.o.groups));
   T* u = static_cast<T*>(w.u);
   const C *d = static_cast<const C*>(w.decay), *cf = static_cast<const C*>(w.coef);
   auto launch = [&](auto kernel) {
@@ -830,26 +779,6 @@ WindowGrid window_grid(int storage, int nx, int ny, int px, int py, int tx, int 
   g.nty = (ny + 1 - py + ty - 1) / ty;
   g.nchunks = (N + 1 + 2 * nm - 1) / (2 * nm);
   return g;
-}
-
-WindowOrder window_order(const WindowGrid& g, int strip) {
-  WindowOrder o;
-  o.ntx = g.ntx;
-  o.nty = g.nty;
-  o.nchunks = g.nchunks;
-  o.strip = strip;
-  // groups of equal size, in whole turns of the XCDs
-  const int ntiles = g.ntx * g.nty, groups = window_groups(g), per = (ntiles + groups - 1) / groups;
-  o.gsize = groups > 1 ? (per + kXcds - 1) / kXcds * kXcds : ntiles;
-  o.items = groups * o.gsize * g.nchunks;
-  o.per = divisor(o.gsize * g.nchunks);
-  o.by_gsize = divisor(o.gsize);
-  const int w = strip >= 2 ? strip : strip <= -2 ? -strip : 1;
-  const int across = strip <= -2 ? g.nty : g.ntx, along = strip <= -2 ? g.ntx : g.nty;
-  o.band = divisor(int(std::min<int64_t>(int64_t(w) * across, 0x7FFFFFFF)));
-  o.rows = divisor(w);
-  o.last = divisor(along % w);
-  return o;
 }
 
 hipError_t launch_window(int storage, const WindowArgs& w, hipStream_t stream) {

@@ -176,3 +176,29 @@ def test_runs_of_orders(N, precision):
     for v, width in others:
         for k, (a, b) in enumerate(zip(_run(prob, init, v, width), ref)):
             assert np.array_equal(a, b), (v, width, k)
+
+
+@pytest.mark.parametrize("precision,tiles", [("fp64", (LDS, 12)), ("fp32", (12, 8))])
+def test_launches_of_very_many_tiles(precision, tiles):
+    """2600^2 points make some 53000 tiles 64 wide and 2 high (the groups of
+    tiles are rounded up, so from 33793 on they hold more than all tiles); FP32
+    tiles 512 wide stay below that.  One instance by itself and in a batch."""
+    prob = _problem(1, (2600, 2600), (X, X), False, precision)
+    prob.t_final = 1e-4  # one step
+    runs = []
+    for v in tiles:
+        s = pa.Solver.from_problem(prob)
+        s.bind_torch()
+        s.set_variant(v)
+        s.run()
+        runs.append(s.moments())
+        s.close()
+    s = pa.Solver.from_problem(prob)
+    b = pa.Batch([s])
+    b.set_variant(tiles[1], 4)
+    b.run()
+    for got in (runs[1], s.moments()):
+        assert any(np.any(a) for a in got)
+        for k, (x, y) in enumerate(zip(got, runs[0])):
+            assert np.array_equal(x, y), k
+    b.close()

@@ -1,0 +1,36 @@
+// Enumerates the workgroup numbering of register-window sweeps on the host.
+//   groups MAX            for every number of tiles up to MAX: groups of gsize
+//                         tiles, none of them empty, hold each tile once
+//   tiles NTX NTY STRIP   prints "x y" of every tile in the order of the numbers
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+
+#include "window_order.hpp"
+
+using namespace starmap;
+
+int main(int argc, char** argv) {
+  if (argc == 3 && !std::strcmp(argv[1], "groups")) {
+    for (int n = 1; n <= std::atoi(argv[2]); ++n) {
+      const WindowOrder o = window_order({n, 1, 3}, 1);
+      if (o.items != o.groups * o.gsize * 3 || (o.groups - 1) * o.gsize >= n || o.groups * o.gsize < n) {
+        std::printf("%d tiles: %d groups of %d\n", n, o.groups, o.gsize);
+        return 1;
+      }
+    }
+    return 0;
+  }
+  if (argc == 5 && !std::strcmp(argv[1], "tiles")) {
+    const WindowOrder o = window_order({std::atoi(argv[2]), std::atoi(argv[3]), 2}, std::atoi(argv[4]));
+    for (int item = 0; item < o.items; ++item) {  // as the batched kernel takes them apart
+      const int grp = divide(item, o.per), within = item - grp * (o.gsize * o.nchunks);
+      const int chunk = divide(within, o.by_gsize), t = tile_number(o, grp, within - chunk * o.gsize);
+      if (t < 0) continue;
+      const TileAt at = tile_at(t, o);
+      std::printf("%d %d %d\n", chunk, at.x, at.y);
+    }
+    return 0;
+  }
+  return 2;
+}
