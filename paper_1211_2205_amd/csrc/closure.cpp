@@ -175,9 +175,11 @@ int mlp_step(starmap_mlp* n, const float* X, const float* T, int B, const MlpAda
   return STARMAP_OK;
 }
 
-MlpAdam adam_args(starmap_mlp* n, double lr) {
-  const double b1 = 0.9, b2 = 0.999;
-  const double c1 = 1.0 - std::pow(b1, double(n->t)), c2 = 1.0 - std::pow(b2, double(n->t));
+// Arguments of the next step's update.  The step counts once its update is
+// launched: a step that fails before leaves the bias correction as it was.
+MlpAdam adam_args(const starmap_mlp* n, double lr) {
+  const double b1 = 0.9, b2 = 0.999, t = double(n->t + 1);
+  const double c1 = 1.0 - std::pow(b1, t), c2 = 1.0 - std::pow(b2, t);
   return {n->params, n->m, n->v, float(lr), float(b1), float(b2), 1e-8f, float(c1), float(c2)};
 }
 
@@ -405,9 +407,9 @@ int starmap_mlp_train_step(starmap_mlp* n, const float* x, const float* t, int32
   int rc = check_batch(n, batch);
   if (rc) return rc;
   if (!x || !t || !(lr > 0.0)) return fail(STARMAP_EINVAL, "bad arguments");
-  n->t += 1;
   rc = mlp_step(n, x, t, batch, adam_args(n, lr));
   if (rc) return rc;
+  n->t += 1;
   if (loss) {
     HIP_TRY(hipMemcpyAsync(loss, n->loss, 8, hipMemcpyDeviceToHost, n->stream));
     HIP_TRY(hipStreamSynchronize(n->stream));
@@ -418,8 +420,8 @@ int starmap_mlp_train_step(starmap_mlp* n, const float* x, const float* t, int32
 int starmap_mlp_adam_step(starmap_mlp* n, const float* grad_host, double lr) {
   if (!n || !grad_host || !(lr > 0.0)) return fail(STARMAP_EINVAL, "bad arguments");
   HIP_TRY(hipMemcpyAsync(n->grads, grad_host, size_t(CLOSURE_PARAMS) * 4, hipMemcpyHostToDevice, n->stream));
-  n->t += 1;
   HIP_TRY(launch_adam(adam_args(n, lr), n->grads, n->stream));
+  n->t += 1;
   HIP_TRY(hipStreamSynchronize(n->stream));
   return STARMAP_OK;
 }
