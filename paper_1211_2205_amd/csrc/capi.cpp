@@ -390,10 +390,8 @@ void layout(starmap_solver* s) {
   // on the tile.
   if (s->chunk_width <= 0) {
     s->chunk_width = kDefaultChunkWidth;
-    if (const char* w = std::getenv("STARMAP_CHUNK_WIDTH")) {
-      s->chunk_width = std::max(2, std::atoi(w));
-      s->width_given = true;
-    }
+    if (const char* w = std::getenv("STARMAP_CHUNK_WIDTH"))
+      s->chunk_width = s->given_width = std::max(2, std::atoi(w));
   }
   s->nchunks = sweep_chunk_count(s->N, s->chunk_width);
   // (FP32 and BF16 sweeps read no programs)
@@ -637,8 +635,7 @@ int load_tune_cache(starmap_solver* s) {
       if (N == s->N && nx == s->nx && ny == s->ny && st == s->storage && v >= 0 && v < sweep_variant_count() &&
           w >= 2) {
         found = v;
-        s->chunk_width = w;
-        s->width_given = true;
+        s->chunk_width = s->given_width = w;
       }
   }
   return found;
@@ -664,11 +661,11 @@ double swept_bytes(const starmap_solver* s) {
 int default_variant(starmap_solver* s) {
   const int cols = s->nx + 1 - s->px, rows = s->ny + 1 - s->py;
   int v = sweep_default_variant(s->storage, s->N, cols, rows, swept_bytes(s));
-  if (!s->width_given) s->chunk_width = sweep_default_width(s->storage, v, s->N, cols, rows);
+  s->chunk_width = s->given_width ? s->given_width : sweep_default_width(s->storage, v, s->N, cols, rows);
   if (s->storage != STORE_FP64) return v;
   // (a given width that the tile's registers do not hold the planes of: the
   // tile of its shape that holds ten)
-  if (s->width_given && !sweep_in_registers(s->storage, v) && s->chunk_width + 2 > sweep_variant(s->storage, v).cap)
+  if (s->given_width && !sweep_in_registers(s->storage, v) && s->chunk_width + 2 > sweep_variant(s->storage, v).cap)
     v = v == 7 ? 5 : 2;
   if (!sweep_in_registers(s->storage, v) &&
       sweep_lds_bytes(v, program_slots(s, v), s->storage) > size_t(max_lds_bytes()))
@@ -1664,15 +1661,15 @@ int starmap_set_range_width(starmap_solver* s, int32_t width) {
     return fail(STARMAP_EINVAL, "unsupported m-range width");
   const int keep = s->chunk_width;
   s->chunk_width = width;
-  s->width_given = true;
   s->nchunks = sweep_chunk_count(s->N, width);
-  if (!s->device_ready) return STARMAP_OK;
-  int rc = upload_program(s);
-  if (!rc && sweep_lds_bytes(s->variant, s->slots, s->storage) > size_t(max_lds_bytes()))
+  int rc = s->device_ready ? upload_program(s) : STARMAP_OK;
+  if (!rc && s->device_ready && sweep_lds_bytes(s->variant, s->slots, s->storage) > size_t(max_lds_bytes()))
     rc = fail(STARMAP_EINVAL, "the tile variant does not fit the LDS at this m-range width");
   if (rc) {
     s->chunk_width = keep;
     (void)upload_program(s);
+  } else {
+    s->given_width = width;
   }
   return rc;
 }
@@ -1773,8 +1770,7 @@ int starmap_autotune(starmap_solver* s, int32_t sweeps) {
   }
   if (best < 0) return fail(STARMAP_ENOMEM, "no sweep tile fits the LDS for this moment order");
   s->variant = best;
-  s->chunk_width = best_w;
-  s->width_given = true;
+  s->chunk_width = s->given_width = best_w;
   rc = upload_program(s);
   if (rc) return rc;
   if (const char* path = std::getenv("STARMAP_TUNE_CACHE")) {
@@ -1986,8 +1982,7 @@ int group_prepare(starmap_batch* b, BatchGroup& g, int variant, int width) {
   for (int i : g.members) {
     starmap_solver* s = b->inst[i];
     s->variant = variant;
-    s->chunk_width = width;
-    s->width_given = true;
+    s->chunk_width = s->given_width = width;
     rc = upload_program(s);
     if (rc) return rc;
     if (!sweep_in_registers(b->storage, variant) && s->prog[0].chunks.size() != s->prog[1].chunks.size())

@@ -1,0 +1,95 @@
+"""The library's host code without a device: each test runs a small program in a
+process whose HIP calls go to tests/fake_hip.cpp (memory from the heap, launches
+that do nothing), and looks at the choices the library makes."""
+import os
+import shutil
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PREAMBLE = """
+import ctypes, os, sys
+fake = ctypes.CDLL({fake!r}, ctypes.RTLD_GLOBAL)
+sys.path.insert(0, {root!r})
+import paper_1211_2205_amd as pa
+import workloads as wl
+
+def problem(N=7, n=(40, 24), precision="fp64", general=False):
+    one = lambda t, x, y: 1.0 + 0.0 * x
+    return wl.Problem(name="host", N=N, n=n, ax=(0.0, 1.0, 0.0, 1.0), bc=("periodic", "extrapolation"), cfl=0.5,
+                      t_final=0.1, precision=precision, sigma_a=one, sigma_s0=one,
+                      sigma_sl=(lambda l, t, x, y: 0.5 ** l + 0.0 * x) if general else None,
+                      source={{k: one for k in range(pa.num_moments(N) if general else 1)}})
+
+def solver(*a, **k):
+    s = pa.Solver.from_problem(problem(*a, **k))
+    s.advance(1)
+    return s
+
+def tile(s):
+    return s.variant()[0], s.chunk_width()
+"""
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("g++ not available")
+    fake = str(tmp_path_factory.mktemp("fake") / "fake_hip.so")
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-w", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__=1", "-I",
+                           os.path.join(rocm, "include"), "-o", fake, os.path.join(HERE, "fake_hip.cpp")])
+
+    def run(body, **env):
+        code = PREAMBLE.format(fake=fake, root=ROOT) + textwrap.dedent(body)
+        base = {k: v for k, v in os.environ.items() if not k.startswith("STARMAP_")}
+        r = subprocess.run([sys.executable, "-c", code], env={**base, **env}, capture_output=True, text=True, timeout=300)
+        assert r.returncode == 0, r.stdout + r.stderr
+    return run
+
+
+def test_a_refused_width_is_not_a_given_one(program):
+    """A width that was not taken on leaves the solver without one of its own:
+    the default tile still brings its width; one that was taken on is kept."""
+    program("""
+        default = tile(solver())
+        assert default[1] != 8
+        s = pa.Solver.from_problem(problem())
+        s.set_variant(0)
+        s.advance(1)
+        assert tile(s) == (0, 8)  # a tile given before the first device call: the widest ranges
+        copies = ctypes.c_int.in_dll(fake, "fake_failing_copies")
+        copies.value = 1
+        try:
+            s.set_chunk_width(4)
+            raise SystemExit("accepted")
+        except pa.StarmapError:
+            pass
+        assert copies.value == 0 and tile(s) == (0, 8)
+        s.set_variant(-1)
+        assert tile(s) == default, (tile(s), default)
+        s.set_variant(0)
+        s.set_chunk_width(6)
+        s.set_variant(-1)
+        assert tile(s) == (default[0], 6)
+    """)
+
+
+def test_refused_widths_leave_the_width(program):
+    """With 64 KiB of LDS a 64 x 8 FP64 tile of P_13 holds four indices of m, not six."""
+    program("""
+        s = solver(N=13)
+        s.set_chunk_width(4)
+        s.set_variant(5)
+        for width in (6, 8):
+            try:
+                s.set_chunk_width(width)
+                raise SystemExit("accepted")
+            except pa.StarmapError:
+                assert tile(s) == (5, 4)
+    """, FAKE_LDS="65536")
