@@ -1982,7 +1982,7 @@ int group_prepare(starmap_batch* b, BatchGroup& g, int variant, int width) {
   for (int i : g.members) {
     starmap_solver* s = b->inst[i];
     s->variant = variant;
-    s->chunk_width = s->given_width = width;
+    s->chunk_width = width;  // (the batch's: set_variant(-1) goes back to the solver's own)
     rc = upload_program(s);
     if (rc) return rc;
     if (!sweep_in_registers(b->storage, variant) && s->prog[0].chunks.size() != s->prog[1].chunks.size())

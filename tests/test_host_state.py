@@ -93,3 +93,24 @@ def test_refused_widths_leave_the_width(program):
             except pa.StarmapError:
                 assert tile(s) == (5, 4)
     """, FAKE_LDS="65536")
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "bf16"])
+def test_default_tile_after_a_batch(program, precision):
+    """The tile and width that a batch gave its solvers are the batch's: the
+    default tile brings its own width back, or the one the user had given."""
+    program(f"""
+        default = tile(solver(precision={precision!r}))
+        for given in (0, 6):
+            a, c = (pa.Solver.from_problem(problem(precision={precision!r})) for _ in range(2))
+            if given:
+                a.set_chunk_width(given)
+            b = pa.Batch([a, c])
+            b.run(use_graph=False)
+            assert b.variant() == (0, 8) and tile(a) == tile(c) == (0, 8)
+            b.close()
+            a.set_variant(-1)
+            c.set_variant(-1)
+            assert tile(c) == default, (tile(c), default)
+            assert tile(a) == (default[0], given or default[1])
+    """)
