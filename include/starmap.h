@@ -257,7 +257,9 @@ int starmap_diagnostics_noalloc(const starmap_solver* s, double* mass_r00, doubl
    variant; all give the same bits.  starmap_autotune times every variant that fits, at every
    m-range width (4, 6, 8), on a few sweeps of this solver, keeps the fastest
    pair and writes it to the cache file named by the environment variable
-   STARMAP_TUNE_CACHE (if set).  Variants are 0 .. starmap_variant_count()-1;
+   STARMAP_TUNE_CACHE (if set).  A line of that file names the tile its
+   variant number stood for; lines that name none, or another one (the numbers
+   mean other tiles than they once did), are passed over.  Variants are 0 .. starmap_variant_count()-1;
    another value fails with STARMAP_EINVAL.  The environment variable
    STARMAP_TILE_STRIP (read by starmap_create) sets
    the order in which workgroups take the tiles: k >= 2 strips of k tile

@@ -622,6 +622,10 @@ int upload_materials(starmap_solver* s, double t_eval) {
   return STARMAP_OK;
 }
 
+// The variant that the tune cache names for this solver, or -1.  A line is the
+// solver's order, cells and storage, the variant and width, and the variant's
+// tile and kernel (TileShape): lines without these, or with others, were tuned
+// when the numbers meant other tiles and say nothing about today's.
 int load_tune_cache(starmap_solver* s) {
   const char* path = std::getenv("STARMAP_TUNE_CACHE");
   if (!path) return -1;
@@ -630,13 +634,14 @@ int load_tune_cache(starmap_solver* s) {
   int found = -1;
   while (std::getline(f, line)) {
     std::istringstream is(line);
-    int N, nx, ny, st, v, w;
-    if (is >> N >> nx >> ny >> st >> v >> w)
-      if (N == s->N && nx == s->nx && ny == s->ny && st == s->storage && v >= 0 && v < sweep_variant_count() &&
-          w >= 2) {
-        found = v;
-        s->chunk_width = s->given_width = w;
-      }
+    int N, nx, ny, st, v, w, tx, ty, cap;
+    if (!(is >> N >> nx >> ny >> st >> v >> w >> tx >> ty >> cap)) continue;
+    if (N != s->N || nx != s->nx || ny != s->ny || st != s->storage || v < 0 || v >= sweep_variant_count() || w < 2)
+      continue;
+    const TileShape ts = sweep_variant(st, v);
+    if (tx != ts.tx || ty != ts.ty || cap != ts.cap) continue;
+    found = v;
+    s->chunk_width = s->given_width = w;
   }
   return found;
 }
@@ -1775,7 +1780,9 @@ int starmap_autotune(starmap_solver* s, int32_t sweeps) {
   if (rc) return rc;
   if (const char* path = std::getenv("STARMAP_TUNE_CACHE")) {
     std::ofstream f(path, std::ios::app);
-    f << s->N << " " << s->nx << " " << s->ny << " " << s->storage << " " << best << " " << best_w << "\n";
+    const TileShape ts = sweep_variant(s->storage, best);
+    f << s->N << " " << s->nx << " " << s->ny << " " << s->storage << " " << best << " " << best_w << " " << ts.tx
+      << " " << ts.ty << " " << ts.cap << "\n";
   }
   return STARMAP_OK;
 }

@@ -114,3 +114,32 @@ def test_default_tile_after_a_batch(program, precision):
             assert tile(c) == default, (tile(c), default)
             assert tile(a) == (default[0], given or default[1])
     """)
+
+
+@pytest.mark.parametrize("precision,storage", [("fp64", 0), ("fp32", 1), ("bf16", 2)])
+def test_tune_cache_lines_name_their_tile(program, precision, storage, tmp_path):
+    """A line counts if its variant number still means the tile it was written
+    for: lines without a tile, from when the numbers meant other tiles, and lines
+    of another tile or kernel leave the default."""
+    program(f"""
+        path = os.environ["STARMAP_TUNE_CACHE"]
+        storage, make = {storage}, lambda: solver(precision={precision!r})
+
+        def chosen(*rows):
+            with open(path, "w") as f:
+                f.writelines(r + chr(10) for r in rows)
+            return tile(make())
+
+        default = chosen()
+        key = f"7 40 24 {{storage}}"
+        for stale in ("4 8", "9 6", "12 4", "6 8", "0 8", "5 8 64 8", "5 6 64 8 9", "5 6 8 64 10", "5 6 64 8 -1", "5 6 64 8 x"):
+            assert chosen(f"{{key}} {{stale}}") == default, stale
+        # the autotuner's line is taken, over stale ones before and after it
+        os.remove(path)
+        s = make()
+        s.autotune(1)
+        tuned = tile(s)
+        (line,) = open(path).read().splitlines()
+        assert chosen(f"{{key}} 9 6", line, f"{{key}} 4 8", f"7 40 25 {{storage}} 1 4") == tuned
+        assert chosen(line, line.replace("7 40 24", "7 41 24")) == tuned
+    """, STARMAP_TUNE_CACHE=str(tmp_path / "cache"))
