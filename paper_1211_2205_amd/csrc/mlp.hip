@@ -16,6 +16,7 @@
 // accumulation, biases and activations before rounding are FP32.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cmath>
 #include <cstdint>
 
@@ -1138,14 +1139,17 @@ size_t closure_infer_lds_bytes() {
 }
 
 namespace {
-// Opts a kernel in to its LDS (once).
+// Opts a kernel in to its LDS, once on every device (devices past 64: each time).
 template <auto kernel>
 hipError_t opt_in_lds(size_t lds) {
-  static bool done = false;
-  if (done) return hipSuccess;
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
-  done = e == hipSuccess;
+  static std::atomic<uint64_t> done{0};
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = dev >= 0 && dev < 64 ? uint64_t(1) << dev : 0;
+  if (done.load(std::memory_order_acquire) & bit) return hipSuccess;
+  e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+  if (e == hipSuccess) done.fetch_or(bit, std::memory_order_release);
   return e;
 }
 

@@ -143,3 +143,23 @@ def test_tune_cache_lines_name_their_tile(program, precision, storage, tmp_path)
         assert chosen(f"{{key}} 9 6", line, f"{{key}} 4 8", f"7 40 25 {{storage}} 1 4") == tuned
         assert chosen(line, line.replace("7 40 24", "7 41 24")) == tuned
     """, STARMAP_TUNE_CACHE=str(tmp_path / "cache"))
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "bf16"])
+def test_closure_network_is_opted_in_on_every_device(program, precision):
+    """The network's weights take more LDS than a kernel gets unasked, and what a
+    kernel gets is set device by device."""
+    program(f"""
+        import numpy as np
+        weights = np.load(os.path.join(os.path.dirname(pa.__file__), "weights", "closure_p5_256.npy"))
+        device = ctypes.c_int.in_dll(fake, "fake_device")
+        for device.value in (0, 1, 0, 70, 1):
+            s = pa.Solver.from_problem(problem(N=5, precision={precision!r}), closure="learned")
+            s.load_closure(weights)
+            s.advance(1)
+            t = pa.Solver.from_problem(problem(N=5, precision={precision!r}), closure="learned")
+            t.load_closure(weights)
+            b = pa.Batch([t])
+            b.run(use_graph=False)
+            b.close()
+    """)
