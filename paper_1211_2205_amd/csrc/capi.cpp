@@ -664,9 +664,16 @@ double swept_bytes(const starmap_solver* s) {
 // Tile of a solver that was given none (and, unless it was given one, its
 // m-range width), from the sizes alone.
 int default_variant(starmap_solver* s) {
-  const int cols = s->nx + 1 - s->px, rows = s->ny + 1 - s->py;
-  int v = sweep_default_variant(s->storage, s->N, cols, rows, swept_bytes(s));
-  s->chunk_width = s->given_width ? s->given_width : sweep_default_width(s->storage, v, s->N, cols, rows);
+  SweepSizes z;
+  z.N = s->N;
+  z.cols = s->nx + 1 - s->px;
+  z.rows = s->ny + 1 - s->py;
+  z.state_bytes = swept_bytes(s);
+  z.decay_bytes = z.state_bytes / s->nmom / s->ssize * s->dmap.nplanes * s->csize;
+  z.by_order = s->anisotropic;
+  z.sources = s->nsrc > (s->qk[0] >= 0 ? 1 : 0);
+  int v = sweep_default_variant(s->storage, z);
+  s->chunk_width = s->given_width ? s->given_width : sweep_default_width(s->storage, v, z);
   if (s->storage != STORE_FP64) return v;
   // (a given width that the tile's registers do not hold the planes of: the
   // tile of its shape that holds ten)
@@ -674,7 +681,7 @@ int default_variant(starmap_solver* s) {
     v = v == 7 ? 5 : 2;
   if (!sweep_in_registers(s->storage, v) &&
       sweep_lds_bytes(v, program_slots(s, v), s->storage) > size_t(max_lds_bytes()))
-    v = sweep_default_variant(s->storage, s->N, 1, 1, 0.0);  // a tile without LDS
+    v = kNoLdsVariant;
   return v;
 }
 

@@ -21,10 +21,19 @@ struct TileShape {
 int sweep_variant_count();
 TileShape sweep_variant(int storage, int v);
 inline bool sweep_in_registers(int storage, int v) { return sweep_variant(storage, v).cap == 0; }
-// Variant of a solver that was given none, by its order, points per axis and
-// the bytes of its state, and its m-range width.
-int sweep_default_variant(int storage, int N, int cols, int rows, double state_bytes);
-int sweep_default_width(int storage, int variant, int N, int cols, int rows);
+// What the choice of a solver's tile goes by: its order, points per axis, the
+// bytes of its state and decay planes, whether the decay planes differ between
+// orders >= 1, whether moments beyond the zeroth have sources.
+struct SweepSizes {
+  int N, cols, rows;
+  double state_bytes, decay_bytes;
+  bool by_order, sources;
+};
+// Variant of a solver that was given none, and its m-range width.
+int sweep_default_variant(int storage, const SweepSizes& z);
+int sweep_default_width(int storage, int variant, const SweepSizes& z);
+// FP64: a tile that takes no LDS.
+constexpr int kNoLdsVariant = 12;
 // Whether states of these bytes are swept past the last-level cache.
 bool sweep_streams(double state_bytes);
 

@@ -23,6 +23,7 @@
 // periodic, clamp for extrapolation), so the stencil itself is uniform.
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstddef>
 #include <cstdint>
 
@@ -622,7 +623,8 @@ TileShape sweep_variant(int storage, int v) {
 }
 
 // The rules behind a solver that was given no tile, from timing every variant
-// and width on 88 sizes (P_1 .. P_39, 48^2 .. 1400^2).  Where two are given,
+// and width on 88 sizes (P_1 .. P_39, 48^2 .. 1400^2) and, in FP64, on 420 with
+// and without decay planes by order and sources on more moments.  Where two are given,
 // microseconds per sweep of the choice, then of the other.
 //
 // The last-level cache holds 256 MB: P_31 345^2 FP32 (253 MB) 77 us with the
@@ -632,13 +634,28 @@ bool sweep_streams(double state_bytes) { return state_bytes > kCache; }
 
 // FP64.  With the window in registers, 64 x 2 tiles (P_7 280^2 11.6, LDS 16;
 // P_3 1000^2 34 and 36; P_5 400^2 14.3 and 15.3; P_9 550^2 44 and 58; P_15 447^2
-// 62 and 77; P_31 150^2 36 and 59), but in LDS
+// 62 and 77; P_31 150^2 36 and 59), but in LDS, above some 350^2 points,
 //   - where one or two orders cannot hide the loads of a large grid: 64 x 8
 //     (P_1 400^2 6.5, registers 6.9; 1000^2 17 and 24);
-//   - beyond the cache, where the y neighbours' lines leave the L1 before they
-//     are asked for: 32 x 8 (P_39 500^2 557, registers 687; P_9 850^2 119 and
-//     142; P_7 1000^2 89 and 132), unless the LDS tiles are too few to fill the
-//     chip (P_39 200^2 118, registers 108).
+//   - where state and decay planes together leave the cache, and with them the y
+//     neighbours' lines the L1 before they are asked for: 32 x 8, up to P_3 64 x 8
+//     (P_39 500^2 557, registers 687; P_9 850^2 119 and 142; P_7 1000^2 89 and 132,
+//     930^2 91 and 98; P_3 1500^2 67 and 84; P_5 1200^2 81 and 103; decay planes by
+//     order: P_9 700^2 85 and 106, P_7 850^2 80 and 103, but P_13 500^2 92 and 83;
+//     the state alone counts from P_7 on with sources on more moments, which the
+//     LDS holds too: P_13 500^2 137 and 113), unless the LDS tiles are too few to
+//     fill the chip (P_39 200^2 118, registers 108);
+//   - up to P_6, whose few orders the general kernel's look-ups hold up most: with
+//     decay planes by order 32 x 8 (P_4 1000^2 47 and 66, 350^2 11.4 and 14.2; P_6
+//     700^2 41 and 50, but 350^2 21 and 20), P_3 from 800^2 on 64 x 8 (1000^2 34 and 44), and with sources
+//     on more moments P_4 (500^2 18 and 23, 1000^2 56 and 86), P_5 from 800^2 on
+//     (850^2 64 and 74, but 700^2 46 and 44) and P_3, P_2 (500^2 14.1 and 16.5; 400^2
+//     9.3, 64 x 8 10.1), these where the tiles' last round on the chip is nearly full
+//     (P_3 600^2 20.5 and 19.2) and the 64 x 8 tiles are not yet better (850^2 24.4
+//     and 22.9), and, but for P_4 with decay planes alone, no second round has just
+//     begun (a step of P_5 550^2 with changing media 351 and 323); of plain solvers P_4 likewise (500^2 15.1 and 18.1, 850^2 36.1 and
+//     37.1, but 600^2 23 and 21), and P_5 and P_6 where one round is just full
+//     (500^2 18.5 and 20.2, 23.0 and 24.4).
 // FP32, BF16.  Large states on wide tiles, which read the fewest lines twice,
 // where the grid fills them (P_39 1000^2 FP32: 512 x 1 993, 128 x 2 1012; 500^2
 // 236 and 247), else
@@ -650,13 +667,40 @@ bool sweep_streams(double state_bytes) { return state_bytes > kCache; }
 // and 15.6).  BF16: 128 x 4 (P_39 250^2 37, 64 x 2 40; P_7 512^2 13.0 and 13.6),
 // small ones 64 x 2 (P_9 150^2 6.6, 128 x 4 7.2; P_21 300^2 19.8 and 20.4; P_31
 // 256^2 29 and 31).
-int sweep_default_variant(int storage, int N, int cols, int rows, double state_bytes) {
-  const double points = double(cols) * rows;
-  const bool cached = !sweep_streams(state_bytes);
-  if (storage == STORE_FP64) {
-    if (cached) return N <= 2 && points > 1.2e5 ? 7 : 12;
-    return points > 6.0e4 ? (N <= 3 ? 7 : 8) : 12;
+static int default_variant64(const SweepSizes& z) {
+  const double points = double(z.cols) * z.rows;
+  const double bytes = z.state_bytes + (z.N <= 6 || !z.sources ? z.decay_bytes : 0.0);
+  const bool cached = !sweep_streams(z.state_bytes) && bytes <= (z.N <= 6 ? 2.5e8 : 2.7e8);
+  if (points <= (cached ? 1.2e5 : 6.0e4)) return kNoLdsVariant;
+  // rounds of 32 x 8 tiles, four on each of 256 compute units, and how full they are
+  const double rounds = std::ceil(z.cols / 32.0) * std::ceil(z.rows / 8.0) / 1024.0, full = rounds / std::ceil(rounds);
+  const bool general = z.by_order || z.sources;
+  const bool spills = rounds > 1.0 && rounds < 1.3;  // into a nearly empty second round
+  bool lds = !cached;
+  switch (z.N) {
+    case 1: return 7;
+    case 2: return z.sources && points < 6.0e5 && (rounds <= 1.0 || full > 0.85) ? 8 : 7;
+    case 3:
+      if (!general) return cached ? kNoLdsVariant : 7;
+      if (!z.sources && points > 6.4e5) return 7;
+      lds = lds || (z.sources ? full > 0.85 : !spills);
+      break;
+    case 4: lds = lds || (z.sources ? !spills : z.by_order || full > 0.85); break;
+    case 5:
+      lds = lds || (z.sources ? points > 6.4e5 : z.by_order ? !spills : rounds <= 1.0 && full > 0.97);
+      break;
+    case 6:
+      lds = lds || (!z.sources && (z.by_order ? !spills && points > 1.4e5 : rounds <= 1.0 && full > 0.97));
+      break;
   }
+  return lds ? 8 : kNoLdsVariant;
+}
+
+int sweep_default_variant(int storage, const SweepSizes& z) {
+  if (storage == STORE_FP64) return default_variant64(z);
+  const int N = z.N, cols = z.cols;
+  const double points = double(cols) * z.rows, state_bytes = z.state_bytes;
+  const bool cached = !sweep_streams(state_bytes);
   auto fills = [&](int wide) { return (cols + wide - 1) / wide * wide - cols <= cols / 20; };
   if (storage == STORE_BF16) return cached ? (points < 1.2e5 && state_bytes < 8.5e7 ? 8 : 4) : fills(256) ? 6 : 4;
   if (!cached) return N >= 8 && N < 16 ? 0 : N >= 16 && fills(512) ? 12 : fills(128) ? 1 : 5;
@@ -665,17 +709,22 @@ int sweep_default_variant(int storage, int N, int cols, int rows, double state_b
 
 // m ranges.  LDS window: one range where it holds every index (P_5 400^2 15.3,
 // at four 20.7; P_7 1000^2 89, at four 122), from P_13 on six (P_39 500^2 557,
-// eight 618, four 580), else four.  Registers: four, more workgroups, while the
-// chip is not full (P_21 150^2 FP32 12, six 15; P_31 128^2 17 and 21.5; P_5 150^2
-// 4.3 and 4.7; BF16 P_31 256^2 29 and 30), and no idle rows in P_15 (FP32 447^2
-// 30.0, six 30.9); of grids that fill it six, which read fewer planes twice
-// (FP32 P_21 300^2 27.6, four 28.2), which is one
-// range of P_4 and P_5 (FP32 400^2 7.3 and 7.7, FP64 300^2 8.7 and 9.7); eight
-// for P_8 .. P_15 (FP32 P_15 1000^2 155, six 160; P_9 1800^2 221 and 229) and in
-// 512 x 1 tiles (P_39 1000^2 993, six 998).
-int sweep_default_width(int storage, int variant, int N, int cols, int rows) {
-  const double points = double(cols) * rows;
-  if (!sweep_in_registers(storage, variant)) return N == 4 || N == 5 ? 6 : N == 6 || N == 7 ? 8 : N >= 13 ? 6 : 4;
+// eight 618, four 580), else four, which from P_16 on is better for the general
+// sweep, whose sources take LDS too (P_21 400^2 171, six 290; decay planes by order
+// alone 130 and 165; P_16 500^2 170 and 198).  Registers: four, more workgroups,
+// while the chip is not full (P_21 150^2 FP32 12, six 15; P_31 128^2 17 and 21.5;
+// P_5 150^2 4.3 and 4.7; BF16 P_31 256^2 29 and 30), and no idle rows in P_15 (FP32
+// 447^2 30.0, six 30.9); of grids that fill it six, which read fewer planes twice
+// (FP32 P_21 300^2 27.6, four 28.2), which is one range of P_4 and P_5 (FP32 400^2
+// 7.3 and 7.7, FP64 300^2 8.7 and 9.7); eight for P_8 .. P_15 (FP32 P_15 1000^2 155,
+// six 160; P_9 1800^2 221 and 229) and in 512 x 1 tiles (P_39 1000^2 993, six 998).
+int sweep_default_width(int storage, int variant, const SweepSizes& z) {
+  const int N = z.N;
+  const double points = double(z.cols) * z.rows;
+  if (!sweep_in_registers(storage, variant)) {
+    if (N >= 16 && (z.by_order || z.sources)) return 4;
+    return N == 4 || N == 5 ? 6 : N == 6 || N == 7 ? 8 : N >= 13 ? 6 : 4;
+  }
   if (storage == STORE_FP64) return (N == 4 || N == 5) && points > 4.0e4 ? 6 : 4;
   if (N == 4 || N == 5) return points > (storage == STORE_FP32 ? 1.2e5 : 2.0e5) ? 6 : 4;
   if (storage == STORE_BF16) return N >= 16 ? (variant == 8 ? 4 : 6) : N >= 8 && points > 5.0e5 ? 6 : 4;

@@ -163,3 +163,34 @@ def test_closure_network_is_opted_in_on_every_device(program, precision):
             b.run(use_graph=False)
             b.close()
     """)
+
+
+def test_default_fp64_tiles_go_by_decay_planes_and_sources(program):
+    """Of grids above some 350^2 points, solvers of few orders take the LDS window
+    (32 x 8 tiles, one m range) where the general sweep's look-ups or the fit of
+    the tiles on the chip make it the faster one."""
+    program("""
+        def chosen(N, n, by_order, sources):
+            p = problem(N, (n, n))
+            p.bc = ("extrapolation", "extrapolation")
+            one = p.sigma_a
+            if by_order:
+                p.sigma_sl = lambda l, t, x, y: 0.5 ** l + 0.0 * x
+            if sources:
+                p.source = {k: one for k in range(pa.num_moments(N))}
+            s = pa.Solver.from_problem(p)
+            s.advance(1)
+            return tile(s)
+
+        window, lds = lambda w: (12, w), lambda w: (8, w)
+        for N, n, by_order, sources, want in (
+            (4, 300, True, True, window(6)), (4, 360, False, False, window(6)), (4, 360, True, False, lds(6)),
+            (4, 360, False, True, lds(6)), (4, 500, False, False, lds(6)), (4, 600, False, False, window(6)),
+            (3, 360, False, False, window(4)), (3, 360, True, False, lds(4)), (3, 360, True, True, window(4)),
+            (3, 500, True, True, lds(4)), (2, 360, False, False, (7, 4)), (2, 360, True, True, lds(4)), (2, 360, True, False, (7, 4)),
+            (5, 360, True, False, lds(6)), (5, 360, True, True, window(6)), (5, 500, False, False, lds(6)),
+            (5, 480, False, False, window(6)), (6, 360, True, False, window(4)), (6, 390, True, False, lds(8)), (6, 360, True, True, window(4)),
+            (7, 360, True, False, window(4)), (1, 360, True, True, (7, 4)),
+        ):
+            assert chosen(N, n, by_order, sources) == want, (N, n, by_order, sources, chosen(N, n, by_order, sources))
+    """)
