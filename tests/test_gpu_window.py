@@ -202,3 +202,41 @@ def test_launches_of_very_many_tiles(precision, tiles):
         for k, (x, y) in enumerate(zip(got, runs[0])):
             assert np.array_equal(x, y), k
     b.close()
+
+
+@pytest.mark.parametrize("general", [False, True])
+@pytest.mark.parametrize("bc", [(P, X), (P, P), (X, P)])
+@pytest.mark.parametrize("nx", [191, 192, 193])
+def test_row_ends_by_one_load_per_order(nx, bc, general):
+    """FP32 launches of 2048 waves and more, in tiles of whole waves per row, take
+    the x neighbours at row ends from one load per order: grids one point below,
+    at and above whole waves, on axes that wrap and that do not, in both parities
+    of the plain and the general sweep, for ranges of four, six and eight indices,
+    against tiles of half a wave per row.  Single runs and batches of two."""
+    shapes = {0: (64, 4), 6: (256, 2), 12: (512, 1)}
+    prob = _problem(13, (nx, 350), bc, general, "fp32")
+    init = _init(prob)
+    ref = _run(prob, init, 2, 8)
+    assert all(np.all(np.isfinite(a)) for a in ref) and all(np.any(a) for a in ref)
+    for v, (tx, ty) in shapes.items():
+        for width in (4, 6, 8):
+            chunks = -(-14 // width)
+            tiles = -(-(nx + (bc[0] == X)) // tx) * -(-(350 + (bc[1] == X)) // ty)
+            assert tiles * tx * ty * chunks >= 2048 * 64
+            for k, (a, b) in enumerate(zip(_run(prob, init, v, width), ref)):
+                assert np.array_equal(a, b), (v, width, k)
+    prob.t_final = 2e-2
+    runs = []
+    for v in (2, 0, 12):
+        solvers = [pa.Solver.from_problem(prob) for _ in range(2)]
+        for s in solvers:
+            for k, a in enumerate(init):
+                s.set_field_array(3, k, a)
+        b = pa.Batch(solvers)
+        b.set_variant(v, 6)
+        b.run()
+        runs.append([m for s in solvers for m in s.moments()])
+        b.close()
+    for got in runs[1:]:
+        for k, (a, b) in enumerate(zip(got, runs[0])):
+            assert np.array_equal(a, b), k
