@@ -29,9 +29,18 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 PMC_SUMMARY = os.path.join(ROOT, "profiles", "sweep_line_source_P39_1000_{}_pmc.json")
-SWEEP_SRC = [os.path.join(ROOT, "paper_1211_2205_amd", "csrc", f) for f in ("sweep.hip", "window.hip")]
+SWEEP_SRC = [os.path.join(ROOT, "paper_1211_2205_amd", "csrc", f) for f in ("sweep.hip", "window.hip", "window_order.hpp")]
 SIZE = {"fp64": 8, "fp32": 4, "bf16": 2}
 DTYPE = {"fp64": "f64", "fp32": "f32", "bf16": "bf16"}
+
+
+# FP64 tile variants whose window of input orders is in registers, as in every
+# variant of FP32 and BF16 storage
+REGISTER_VARIANTS64 = (4, 9, 12)
+
+
+def _sweep_kernel(precision, variant):
+    return "window_kernel" if precision != "fp64" or variant in REGISTER_VARIANTS64 else "sweep_kernel"
 
 
 def _sweep_source_hash():
@@ -325,7 +334,7 @@ def timed_run(prob, steps, warmup, variant=None, width=None):
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
                      "traffic": traffic,
-                     "kernel": "sweep_kernel", "avg_launch_ms": avg_ms,
+                     "kernel": _sweep_kernel(prec, v), "avg_launch_ms": avg_ms,
                      "algorithmic_bytes_per_launch": per_launch,
                      "algorithmic_bytes_odd": b_odd, "algorithmic_bytes_even": b_even,
                      # HBM bytes of the counter runs over this run's launch time,

@@ -248,24 +248,27 @@ int starmap_diagnostics(const starmap_solver* s, double* mass_r00, double* l2, d
 int starmap_diagnostics_noalloc(const starmap_solver* s, double* mass_r00, double* l2, double* maxabs,
                                 int32_t* nonfinite);
 
-/* Tile variant of the sweep kernel; by default chosen from the order, grid and
-   storage type at the first device call.
+/* Tile variant of the sweep kernel; by default chosen from the order, grid,
+   storage type, and with FP64 the decay planes and sources, at the first device
+   call.
    Variants differ in the spatial tile (tile_x x tile_y points) and, with FP64
    storage, in where the window of input orders is kept: in LDS (and then in
    how many planes of one order are held in registers while the next order
    loads) or in registers alone, as with FP32 and BF16 storage in every
-   variant; all give the same bits.  starmap_autotune times every variant that fits, at every
-   m-range width (4, 6, 8), on a few sweeps of this solver, keeps the fastest
-   pair and writes it to the cache file named by the environment variable
-   STARMAP_TUNE_CACHE (if set).  A line of that file names the tile its
+   variant; all give the same bits.  starmap_autotune times every variant that
+   fits, at every m-range width (4, 6, 8), on a few sweeps of this solver, keeps
+   the fastest pair and writes it to the cache file named by the environment
+   variable STARMAP_TUNE_CACHE (if set).  A line of that file names the tile its
    variant number stood for; lines that name none, or another one (the numbers
-   mean other tiles than they once did), are passed over.  Variants are 0 .. starmap_variant_count()-1;
-   another value fails with STARMAP_EINVAL.  The environment variable
+   mean other tiles than they once did), are passed over.  Variants are
+   0 .. starmap_variant_count()-1; -1 is the default, another value fails with
+   STARMAP_EINVAL.  The environment variable
    STARMAP_TILE_STRIP (read by starmap_create) sets
    the order in which workgroups take the tiles: k >= 2 strips of k tile
-   rows taken column by column (default 8), k <= -2 strips of -k tile
-   columns taken row by row, otherwise row by row; every order gives the
-   same bits. */
+   rows taken column by column, k <= -2 strips of -k tile columns taken row by
+   row, otherwise row by row (by default strips of 8 rows, or row by row where
+   the state is swept in registers out of the last-level cache); every order
+   gives the same bits. */
 int starmap_variant_count(void);
 int starmap_set_variant(starmap_solver* s, int32_t variant);
 int starmap_get_variant(const starmap_solver* s, int32_t* variant, int32_t* tile_x, int32_t* tile_y);
@@ -487,8 +490,11 @@ int starmap_reset(starmap_solver* s);
    launch of the network over all running instances followed by one batched
    odd sweep, or with fused solvers one launch of the fused closure kernel
    over all running instances; starmap_batch_run and starmap_batch_autotune
-   return STARMAP_EINVAL if the solvers' settings differ.  While in a batch, a solver's tile variant is the batch's: do not
-   call starmap_set_variant on it. */
+   return STARMAP_EINVAL if the solvers' settings differ.  While in a batch, a
+   solver's tile variant and m-range width are the batch's: do not call
+   starmap_set_variant, starmap_set_range_width or starmap_autotune on it.  They
+   stay after the batch until starmap_set_variant; -1 there gives the solver its
+   default tile and its own width back. */
 typedef struct starmap_batch starmap_batch;
 
 /* count >= 1 distinct solvers.  The array is copied. */

@@ -1950,7 +1950,9 @@ namespace detail {
 // The batch's device table: BatchEntry[count], WindowEntry[count] (an instance
 // has the one of its group's kernel), the plans' workgroup prefixes.
 size_t batch_window_offset(int count) { return align256(size_t(count) * sizeof(BatchEntry)); }
-size_t batch_first_offset(int count) { return batch_window_offset(count) + align256(size_t(count) * sizeof(WindowEntry)); }
+size_t batch_first_offset(int count) {
+  return batch_window_offset(count) + align256(size_t(count) * sizeof(WindowEntry));
+}
 size_t batch_table_bytes(int count, int ngroups) { return batch_first_offset(count) + size_t(count + ngroups) * 4; }
 size_t closure_table_bytes(int count) {
   return align256(size_t(count) * sizeof(ClosureInst)) + size_t(count + 1) * 4;
@@ -2035,7 +2037,8 @@ int batch_ready(starmap_batch* b) {
 int items_of(const starmap_solver* s) {
   const TileShape ts = sweep_variant(s->storage, s->variant);
   if (sweep_in_registers(s->storage, s->variant)) {
-    const WindowGrid g = window_grid(s->storage, s->nx, s->ny, s->px, s->py, ts.tx, ts.ty, s->N, window_nm(s->N, s->chunk_width));
+    const int nm = window_nm(s->N, s->chunk_width);
+    const WindowGrid g = window_grid(s->storage, s->nx, s->ny, s->px, s->py, ts.tx, ts.ty, s->N, nm);
     return window_order(g, tile_strip_of(s, false)).items;
   }
   const int ntx = (s->nx + 1 + ts.tx - 1) / ts.tx, nty = (s->ny + 1 + ts.ty - 1) / ts.ty;
@@ -2216,7 +2219,8 @@ int launch_plan(starmap_batch* b, const BatchPlan& g, int na, int j, hipStream_t
   if (sweep_in_registers(b->storage, g.variant)) {
     const TileShape ts = sweep_variant(b->storage, g.variant);
     const WindowEntry* tab = reinterpret_cast<const WindowEntry*>(base + batch_window_offset(count)) + g.tab0;
-    HIP_TRY(launch_window_batch(b->storage, tab, first, na, g.first[na], j, ts.tx, ts.ty, g.nm, g.max_stride, g.general, sweep_streams(b->state_bytes), stream));
+    HIP_TRY(launch_window_batch(b->storage, tab, first, na, g.first[na], j, ts.tx, ts.ty, g.nm, g.max_stride,
+                                g.general, sweep_streams(b->state_bytes), stream));
   } else {
     const BatchEntry* tab = reinterpret_cast<const BatchEntry*>(base) + g.tab0;
     HIP_TRY(launch_sweep_batch(g.variant, tab, first, na, g.first[na], j, g.slots, stream));

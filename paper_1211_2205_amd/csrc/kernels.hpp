@@ -123,7 +123,8 @@ struct WindowEntry {
   int pitch, nx, ny, px, py, N, nm, nsweeps, top_shift, pad;
 };
 // Sweep number j over the first n_active instances (arguments as
-// launch_sweep_batch); nm, max_stride: the largest of them; general: one of them needs it; streaming: as for all together.
+// launch_sweep_batch); nm, max_stride: the largest of them; general: one of them
+// needs it; streaming: as for all together.
 hipError_t launch_window_batch(int storage, const WindowEntry* table, const int* first, int n_active, int items, int j,
                                int tx, int ty, int nm, int64_t max_stride, bool general, bool streaming,
                                hipStream_t stream);

@@ -115,7 +115,8 @@ struct starmap_solver {
   int given_width = 0;           // ... that the user, the environment, the cache or the autotuner chose (0: none did)
   bool win_general = false;      // register-window sweep: per-order decay planes or sources beyond the zeroth moment's
   starmap::WindowPlanes win_planes[2];    // register-window sweep: planes by parity
-  int tile_strip = 0;            // tile order of the sweep: strips of k tile rows (k >= 2) or -k columns (k <= -2); 0: by tile_strip_of
+  // tile order of the sweep: strips of k tile rows (k >= 2) or -k columns (k <= -2); 0: by tile_strip_of
+  int tile_strip = 0;
   starmap::SweepProgram prog[2];
   bool prog_uploaded = false;
 

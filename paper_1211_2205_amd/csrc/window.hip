@@ -11,9 +11,10 @@
 // the x and y differences of the NM + 1 R and I planes of the input orders
 // l + 1 and l - 1 in the range.  The differences of order l + 1 are in
 // registers from the rows before; of each plane of order l - 1 the thread has
-// loaded its own points, the y neighbour and, but with FP64, the x neighbour
-// (kOverlap): it forms the plane's two differences, at once reloads the plane's registers with the
-// order two below, and updates the row whose last input that plane was.
+// loaded its own points and the y neighbour (the x neighbour is the next lane's
+// value, but in small FP32 launches: kOverlap and by_edge below): it forms the
+// plane's two differences, at once reloads the plane's registers with the order
+// two below, and updates the row whose last input that plane was.
 // Nothing is shared between threads: no LDS, no barrier, and every wave has a
 // whole order's planes and rows in flight while it computes the order before.
 //
@@ -77,6 +78,7 @@ constexpr int kPoints = sizeof(T) == 2 ? 2 : 1;
 // 317 x 203 FP32 7.2 -> 8.5).
 template <typename T>
 constexpr bool kOverlap = sizeof(T) == 8;
+constexpr int kPiece = 62;  // points of a row that a wave of overlapping tiles owns
 
 // With single points of four bytes and rows of whole waves (EDGE) the x neighbours
 // are the values of the next lanes too, but the tiles do not overlap: one load
@@ -195,14 +197,12 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
   int X;
   bool in;
   if constexpr (kOverlap<T>) {
-    // a piece of a row lies in one wave, and its end lanes stand on the points
-    // next to it; the last point of an axis that does not wrap needs none, nor
-    // does its first one, if it is a wave's first lane
-    const int lp = min(a.lbw, 6), last = (1 << lp) - 1, q = col & last;
-    const int lead = a.px || lp < 6 ? 1 : 0, x0 = ((txy.x << (a.lbw - lp)) + (col >> lp)) * (last - 1);
-    X = x0 + q - lead;
-    in = Y < rows && X < cols && (q > 0 || (!lead && X == 0)) && (q < last || (!a.px && X == a.nx)) &&
-         (x0 == 0 || x0 < cols - (a.px ? 0 : 2 - lead));  // (a piece that is one too many)
+    // a piece of a row is a wave's, and its end lanes stand on the points next to
+    // it; the first and the last point of an axis that does not wrap need none
+    const int q = col & 63, x0 = ((txy.x << (a.lbw - 6)) + (col >> 6)) * kPiece;
+    X = x0 + q - (a.px ? 1 : 0);
+    in = Y < rows && X < cols && (q > 0 || (!a.px && X == 0)) && (q < 63 || (!a.px && X == a.nx)) &&
+         (x0 == 0 || x0 < cols - (a.px ? 0 : 2));  // (a piece that is one too many)
     Y = min(Y, rows - 1);
   } else if constexpr (EDGE) {
     X = txy.x * bw + col;
@@ -546,7 +546,7 @@ window_kernel(T* __restrict__ U, const typename ComputeOf<T>::type* __restrict__
   using C = typename ComputeOf<T>::type;
   // (a launch of several runs of orders has one group)
   window_tile<T, NM, P, G, S, EDGE>(U, decay, (cptr<C>)coef, (cptr<int>)tab, a, a.nseg > 1 ? 0 : int(blockIdx.z),
-                              int(blockIdx.y), int(blockIdx.x), int(blockIdx.z));
+                                    int(blockIdx.y), int(blockIdx.x), int(blockIdx.z));
 }
 
 // WindowEntry as the device reads it (pointers with their address space, as
@@ -567,10 +567,9 @@ struct WindowEntryG {
 static_assert(sizeof(WindowEntryG) == sizeof(WindowEntry), "device view of WindowEntry");
 
 // Sweep number j of a batched run (instances and workgroup prefix as for the
-// LDS kernel); each instance brings its own width of m ranges, up to NMAX (a
-// batch of narrow ones needs fewer registers: 24 media of P_3 .. P_9 on 64^2 ..
-// 256^2 cells, FP32, 88 -> 75: with the shorter way to the first load 28 -> 26
-// us per sweep).
+// LDS kernel); each instance brings its own width of m ranges, up to NMAX: a
+// batch of narrow ones needs fewer registers (with the shorter way to the first
+// load, 24 media of P_3 .. P_9 on 64^2 .. 256^2 cells, FP32: 3.63 -> 3.43 ms).
 template <typename T, int NMAX, int P, bool G, bool S, bool EDGE>
 __global__ void __launch_bounds__(kMaxThreads<T>)
 window_batch_kernel(const WindowEntry* __restrict__ table, const int* __restrict__ first, const int n_active,
@@ -627,7 +626,8 @@ window_batch_kernel(const WindowEntry* __restrict__ table, const int* __restrict
 // 14.6 -> 11.7; BF16 P_9 64^2 6.0 -> 4.4, P_31 100^2 15.5 -> 11.8.  Beyond it
 // costs (FP32 P_7 128^2 in three 4.67, P_31 64^2 in three 9.0).  FP64, whose waves
 // load twice the bytes, gains with fewer: P_9 64^2 5.6 -> 5.1, P_39 64^2 19.7 ->
-// 16.5, but P_3 150^2 4.3 -> 4.55, P_7 128^2 5.6 -> 6.4; an order of the general
+// 16.5 in two (more, and smaller grids of P_16 and up, were not timed), but P_3
+// 150^2 4.3 -> 4.55, P_7 128^2 5.6 -> 6.4; an order of the general
 // kernel, with decay planes and sources to look up, takes longer (beam P_7 100^2
 // 7.4 -> 6.3, P_13 100^2 11.4 -> 9.5, P_7 128^2 7.7 -> 7.25; P_9 150^2 9.65 -> 9.9).
 int window_runs(int value_bytes, bool general, const WindowOrder& o, int waves_per_tile, int N) {
@@ -638,7 +638,7 @@ int window_runs(int value_bytes, bool general, const WindowOrder& o, int waves_p
     n = N >= 16                   ? (waves <= 1400 ? 2 : 1)
         : waves <= 400            ? 1200 / waves
         : general && waves <= 1000 ? 2
-                                  : 512 / waves;
+                                  : 1;
   else
     n = N >= 16 ? std::max(2400 / waves, waves <= 1650 ? 2 : 1) : 2048 / waves;
   return std::min(std::max(n, 1), N / 2 + 1);
@@ -700,7 +700,7 @@ hipError_t launch_t(int storage, const WindowArgs& w, hipStream_t stream) {
   a.N = w.N;
   a.top_shift = w.top_shift;
   a.tau = C(w.tau);
-  if (a.lbw < 0 || a.threads < 64 || a.threads > kMaxThreads<T>) return hipErrorInvalidValue;
+  if (a.lbw < (kOverlap<T> ? 6 : 0) || a.threads < 64 || a.threads > kMaxThreads<T>) return hipErrorInvalidValue;
   if (blocks1 < 1 || g.nchunks > 65535 || a.o.groups > 65535) return hipErrorInvalidValue;
   const dim3 blocks(unsigned(a.o.gsize), unsigned(g.nchunks), unsigned(a.nseg > 1 ? a.nseg : a.o.groups));
   T* u = static_cast<T*>(w.u);
@@ -709,7 +709,8 @@ hipError_t launch_t(int storage, const WindowArgs& w, hipStream_t stream) {
     hipLaunchKernelGGL(kernel, blocks, dim3(a.threads), 0, stream, u, d, cf, w.tab, a);
     return hipGetLastError();
   };
-  return by_flags<T>(w.parity, w.general, w.streaming, by_edge<T>(w.tx, NM, w.plane_stride, int64_t(blocks1) * a.threads),
+  const bool edge = by_edge<T>(w.tx, NM, w.plane_stride, int64_t(blocks1) * a.threads);
+  return by_flags<T>(w.parity, w.general, w.streaming, edge,
                      [&](auto p, auto g, auto s, auto e) {
                        return launch(&window_kernel<T, NM, decltype(p)::value, decltype(g)::value, decltype(s)::value,
                                                     decltype(e)::value>);
@@ -730,7 +731,7 @@ template <typename T, int NMAX>
 hipError_t launch_batch_t(const WindowEntry* table, const int* first, int n_active, int items, int j, int tx, int ty,
                           int64_t max_stride, bool general, bool streaming, hipStream_t stream) {
   const int lbw = log2_of(tx / kPoints<T>), threads = tx / kPoints<T> * ty;
-  if (lbw < 0 || threads < 64 || threads > kMaxThreads<T>) return hipErrorInvalidValue;
+  if (lbw < (kOverlap<T> ? 6 : 0) || threads < 64 || threads > kMaxThreads<T>) return hipErrorInvalidValue;
   auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(items), dim3(threads), 0, stream, table, first, n_active, j, lbw);
     return hipGetLastError();
@@ -763,15 +764,13 @@ int window_nm(int N, int width) {
 }
 
 WindowGrid window_grid(int storage, int nx, int ny, int px, int py, int tx, int ty, int N, int nm) {
-  // tiles over every point that lies on one of the grids.  With FP64 the end lanes of a row's pieces (64 lanes at most) stand on the points
-  // next to the piece, except at an end of the grid (window_tile).
+  // tiles over every point that lies on one of the grids.  With FP64 the end lanes
+  // of a row's pieces stand on the points next to the piece, except at an end of the
+  // grid (window_tile).
   WindowGrid g;
   const int cols = nx + 1 - px;
   if (storage == STORE_FP64) {
-    const int piece = tx < 64 ? tx : 64, own = piece - 2;
-    const int ends = px ? 0 : piece < 64 ? 1 : 2;
-    const int pieces = std::max(1, (cols - ends + own - 1) / own);
-    const int across = tx / piece;
+    const int pieces = std::max(1, (cols - (px ? 0 : 2) + kPiece - 1) / kPiece), across = std::max(1, tx / 64);
     g.ntx = (pieces + across - 1) / across;
   } else {
     g.ntx = (cols + tx - 1) / tx;
@@ -795,9 +794,15 @@ hipError_t launch_window_batch(int storage, const WindowEntry* table, const int*
                                hipStream_t stream) {
   if (n_active < 1 || items < 1) return hipErrorInvalidValue;
   switch (storage) {
-    case STORE_FP64: return launch_batch_nm<double>(nm, table, first, n_active, items, j, tx, ty, max_stride, general, streaming, stream);
-    case STORE_FP32: return launch_batch_nm<float>(nm, table, first, n_active, items, j, tx, ty, max_stride, general, streaming, stream);
-    case STORE_BF16: return launch_batch_nm<bf16>(nm, table, first, n_active, items, j, tx, ty, max_stride, general, streaming, stream);
+    case STORE_FP64:
+      return launch_batch_nm<double>(nm, table, first, n_active, items, j, tx, ty, max_stride, general, streaming,
+                                     stream);
+    case STORE_FP32:
+      return launch_batch_nm<float>(nm, table, first, n_active, items, j, tx, ty, max_stride, general, streaming,
+                                    stream);
+    case STORE_BF16:
+      return launch_batch_nm<bf16>(nm, table, first, n_active, items, j, tx, ty, max_stride, general, streaming,
+                                   stream);
   }
   return hipErrorInvalidValue;
 }
