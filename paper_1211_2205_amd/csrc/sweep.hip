@@ -636,7 +636,8 @@ bool sweep_streams(double state_bytes) { return state_bytes > kCache; }
 // P_3 1000^2 34 and 36; P_5 400^2 14.3 and 15.3; P_9 550^2 44 and 58; P_15 447^2
 // 62 and 77; P_31 150^2 36 and 59), but in LDS, above some 350^2 points,
 //   - where one or two orders cannot hide the loads of a large grid: 64 x 8
-//     (P_1 400^2 6.5, registers 6.9; 1000^2 17 and 24);
+//     (P_1 400^2 6.5, registers 6.9; 1000^2 17 and 24), for P_2 below 430^2 points
+//     32 x 8 (380^2 9.1, 64 x 8 9.7; 440^2 10.1 and 9.4);
 //   - where state and decay planes together leave the cache, and with them the y
 //     neighbours' lines the L1 before they are asked for: 32 x 8, up to P_3 64 x 8
 //     (P_39 500^2 557, registers 687; P_9 850^2 119 and 142; P_7 1000^2 89 and 132,
@@ -645,17 +646,18 @@ bool sweep_streams(double state_bytes) { return state_bytes > kCache; }
 //     the state alone counts from P_7 on with sources on more moments, which the
 //     LDS holds too: P_13 500^2 137 and 113), unless the LDS tiles are too few to
 //     fill the chip (P_39 200^2 118, registers 108);
-//   - up to P_6, whose few orders the general kernel's look-ups hold up most: with
-//     decay planes by order 32 x 8 (P_4 1000^2 47 and 66, 350^2 11.4 and 14.2; P_6
-//     700^2 41 and 50, but 350^2 21 and 20), P_3 from 800^2 on 64 x 8 (1000^2 34 and 44), and with sources
-//     on more moments P_4 (500^2 18 and 23, 1000^2 56 and 86), P_5 from 800^2 on
-//     (850^2 64 and 74, but 700^2 46 and 44) and P_3, P_2 (500^2 14.1 and 16.5; 400^2
-//     9.3, 64 x 8 10.1), these where the tiles' last round on the chip is nearly full
-//     (P_3 600^2 20.5 and 19.2) and the 64 x 8 tiles are not yet better (850^2 24.4
-//     and 22.9), and, but for P_4 with decay planes alone, no second round has just
-//     begun (a step of P_5 550^2 with changing media 351 and 323); of plain solvers P_4 likewise (500^2 15.1 and 18.1, 850^2 36.1 and
-//     37.1, but 600^2 23 and 21), and P_5 and P_6 where one round is just full
-//     (500^2 18.5 and 20.2, 23.0 and 24.4).
+//   - up to P_6, whose few orders the general kernel's look-ups hold up most.  With
+//     decay planes by order: 32 x 8 (P_4 1000^2 47 and 66, 350^2 11.4 and 14.2; P_6
+//     700^2 41 and 50, but 350^2 21 and 20), P_3 from 800^2 on 64 x 8 (1000^2 34 and
+//     44).  With sources on more moments: 32 x 8 for P_4 (500^2 18 and 23, 1000^2 56
+//     and 86), P_5 from 800^2 on (850^2 64 and 74, but 700^2 46 and 44), P_3 and P_2
+//     (500^2 14.1 and 16.5; 400^2 9.3, 64 x 8 10.1) where the tiles' last round on
+//     the chip is nearly full (P_3 600^2 20.5 and 19.2), P_2 below 770^2 (850^2 24.4,
+//     64 x 8 22.9).  But for P_4 with decay planes alone, not where a second round has
+//     just begun (three steps of P_5 550^2 in changing media 351 and 323);
+//   - for plain solvers of P_4 where the last round is nearly full (500^2 15.1 and
+//     18.1, 850^2 36.1 and 37.1, but 600^2 23 and 21), of P_5 and P_6 where one round
+//     is just full (500^2 18.5 and 20.2, 23.0 and 24.4).
 // FP32, BF16.  Large states on wide tiles, which read the fewest lines twice,
 // where the grid fills them (P_39 1000^2 FP32: 512 x 1 993, 128 x 2 1012; 500^2
 // 236 and 247), else
@@ -679,7 +681,7 @@ static int default_variant64(const SweepSizes& z) {
   bool lds = !cached;
   switch (z.N) {
     case 1: return 7;
-    case 2: return z.sources && points < 6.0e5 && (rounds <= 1.0 || full > 0.85) ? 8 : 7;
+    case 2: return points < 1.8e5 || (z.sources && points < 6.0e5 && (rounds <= 1.0 || full > 0.85)) ? 8 : 7;
     case 3:
       if (!general) return cached ? kNoLdsVariant : 7;
       if (!z.sources && points > 6.4e5) return 7;

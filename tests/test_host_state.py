@@ -187,7 +187,7 @@ def test_default_fp64_tiles_go_by_decay_planes_and_sources(program):
             (4, 300, True, True, window(6)), (4, 360, False, False, window(6)), (4, 360, True, False, lds(6)),
             (4, 360, False, True, lds(6)), (4, 500, False, False, lds(6)), (4, 600, False, False, window(6)),
             (3, 360, False, False, window(4)), (3, 360, True, False, lds(4)), (3, 360, True, True, window(4)),
-            (3, 500, True, True, lds(4)), (2, 360, False, False, (7, 4)), (2, 360, True, True, lds(4)), (2, 360, True, False, (7, 4)),
+            (3, 500, True, True, lds(4)), (2, 360, False, False, lds(4)), (2, 440, False, False, (7, 4)), (2, 360, True, True, lds(4)), (2, 440, True, False, (7, 4)),
             (5, 360, True, False, lds(6)), (5, 360, True, True, window(6)), (5, 500, False, False, lds(6)),
             (5, 480, False, False, window(6)), (6, 360, True, False, window(4)), (6, 390, True, False, lds(8)), (6, 360, True, True, window(4)),
             (7, 360, True, False, window(4)), (1, 360, True, True, (7, 4)),
