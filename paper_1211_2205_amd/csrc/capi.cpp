@@ -2039,7 +2039,7 @@ int items_of(const starmap_solver* s) {
   if (sweep_in_registers(s->storage, s->variant)) {
     const int nm = window_nm(s->N, s->chunk_width);
     const WindowGrid g = window_grid(s->storage, s->nx, s->ny, s->px, s->py, ts.tx, ts.ty, s->N, nm);
-    return window_order(g, tile_strip_of(s, false)).items;
+    return window_items(window_order(g, tile_strip_of(s, false)));
   }
   const int ntx = (s->nx + 1 + ts.tx - 1) / ts.tx, nty = (s->ny + 1 + ts.ty - 1) / ts.ty;
   return ntx * nty * int(s->prog[0].chunks.size());

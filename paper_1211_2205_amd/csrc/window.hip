@@ -173,8 +173,9 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
   constexpr int AUX = S ? kStream : 0;
   constexpr int NB = NM + 1;  // input planes of one order that the range needs, R and I each
 
-  const int tile = tile_number(a.o, grp, tl);
-  if (tile < 0) return;
+  const int gtiles = group_tiles(a.o, grp);
+  if (tl >= gtiles) return;
+  const int tile = tile_number(a.o, grp, uint32_t(gtiles), uint32_t(tl));
   int m0 = chunk * 2 * NM;
   const int ltop = a.N - ((a.N - P) & 1), lbot = m0 + P;
   if (lbot > ltop) return;  // no output rows in this m range

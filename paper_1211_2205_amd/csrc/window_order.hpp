@@ -40,8 +40,9 @@ struct WindowOrder {
   Divisor per, by_gsize;     // numbers per group and per range of a group
   Divisor band, rows, last;  // tiles per strip; a strip's width, the last strip's
   int ntx, nty, nchunks, strip, gsize, groups;
-  int items;                 // numbers in all
 };
+// Numbers in all.
+constexpr int window_items(const WindowOrder& o) { return o.groups * o.gsize * o.nchunks; }
 
 // Tiles of one group, about: the workgroups of a group are numbered range by
 // range, and the ranges of low m, which have the most orders, come first.
@@ -65,7 +66,6 @@ constexpr WindowOrder window_order(const WindowGrid& g, int strip) {
   const int per = (ntiles + o.groups - 1) / o.groups;
   o.gsize = o.groups > 1 ? (per + kXcds - 1) / kXcds * kXcds : ntiles;
   o.groups = (ntiles + o.gsize - 1) / std::max(o.gsize, 1);
-  o.items = o.groups * o.gsize * g.nchunks;
   o.per = divisor(o.gsize * g.nchunks);
   o.by_gsize = divisor(o.gsize);
   const int w = strip >= 2 ? strip : strip <= -2 ? -strip : 1;
@@ -76,15 +76,14 @@ constexpr WindowOrder window_order(const WindowGrid& g, int strip) {
   return o;
 }
 
-// Tile number of a group's member tl, or -1 (the last group may be smaller).
-// Consecutive workgroups run on the chip's XCDs in turn: each takes a run of
+// Tiles of a group (the last one may be smaller).
+constexpr int group_tiles(const WindowOrder& o, int grp) { return std::min(o.gsize, o.ntx * o.nty - grp * o.gsize); }
+// Tile number of member tl < n of a group of n tiles.  Consecutive workgroups run on the chip's XCDs in turn: each takes a run of
 // neighbouring tiles, whose shared rows its L2 then holds (P_9 317 x 203 FP32
 // 8.2 -> 7.5 us, P_7 280^2 FP64 14.6 -> 14.0, P_39 1000^2 BF16 528 -> 517).
-constexpr int tile_number(const WindowOrder& o, int grp, int tl) {
-  const int gtiles = std::min(o.gsize, o.ntx * o.nty - grp * o.gsize);
-  if (tl >= gtiles) return -1;
-  const uint32_t n = uint32_t(gtiles), t = uint32_t(tl), xcd = t % kXcds;
-  return grp * o.gsize + int(xcd * (n / kXcds) + std::min(xcd, n % kXcds) + t / kXcds);
+constexpr int tile_number(const WindowOrder& o, int grp, uint32_t n, uint32_t tl) {
+  const uint32_t xcd = tl % kXcds;
+  return grp * o.gsize + int(xcd * (n / kXcds) + std::min(xcd, n % kXcds) + tl / kXcds);
 }
 
 // Tile number t of the order (tile_xy of device.hpp with its divisors).

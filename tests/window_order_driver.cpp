@@ -14,7 +14,7 @@ int main(int argc, char** argv) {
   if (argc == 3 && !std::strcmp(argv[1], "groups")) {
     for (int n = 1; n <= std::atoi(argv[2]); ++n) {
       const WindowOrder o = window_order({n, 1, 3}, 1);
-      if (o.items != o.groups * o.gsize * 3 || (o.groups - 1) * o.gsize >= n || o.groups * o.gsize < n) {
+      if (window_items(o) != o.groups * o.gsize * 3 || (o.groups - 1) * o.gsize >= n || o.groups * o.gsize < n) {
         std::printf("%d tiles: %d groups of %d\n", n, o.groups, o.gsize);
         return 1;
       }
@@ -23,11 +23,11 @@ int main(int argc, char** argv) {
   }
   if (argc == 5 && !std::strcmp(argv[1], "tiles")) {
     const WindowOrder o = window_order({std::atoi(argv[2]), std::atoi(argv[3]), 2}, std::atoi(argv[4]));
-    for (int item = 0; item < o.items; ++item) {  // as the batched kernel takes them apart
+    for (int item = 0; item < window_items(o); ++item) {  // as the batched kernel takes them apart
       const int grp = divide(item, o.per), within = item - grp * (o.gsize * o.nchunks);
-      const int chunk = divide(within, o.by_gsize), t = tile_number(o, grp, within - chunk * o.gsize);
-      if (t < 0) continue;
-      const TileAt at = tile_at(t, o);
+      const int chunk = divide(within, o.by_gsize), tl = within - chunk * o.gsize, n = group_tiles(o, grp);
+      if (tl >= n) continue;
+      const TileAt at = tile_at(tile_number(o, grp, n, tl), o);
       std::printf("%d %d %d\n", chunk, at.x, at.y);
     }
     return 0;
