@@ -147,7 +147,7 @@ template <typename C>
 struct WindowScalars {
   uint32_t ps;  // plane stride in elements
   int pitch, nx, ny, px, py;
-  int lbw, threads;  // lanes per tile row (logarithm), threads per tile
+  int lbw, ty;       // lanes per tile row (logarithm), tile rows
   int nseg;          // runs of output orders
   Divisor by_nseg;
   WindowOrder o;     // m ranges and tiles
@@ -191,9 +191,8 @@ __device__ __forceinline__ void window_tile(T* __restrict__ U, const typename Co
   // this thread's points (X .. X + V - 1, Y)
   const TileAt txy = tile_at(tile, a.o);
   const int bw = 1 << a.lbw;
-  const int f = txy.y * a.threads + int(threadIdx.x);
-  int Y = f >> a.lbw;
-  const int col = f & (bw - 1);
+  int Y = row_of(txy, a.ty, a.lbw, int(threadIdx.x));
+  const int col = int(threadIdx.x) & (bw - 1);
   const int rows = a.ny + 1 - a.py, cols = a.nx + 1 - a.px;
   int X;
   bool in;
@@ -594,7 +593,7 @@ window_batch_kernel(const WindowEntry* __restrict__ table, const int* __restrict
   a.px = e.px;
   a.py = e.py;
   a.lbw = lbw;
-  a.threads = int(blockDim.x);
+  a.ty = int(blockDim.x) >> lbw;
   a.o = e.order;
   a.planes = e.planes[P];
   a.nseg = 1;
@@ -691,26 +690,27 @@ hipError_t launch_t(int storage, const WindowArgs& w, hipStream_t stream) {
   a.py = w.py;
   const int bw = w.tx / kPoints<T>;
   a.lbw = log2_of(bw);
-  a.threads = bw * w.ty;
+  a.ty = w.ty;
+  const int threads = bw * w.ty;
   const WindowGrid g = window_grid(storage, w.nx, w.ny, w.px, w.py, w.tx, w.ty, w.N, w.nm);
   a.o = window_order(g, w.strip);
   const int blocks1 = g.ntx * g.nty * g.nchunks;
-  a.nseg = window_runs(int(sizeof(T)), w.general != 0, a.o, a.threads / 64, w.N);
+  a.nseg = window_runs(int(sizeof(T)), w.general != 0, a.o, threads / 64, w.N);
   a.by_nseg = divisor(a.nseg);
   a.planes = w.planes;
   a.N = w.N;
   a.top_shift = w.top_shift;
   a.tau = C(w.tau);
-  if (a.lbw < (kOverlap<T> ? 6 : 0) || a.threads < 64 || a.threads > kMaxThreads<T>) return hipErrorInvalidValue;
+  if (a.lbw < (kOverlap<T> ? 6 : 0) || threads < 64 || threads > kMaxThreads<T>) return hipErrorInvalidValue;
   if (blocks1 < 1 || g.nchunks > 65535 || a.o.groups > 65535) return hipErrorInvalidValue;
   const dim3 blocks(unsigned(a.o.gsize), unsigned(g.nchunks), unsigned(a.nseg > 1 ? a.nseg : a.o.groups));
   T* u = static_cast<T*>(w.u);
   const C *d = static_cast<const C*>(w.decay), *cf = static_cast<const C*>(w.coef);
   auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, blocks, dim3(a.threads), 0, stream, u, d, cf, w.tab, a);
+    hipLaunchKernelGGL(kernel, blocks, dim3(threads), 0, stream, u, d, cf, w.tab, a);
     return hipGetLastError();
   };
-  const bool edge = by_edge<T>(w.tx, NM, w.plane_stride, int64_t(blocks1) * a.threads);
+  const bool edge = by_edge<T>(w.tx, NM, w.plane_stride, int64_t(blocks1) * threads);
   return by_flags<T>(w.parity, w.general, w.streaming, edge,
                      [&](auto p, auto g, auto s, auto e) {
                        return launch(&window_kernel<T, NM, decltype(p)::value, decltype(g)::value, decltype(s)::value,

@@ -105,4 +105,8 @@ constexpr TileAt tile_at(int t, const WindowOrder& o) {
   return {t - band * o.ntx, band};
 }
 
+// Row of the grid that a thread of a tile of ty rows stands on: 2^lbw lanes per
+// row.  (Rows times lanes may exceed an int.)
+constexpr int row_of(const TileAt& tile, int ty, int lbw, int thread) { return tile.y * ty + (thread >> lbw); }
+
 }  // namespace starmap

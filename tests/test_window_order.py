@@ -28,6 +28,11 @@ def test_no_group_is_empty_or_missing(driver):
     assert r.returncode == 0, r.stdout + r.stderr
 
 
+def test_rows_of_the_tallest_grids(driver):
+    r = subprocess.run([driver, "rows"], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
 @pytest.mark.parametrize("strip", [0, 1, 8, -8, 5, -3, 1000])
 @pytest.mark.parametrize("ntx,nty", [(1, 1), (3, 1), (7, 9), (8, 64), (1, 767), (24, 32), (769, 1), (31, 33),
                                      (23, 1471), (24, 1473), (33793, 1), (1, 33793), (42, 1301)])

@@ -1,6 +1,8 @@
 // Enumerates the workgroup numbering of register-window sweeps on the host.
 //   groups MAX            for every number of tiles up to MAX: groups of gsize
 //                         tiles, none of them empty, hold each tile once
+//   rows                  tiles of every shape on the last rows that planes of 2^31
+//                         bytes leave room for: each row once, in order
 //   tiles NTX NTY STRIP   prints "x y" of every tile in the order of the numbers
 #include <cstdio>
 #include <cstdlib>
@@ -19,6 +21,21 @@ int main(int argc, char** argv) {
         return 1;
       }
     }
+    return 0;
+  }
+  if (argc == 2 && !std::strcmp(argv[1], "rows")) {
+    const int last = int((int64_t(1) << 31) / (64 * 4));  // rows of 64 values, the shortest, of four bytes
+    for (int threads = 64; threads <= 512; threads *= 2)
+      for (int lbw = 3; (1 << lbw) <= threads; ++lbw) {
+        const int ty = threads >> lbw;
+        for (int y = last / ty - 2; y <= last / ty; ++y)
+          for (int t = 0; t < threads; ++t)
+            if (row_of({0, y}, ty, lbw, t) != y * ty + t / (1 << lbw)) {
+              std::printf("%d threads, %d per row, tile row %d: %d\n", threads, 1 << lbw, y,
+                          row_of({0, y}, ty, lbw, t));
+              return 1;
+            }
+      }
     return 0;
   }
   if (argc == 5 && !std::strcmp(argv[1], "tiles")) {
