@@ -4,6 +4,8 @@ of the m ranges, sources and decay planes of every order, launches of fewer
 workgroups than compute units (orders split into runs) and more, a value that
 is not finite.  FP64 variants run the same operations in the same order with
 the window in registers or in LDS, so they must agree bit for bit."""
+import os
+
 import numpy as np
 import pytest
 
@@ -240,3 +242,60 @@ def test_row_ends_by_one_load_per_order(nx, bc, general):
     for got in runs[1:]:
         for k, (a, b) in enumerate(zip(got, runs[0])):
             assert np.array_equal(a, b), k
+
+
+def _model(kind):
+    if kind == "filtered":
+        p = wl.checkerboard(N=6, n=45, t_final=0.3)
+        p.filter_damping = wl.filter_damping(6, 8.0, power=4)
+    elif kind == "changing media":
+        p = wl.pulsed_medium(37, 4, 41)
+    elif kind == "diffusion":
+        p = wl.checkerboard(N=3, n=39, t_final=0.3)
+        p.diffusion = lambda t, x, y: 0.002 + 0.0 * x
+    else:
+        p = wl.closure_instance(3, 5, 50)
+    p.precision = "fp64"
+    return p
+
+
+@pytest.mark.parametrize("kind", ["filtered", "changing media", "diffusion", "closure", "fused closure"])
+def test_models_with_either_window(kind):
+    """The default FP64 tile of a model's larger grids is an LDS one, of its smaller
+    ones a register window: both give the same bits, over split advances, and for
+    closures (whose fused odd sweep moves the order-5 moments) in batches too."""
+    weights = np.load(os.path.join(os.path.dirname(pa.__file__), "weights", "closure_p5_256.npy"))
+
+    def solver():
+        s = pa.Solver.from_problem(_model(kind), closure="learned" if "closure" in kind else "pn")
+        s.bind_torch()
+        if "closure" in kind:
+            s.load_closure(weights)
+            s.set_closure_fused(kind == "fused closure")
+        return s
+
+    runs = []
+    for v, width in ((12, 4), (8, 6), (7, 4), (8, 8)):
+        s = solver()
+        s.set_variant(v)
+        s.set_chunk_width(width)
+        for k in (1, 4, 2):
+            s.advance(k)
+        runs.append(s.moments())
+        s.close()
+    assert any(np.any(a) for a in runs[0])
+    for i, got in enumerate(runs[1:]):
+        for k, (a, b) in enumerate(zip(got, runs[0])):
+            assert np.array_equal(a, b), (i, k)
+    if "closure" not in kind:
+        return
+    ends = []
+    for v in (12, 8):
+        pair = [solver(), solver()]
+        b = pa.Batch(pair)
+        b.set_variant(v, 6)
+        b.run()
+        ends.append([m for s in pair for m in s.moments()])
+        b.close()
+    for k, (a, b) in enumerate(zip(*ends)):
+        assert np.array_equal(a, b), k
